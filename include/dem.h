@@ -267,9 +267,9 @@ dem_status dem_time_forces(dem_handle h, int32_t reps, double *mean_ms);
  * bit for bit): lanes_per_pair (8 or 16) lanes evaluate one particle pair in
  * the feature stage, so a 64-lane wavefront takes 8 or 4 pairs at a time;
  * the grid holds grid_factor (1 to 4) times as many workgroups as the
- * device keeps resident at once; the kernel is compiled for waves_per_simd
- * (2 or 3) resident wavefronts per SIMD (3 overlaps more memory round
- * trips, 2 gives the compiler more registers); and sep_lanes (4, or 16 with
+ * device keeps resident at once; waves_per_simd (2 or 3) is kept so that
+ * calls stay valid: one build, for 3 resident wavefronts per SIMD, serves
+ * both; and sep_lanes (4, or 16 with
  * 16 lanes per pair) lanes take one pair in the separation stage, so a
  * wavefront settles 16 or 4 pairs at a time and a tile holds 64 or 16
  * pairs (16 spreads a small system over four times the wavefronts).
@@ -279,7 +279,7 @@ dem_status dem_time_forces(dem_handle h, int32_t reps, double *mean_ms);
  * compacts the pairs no supporting plane separates, per replica, into a
  * buffer as large as the pair entries; a force kernel then gives each
  * wavefront one feature round of those pairs (lanes_per_pair and
- * waves_per_simd apply to it; grid_factor does not).  The default is
+ * applies to it; grid_factor does not).  The default is
  * {16, 1, 2, 4, 0}.  The next dem_step captures its graph again.
  * DEM_E_ARG for other values. */
 enum { DEM_PAIR_SHAPES = 16 };

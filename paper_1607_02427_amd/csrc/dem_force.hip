@@ -67,7 +67,7 @@ __device__ inline V3<T> cross(V3<T> a, V3<T> b)
     return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 template <typename T>
-__device__ inline V3<T> ld3(const T (&a)[3]) { return {a[0], a[1], a[2]}; }
+__device__ inline V3<T> xyz(const Vec4<T> &a) { return {a.x, a.y, a.z}; }
 template <typename T>
 __device__ inline T clamp01(T t) { return t < T(0) ? T(0) : (t > T(1) ? T(1) : t); }
 template <typename T, typename U>
@@ -95,6 +95,13 @@ __device__ inline V3<T> mulT(const M3<T> &R, V3<T> v)
 // rounding error of one FP32 multiply, so truncation is exact.
 __device__ inline int qdiv(int q, float inv_d) { return (int)(((float)q + 0.5f) * inv_d); }
 
+// Signed distance of v beyond a plane (unit normal, offset).
+template <typename T>
+__device__ inline T plane_gap(const Vec4<T> &pl, V3<T> v)
+{
+    return dot(xyz(pl), v) - pl.w;
+}
+
 // Nearest point of the closed segment a + t u (t in [0,1]) to p.
 template <typename T>
 __device__ inline V3<T> seg_point(V3<T> p, V3<T> a, V3<T> u, T inv_uu)
@@ -102,31 +109,36 @@ __device__ inline V3<T> seg_point(V3<T> p, V3<T> a, V3<T> u, T inv_uu)
     return a + clamp01(dot(p - a, u) * inv_uu) * u;
 }
 
-// Nearest point of face f of shape S to p, both in S's body frame: the
+// Nearest point of a face of shape S to p, both in S's body frame: the
 // projection if it is inside the closed polygon (in-plane half-spaces for
 // convex faces, crossing number for concave ones), else the nearest point of
-// the face's own boundary edges.  The face's loop (foff, floop, fconvex) is
-// read from `top`, a table of the same shape that may sit in faster memory
-// than S (the FP32 table in LDS beside the FP64 one in global memory); the
-// loops are unrolled and free of early exits, so the loads of a face's
-// loop entries are issued together instead of one round trip each.
-template <typename T, typename TT>
-__device__ inline V3<T> face_point(const TT &top, const ShapeTab<T> &S, int f, V3<T> p)
+// the face's own boundary edges.  fi is the face's packed loop range, which
+// the FP64 redo reads from the FP32 table in LDS.  The loops take kU loop
+// entries at a time with no branch between them, so their loads are issued
+// together; entries past the last repeat it, which changes neither the test
+// nor the strict minimum.
+template <typename T>
+__device__ inline V3<T> face_point(const ShapeTab<T> &S, int f, int fi, V3<T> p)
 {
-    // unrolled where S is in global memory or FP32 (registers allow it)
-    constexpr int kU = (sizeof(T) == 8 && sizeof(TT) == sizeof(ShapeTab<T>)) ? 1 : 4;
-    const V3<T> n = ld3(S.fn[f]);
-    const T sd = dot(n, p) - S.fo[f];
-    const int k0 = top.foff[f], k1 = top.foff[f + 1];
+    constexpr int kU = sizeof(T) == 8 ? 2 : 4;
+    const Vec4<T> nf = S.fn[f];
+    const V3<T> n = xyz(nf);
+    const T sd = dot(n, p) - nf.w;
+    const int k0 = face_first(fi), k1 = face_end(fi);
     bool inside;
-    if (top.fconvex[f]) {
+    if (face_convex(fi)) {
         inside = true;
-#pragma unroll kU
-        for (int k = k0; k < k1; ++k) inside &= dot(ld3(S.lnrm[k]), p) >= S.loff[k];
+        for (int k = k0; k < k1; k += kU) {
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const Vec4<T> l = S.ln[k + u < k1 ? k + u : k1 - 1];
+                inside &= dot(xyz(l), p) >= l.w;
+            }
+        }
     } else {
-        const V3<T> e1 = ld3(S.fe1[f]);
+        const V3<T> e1 = xyz(S.fe1[f]);
         const V3<T> e2 = cross(n, e1);
-        const V3<T> o = ld3(S.v[top.floop[k0]]);
+        const V3<T> o = xyz(S.lv[k0]);
         const T px = dot(p - o, e1), py = dot(p - o, e2);
         inside = false;
         for (int k = k0; k < k1; ++k) {
@@ -141,16 +153,19 @@ __device__ inline V3<T> face_point(const TT &top, const ShapeTab<T> &S, int f, V
     if (inside) return p - sd * n;
     T best = T(3.0e38);
     V3<T> q = p;
-#pragma unroll kU
-    for (int k = k0; k < k1; ++k) {
-        const int kn = (k + 1 < k1) ? k + 1 : k0;
-        const V3<T> a = ld3(S.v[top.floop[k]]);
-        const V3<T> c = seg_point(p, a, ld3(S.v[top.floop[kn]]) - a, S.linv[k]);
-        const V3<T> d = p - c;
-        const T d2 = dot(d, d);
-        if (d2 < best) {
-            best = d2;
-            q = c;
+    for (int k = k0; k < k1; k += kU) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int ku = k + u < k1 ? k + u : k1 - 1;
+            const Vec4<T> a4 = S.lv[ku];
+            const V3<T> a = xyz(a4);
+            const V3<T> c = seg_point(p, a, xyz(S.lv[ku + 1 < k1 ? ku + 1 : k0]) - a, a4.w);
+            const V3<T> d = p - c;
+            const T d2 = dot(d, d);
+            if (d2 < best) {
+                best = d2;
+                q = c;
+            }
         }
     }
     return q;
@@ -200,17 +215,22 @@ constexpr int kVirt = 16;
 __device__ inline float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ inline double rcp(double x) { return 1.0 / x; }
 
+__device__ inline unsigned plane_bits(float w) { return __float_as_uint(w); }
+__device__ inline unsigned plane_bits(double w) { return (unsigned)__double_as_longlong(w); }
+__device__ inline void set_plane_bits(float &w, unsigned m) { w = __uint_as_float(m); }
+__device__ inline void set_plane_bits(double &w, unsigned m) { w = __longlong_as_double((long long)m); }
+
 template <typename T>
-struct PairLds {
-    T vj[DEM_MAX_VERTS][3];   // j's vertices in i's frame
-    T vi[DEM_MAX_VERTS][3];   // i's vertices in j's frame
+struct alignas(16) PairLds {
+    // j's vertices in i's frame and i's in j's; w: the supporting planes of
+    // the other body that the vertex lies more than r_cut beyond (bit p:
+    // plane p), as bits (plane_bits)
+    Vec4<T> vj[DEM_MAX_VERTS];
+    Vec4<T> vi[DEM_MAX_VERTS];
     // features that can reach the other body (conservative prefilter), by index
     unsigned char vi_near[DEM_MAX_VERTS], vj_near[DEM_MAX_VERTS];
     unsigned char ei_near[DEM_MAX_EDGES], ej_near[DEM_MAX_EDGES];
     unsigned char fi_near[DEM_MAX_FACES], fj_near[DEM_MAX_FACES];
-    // supporting planes of the other body that each vertex lies more than
-    // r_cut beyond (bit p: plane p)
-    unsigned vib[DEM_MAX_VERTS], vjb[DEM_MAX_VERTS];
     unsigned short queue[kQueue];
     // the pair's problem counts and queue length, for the lanes of other
     // groups that solve its problems in the pooled solve (16 lanes per pair)
@@ -322,11 +342,11 @@ struct Problem {
             if (lo < nA) {
                 fam = 0;
                 x = W.vi_near[lo];
-                m = W.vib[x];
+                m = plane_bits(W.vi[x].w);
             } else if (lo < nA + nB) {
                 fam = 1;
                 x = W.vj_near[lo - nA];
-                m = W.vjb[x];
+                m = plane_bits(W.vj[x].w);
             } else {
                 fam = 2;
                 x = W.ei_near[lo - nA - nB];
@@ -375,31 +395,33 @@ struct Problem {
     {
         int fam, x, y;
         decode(q, fam, x, y);
+        const ShapeTab<T> &S = fam == 0 ? Sj : Si;  // the face's (2D: edge's) owner
         if (DIM == 3) {
             if (fam < 2) {  // vertex against face, in the face owner's frame
-                const ShapeTab<T> &S = fam == 0 ? Sj : Si;
-                const V3<T> pt = fam == 0 ? ld3(W.vi[x]) : ld3(W.vj[x]);
-                const T sd = dot(ld3(S.fn[y]), pt) - S.fo[y];
-                const V3<T> dc = pt - ld3(S.fc[y]);
-                const T lim = S.frad[y] + rc;
+                const V3<T> pt = xyz(fam == 0 ? W.vi[x] : W.vj[x]);
+                const Vec4<T> nf = S.fn[y], fc = S.fc[y];
+                const T sd = dot(xyz(nf), pt) - nf.w;
+                const V3<T> dc = pt - xyz(fc);
+                const T lim = fc.w + rc;
                 return fabs(sd) < rc && dot(dc, dc) < lim * lim;
             }
             // edge against edge: bounding spheres of the two segments, then,
             // unless they are close to parallel, the distance between their
             // lines (a lower bound of the segments' distance)
-            const V3<T> a = ld3(W.vj[Sj.e[y][0]]), d2 = ld3(W.vj[Sj.e[y][1]]) - a;
-            const V3<T> dm = ld3(Si.em[x]) - (a + T(0.5) * d2);
-            const T lim = Si.eh[x] + Sj.eh[y] + rc;
+            const V3<T> a = xyz(W.vj[Sj.e[y][0]]), d2 = xyz(W.vj[Sj.e[y][1]]) - a;
+            const Vec4<T> em = Si.em[x];
+            const V3<T> dm = xyz(em) - (a + T(0.5) * d2);
+            const T lim = em.w + Sj.em[y].w + rc;
             if (!(dot(dm, dm) < lim * lim)) return false;
-            const V3<T> d1 = ld3(Si.ed[x]);
+            const V3<T> d1 = xyz(Si.ed[x]);
             const V3<T> n = cross(d1, d2);
             const T nn = dot(n, n);
-            const T rn = dot(ld3(Si.em[x]) - a, n);
-            return !(nn > T(1e-4) * Si.el2[x] * dot(d2, d2) && rn * rn > T(1.001) * rc * rc * nn);
+            const T rn = dot(xyz(em) - a, n);
+            return !(nn > T(1e-4) * Si.ea[x].w * dot(d2, d2) && rn * rn > T(1.001) * rc * rc * nn);
         } else {  // vertex against edge, in the edge owner's frame
-            const ShapeTab<T> &S = fam == 0 ? Sj : Si;
-            const V3<T> dm = (fam == 0 ? ld3(W.vi[x]) : ld3(W.vj[x])) - ld3(S.em[y]);
-            const T lim = S.eh[y] + rc;
+            const Vec4<T> em = S.em[y];
+            const V3<T> dm = xyz(fam == 0 ? W.vi[x] : W.vj[x]) - xyz(em);
+            const T lim = em.w + rc;
             return dot(dm, dm) < lim * lim;
         }
     }
@@ -413,23 +435,33 @@ struct Problem {
         ex = x;
         ey = y;
         sin2 = T(1);
-        if (fam == 0) {
-            const V3<T> pt = ld3(W.vi[x]);
-            P = ld3(Si.v[x]);
-            const V3<T> qj = (DIM == 3) ? face_point(Sj, Sj, y, pt)
-                                        : seg_point(pt, ld3(Sj.v[Sj.e[y][0]]), ld3(Sj.ed[y]), Sj.einv[y]);
-            rho = mul(Rr, pt - qj);  // offset formed in j's frame, then rotated
-        } else if (fam == 1) {
-            const V3<T> pt = ld3(W.vj[x]);
-            P = (DIM == 3) ? face_point(Si, Si, y, pt) : seg_point(pt, ld3(Si.v[Si.e[y][0]]), ld3(Si.ed[y]), Si.einv[y]);
-            rho = P - pt;
+        if (fam < 2) {
+            // both vertex families in one path, the operands selected, so a
+            // wavefront that holds both runs the face search once
+            const ShapeTab<T> &S = fam == 0 ? Sj : Si;
+            const V3<T> pt = xyz(fam == 0 ? W.vi[x] : W.vj[x]);
+            V3<T> c;
+            if (DIM == 3) {
+                c = face_point(S, y, S.fi[y], pt);
+            } else {
+                const Vec4<T> ed = S.ed[y];
+                c = seg_point(pt, xyz(S.ea[y]), xyz(ed), ed.w);
+            }
+            if (fam == 0) {
+                P = xyz(Si.v[x]);
+                rho = mul(Rr, pt - c);  // offset formed in j's frame, then rotated
+            } else {
+                P = c;
+                rho = P - pt;
+            }
         } else {
-            const V3<T> b0 = ld3(W.vj[Sj.e[y][0]]);
-            const V3<T> d2 = ld3(W.vj[Sj.e[y][1]]) - b0;
+            const V3<T> b0 = xyz(W.vj[Sj.e[y][0]]);
+            const V3<T> d2 = xyz(W.vj[Sj.e[y][1]]) - b0;
+            const Vec4<T> a = Si.ea[x], d1 = Si.ed[x];
+            const T e = Sj.ea[y].w, ie = Sj.ed[y].w;
             V3<T> Q;
-            const T den = seg_seg(ld3(Si.v[Si.e[x][0]]), ld3(Si.ed[x]), Si.el2[x], Si.einv[x], b0, d2, Sj.el2[y],
-                                  Sj.einv[y], par_s2, P, Q);
-            sin2 = den * Si.einv[x] * Sj.einv[y];
+            const T den = seg_seg(xyz(a), xyz(d1), a.w, d1.w, b0, d2, e, ie, par_s2, P, Q);
+            sin2 = den * d1.w * ie;
             rho = P - Q;
         }
         return fam;
@@ -525,8 +557,8 @@ __device__ inline bool fp32_unresolved(int fam, T r2, T rc2, T rc, T sin2, V3<T>
 // of the cutoff, where the force is a steep function of the distance
 // (dF/dr = 72 eps / r_cut^2 there), and for nearly parallel edges, whose
 // closest points are ill-conditioned (error ~ eps / sin).  Returns 1 if the
-// pair is inside the cutoff.  Indices (edge ends, face loops) are read from
-// the FP32 tables Ti, Tj in LDS, coordinates from the FP64 tables Di, Dj.
+// pair is inside the cutoff.  Face loop ranges are read from the FP32 tables
+// Ti, Tj in LDS, coordinates from the FP64 tables Di, Dj.
 template <typename T, int DIM>
 __device__ int refine_pair(const double *box, double eps, double par_s2, const PartRec64 &ri, const PartRec64 &rj,
                            const ShapeTab<T> &Ti, const ShapeTab<T> &Tj, const ShapeTab<double> &Di,
@@ -544,22 +576,37 @@ __device__ int refine_pair(const double *box, double eps, double par_s2, const P
                                      DIM == 3 ? min_image_near(rj.z - ri.z, box[2]) : 0.0);
     const V3<double> td = qrot(qi, dd);
     V3<double> P, rho;
-    if (fam == 0) {
-        const V3<double> pt = qrot(qrc, ld3(Di.v[x]) - td);  // i's vertex in j's frame
-        const V3<double> q = (DIM == 3) ? face_point(Tj, Dj, y, pt)
-                                        : seg_point(pt, ld3(Dj.v[Tj.e[y][0]]), ld3(Dj.ed[y]), Dj.einv[y]);
-        P = ld3(Di.v[x]);
-        rho = qrot(qr, pt - q);
-    } else if (fam == 1) {
-        const V3<double> pt = td + qrot(qr, ld3(Dj.v[x]));  // j's vertex in i's frame
-        P = (DIM == 3) ? face_point(Ti, Di, y, pt) : seg_point(pt, ld3(Di.v[Ti.e[y][0]]), ld3(Di.ed[y]), Di.einv[y]);
-        rho = P - pt;
+    if (fam < 2) {
+        // one path for both vertex families: i's vertex in j's frame, or j's
+        // in i's
+        const bool A0 = fam == 0;
+        const ShapeTab<double> &D = A0 ? Dj : Di;
+        const ShapeTab<T> &F = A0 ? Tj : Ti;
+        const V3<double> vx = xyz(A0 ? Di.v[x] : Dj.v[x]);
+        double qs[4];
+        for (int k = 0; k < 4; ++k) qs[k] = A0 ? qrc[k] : qr[k];
+        const V3<double> rv = qrot(qs, A0 ? vx - td : vx);
+        const V3<double> pt = A0 ? rv : td + rv;
+        V3<double> c;
+        if (DIM == 3) {
+            c = face_point(D, y, F.fi[y], pt);
+        } else {
+            const Vec4<double> ed = D.ed[y];
+            c = seg_point(pt, xyz(D.ea[y]), xyz(ed), ed.w);
+        }
+        if (A0) {
+            P = vx;
+            rho = qrot(qr, pt - c);
+        } else {
+            P = c;
+            rho = P - pt;
+        }
     } else {
-        const V3<double> b0 = td + qrot(qr, ld3(Dj.v[Tj.e[y][0]]));
-        const V3<double> d2 = qrot(qr, ld3(Dj.ed[y]));
+        const Vec4<double> a = Di.ea[x], d1 = Di.ed[x], b = Dj.ea[y], db = Dj.ed[y];
+        const V3<double> b0 = td + qrot(qr, xyz(b));
+        const V3<double> d2 = qrot(qr, xyz(db));
         V3<double> Q;
-        seg_seg(ld3(Di.v[Ti.e[x][0]]), ld3(Di.ed[x]), Di.el2[x], Di.einv[x], b0, d2, Dj.el2[y], Dj.einv[y], par_s2,
-                P, Q);
+        seg_seg(xyz(a), xyz(d1), a.w, d1.w, b0, d2, b.w, db.w, par_s2, P, Q);
         rho = P - Q;
     }
     const double rc = kWcaCut * sig;
@@ -835,25 +882,23 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 const int vk = v0 + sub;
                 bool nj = false, ni = false;
                 if (live && vk < Sj.nv) {
-                    const V3<T> v = t + mul(Rr, ld3(Sj.v[vk]));
-                    W.vj[vk][0] = v.x;
-                    W.vj[vk][1] = v.y;
-                    W.vj[vk][2] = v.z;
+                    const V3<T> v = t + mul(Rr, xyz(Sj.v[vk]));
                     unsigned mb = 0;
 #pragma unroll 4
-                    for (int p = 0; p < Si.nsep; ++p) mb |= (dot(ld3(Si.sn[p]), v) - Si.so[p] > thr ? 1u : 0u) << p;
-                    W.vjb[vk] = mb;
+                    for (int p = 0; p < Si.nsep; ++p) mb |= (plane_gap(Si.sp[p], v) > thr ? 1u : 0u) << p;
+                    Vec4<T> v4 = {v.x, v.y, v.z, T(0)};
+                    set_plane_bits(v4.w, mb);
+                    W.vj[vk] = v4;
                     nj = mb == 0 && dot(v, v) < grow * Bi * Bi;
                 }
                 if (live && vk < Si.nv) {
-                    const V3<T> v = mulT(Rr, ld3(Si.v[vk]) - t);
-                    W.vi[vk][0] = v.x;
-                    W.vi[vk][1] = v.y;
-                    W.vi[vk][2] = v.z;
+                    const V3<T> v = mulT(Rr, xyz(Si.v[vk]) - t);
                     unsigned mb = 0;
 #pragma unroll 4
-                    for (int p = 0; p < Sj.nsep; ++p) mb |= (dot(ld3(Sj.sn[p]), v) - Sj.so[p] > thr ? 1u : 0u) << p;
-                    W.vib[vk] = mb;
+                    for (int p = 0; p < Sj.nsep; ++p) mb |= (plane_gap(Sj.sp[p], v) > thr ? 1u : 0u) << p;
+                    Vec4<T> v4 = {v.x, v.y, v.z, T(0)};
+                    set_plane_bits(v4.w, mb);
+                    W.vi[vk] = v4;
                     ni = mb == 0 && dot(v, v) < grow * Bj * Bj;
                 }
                 cvj = group_append(nj, W.vj_near, cvj, vk, gmask);
@@ -865,14 +910,16 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 const int e = e0 + sub;
                 bool ne = false, me = false;
                 if (live && e < Si.ne) {
-                    const V3<T> d = ld3(Si.em[e]) - t;
-                    const T lim = Bj + Si.eh[e];
-                    ne = (W.vib[Si.e[e][0]] & W.vib[Si.e[e][1]]) == 0 && dot(d, d) < grow * lim * lim;
+                    const Vec4<T> em = Si.em[e];
+                    const V3<T> d = xyz(em) - t;
+                    const T lim = Bj + em.w;
+                    ne = (plane_bits(W.vi[Si.e[e][0]].w) & plane_bits(W.vi[Si.e[e][1]].w)) == 0 && dot(d, d) < grow * lim * lim;
                 }
                 if (live && e < Sj.ne) {
-                    const V3<T> m = T(0.5) * (ld3(W.vj[Sj.e[e][0]]) + ld3(W.vj[Sj.e[e][1]]));
-                    const T lim = Bi + Sj.eh[e];
-                    me = (W.vjb[Sj.e[e][0]] & W.vjb[Sj.e[e][1]]) == 0 && dot(m, m) < grow * lim * lim;
+                    const Vec4<T> a = W.vj[Sj.e[e][0]], b = W.vj[Sj.e[e][1]];
+                    const V3<T> m = T(0.5) * (xyz(a) + xyz(b));
+                    const T lim = Bi + Sj.em[e].w;
+                    me = (plane_bits(a.w) & plane_bits(b.w)) == 0 && dot(m, m) < grow * lim * lim;
                 }
                 cei = group_append(ne, W.ei_near, cei, e, gmask);
                 cej = group_append(me, W.ej_near, cej, e, gmask);
@@ -884,19 +931,23 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     const int f = f0 + sub;
                     bool nf = false, mf = false;
                     if (live && f < Si.nf) {
-                        const V3<T> d = ld3(Si.fc[f]) - t;
-                        const T lim = Bj + Si.frad[f];
+                        const Vec4<T> fc = Si.fc[f];
+                        const V3<T> d = xyz(fc) - t;
+                        const T lim = Bj + fc.w;
+                        const int fi = Si.fi[f];
                         unsigned all = ~0u;
 #pragma unroll 4
-                        for (int k = Si.foff[f]; k < Si.foff[f + 1]; ++k) all &= W.vib[Si.floop[k]];
+                        for (int k = face_first(fi); k < face_end(fi); ++k) all &= plane_bits(W.vi[Si.floop[k]].w);
                         nf = all == 0 && dot(d, d) < grow * lim * lim;
                     }
                     if (live && f < Sj.nf) {
-                        const V3<T> d = ld3(Sj.fc[f]) - ti;
-                        const T lim = Bi + Sj.frad[f];
+                        const Vec4<T> fc = Sj.fc[f];
+                        const V3<T> d = xyz(fc) - ti;
+                        const T lim = Bi + fc.w;
+                        const int fi = Sj.fi[f];
                         unsigned all = ~0u;
 #pragma unroll 4
-                        for (int k = Sj.foff[f]; k < Sj.foff[f + 1]; ++k) all &= W.vjb[Sj.floop[k]];
+                        for (int k = face_first(fi); k < face_end(fi); ++k) all &= plane_bits(W.vj[Sj.floop[k]].w);
                         mf = all == 0 && dot(d, d) < grow * lim * lim;
                     }
                     cfi = group_append(nf, W.fi_near, cfi, f, gmask);
@@ -926,16 +977,16 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 const uint2 *cellj = l.fcells + (size_t)(rl.sbase + sj) * kFcCells;
                 for (int k = sub; k < cvi; k += kGL) {
                     const int x = W.vi_near[k];
-                    W.vib[x] = fc_lookup<T, DIM>(cellj, Sj, ld3(W.vi[x])).x & tj;
+                    set_plane_bits(W.vi[x].w, fc_lookup<T, DIM>(cellj, Sj, xyz(W.vi[x])).x & tj);
                 }
                 for (int k = sub; k < cvj; k += kGL) {
                     const int x = W.vj_near[k];
-                    W.vjb[x] = fc_lookup<T, DIM>(celli, Si, ld3(W.vj[x])).x & ti;
+                    set_plane_bits(W.vj[x].w, fc_lookup<T, DIM>(celli, Si, xyz(W.vj[x])).x & ti);
                 }
                 if (DIM == 3)
                     for (int k = sub; k < cei; k += kGL) {
                         const int e = W.ei_near[k];
-                        const V3<T> m = T(0.5) * (ld3(W.vi[Si.e[e][0]]) + ld3(W.vi[Si.e[e][1]]));
+                        const V3<T> m = T(0.5) * (xyz(W.vi[Si.e[e][0]]) + xyz(W.vi[Si.e[e][1]]));
                         Fc.eib[e] = fc_lookup<T, DIM>(cellj, Sj, m).y & mej;
                     }
                 wave_sync_lds();
@@ -947,8 +998,9 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     const int k = k0 + sub;
                     int c = 0;
                     if (k < nent)
-                        c = __popc(k < cvi ? W.vib[W.vi_near[k]]
-                                           : (k < cvi + cvj ? W.vjb[W.vj_near[k - cvi]] : Fc.eib[W.ei_near[k - cvi - cvj]]));
+                        c = __popc(k < cvi ? plane_bits(W.vi[W.vi_near[k]].w)
+                                           : (k < cvi + cvj ? plane_bits(W.vj[W.vj_near[k - cvi]].w)
+                                                            : Fc.eib[W.ei_near[k - cvi - cvj]]));
                     for (int off = 1; off < kGL; off <<= 1) {
                         const int u = __shfl_up(c, off, kGL);
                         if (sub >= off) c += u;
@@ -1312,8 +1364,8 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 hj[p] = live && k < Sj.nv;
                 hi[p] = live && k < Si.nv;
                 wj[p] = wi[p] = v3<T>(0, 0, 0);
-                if (hj[p]) wj[p] = t + mul(Rr, ld3(Sj.v[k]));
-                if (hi[p]) wi[p] = mulT(Rr, ld3(Si.v[k]) - t);
+                if (hj[p]) wj[p] = t + mul(Rr, xyz(Sj.v[k]));
+                if (hi[p]) wi[p] = mulT(Rr, xyz(Si.v[k]) - t);
             }
             // bit p of bi (bj): every vertex of j (i) this lane holds lies
             // more than thr beyond supporting plane p of i (j); no early exit
@@ -1323,24 +1375,22 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             const int nsi = live ? Si.nsep : 0, nsj = live ? Sj.nsep : 0;
 #pragma unroll 2
             for (int p = 0; p < nsi; ++p) {
-                const V3<T> n = ld3(Si.sn[p]);
-                const T o = Si.so[p];
+                const Vec4<T> pl = Si.sp[p];
                 bool all = true;
 #pragma unroll
                 for (int v = 0; v < kVP; ++v) {
-                    all &= !hj[v] || dot(n, wj[v]) - o > thr;
+                    all &= !hj[v] || plane_gap(pl, wj[v]) > thr;
                     c_pv.add(hj[v] ? 1 : 0);
                 }
                 bi |= (all ? 1u : 0u) << p;
             }
 #pragma unroll 2
             for (int p = 0; p < nsj; ++p) {
-                const V3<T> n = ld3(Sj.sn[p]);
-                const T o = Sj.so[p];
+                const Vec4<T> pl = Sj.sp[p];
                 bool all = true;
 #pragma unroll
                 for (int v = 0; v < kVP; ++v) {
-                    all &= !hi[v] || dot(n, wi[v]) - o > thr;
+                    all &= !hi[v] || plane_gap(pl, wi[v]) > thr;
                     c_pv.add(hi[v] ? 1 : 0);
                 }
                 bj |= (all ? 1u : 0u) << p;
@@ -1840,32 +1890,28 @@ __global__ void k_rotations(BatchParams b, const SysParams *reps, StatePtrs s, L
 template <typename T, int DIM, int GL, int OCC, int SL, int STAGE, bool FC>
 void pairs_t(const Launch &L, unsigned long long *stats, hipStream_t stream);
 
-// The compiled shapes: {8, 16} lanes per pair x {2, 3} wavefronts per SIMD
-// with the 4-lane separation stage, and 16 lanes x {2, 3} with the 16-lane
-// one; in the split form, the search kernel (4-lane separation stage,
-// kSearchOcc wavefronts per SIMD) and then the force kernel at {8, 16}
-// lanes x {2, 3} wavefronts.  Each feature stage with the supporting-plane
-// prefilter or with the shape-local feature cells (FC); the FC feature
-// stage does not fit the 168 registers of 3 wavefronts per SIMD, so it is
-// compiled for 2 whatever the shape asks.
+// The compiled shapes: 8 or 16 lanes per pair with the 4-lane separation
+// stage, 16 lanes with the 16-lane one; in the split form, the search kernel
+// (4-lane separation stage, kSearchOcc wavefronts per SIMD) and then the
+// force kernel at 8 or 16 lanes.  Each feature stage with the supporting-
+// plane prefilter or with the shape-local feature cells (FC).  All are built
+// for 3 wavefronts per SIMD (168 registers), whether the shape asks for 2 or
+// 3: a build for 2 was no faster on any of twelve workloads (4096 FP64
+// cubes 24.0 us against 24.2-24.7, 16 lanes) and, where it takes more than
+// 168 registers, slower (8 lanes, 262,144 octahedra: 698 us against 536).
+// The FC feature stage does not fit 168 registers and is built for 2.
 template <typename T, int DIM, bool FC>
 void pairs_form(const Launch &L, unsigned long long *stats, hipStream_t stream)
 {
-    const bool g8 = L.b.pair_lanes == 8, o3 = !FC && L.b.pair_waves == 3;
-    constexpr int O3 = FC ? 2 : 3;  // (FC: never taken, o3 is false)
+    const bool g8 = L.b.pair_lanes == 8;
+    constexpr int O = FC ? 2 : 3;
     if (L.b.pair_split) {
         pairs_t<T, DIM, 16, kSearchOcc, 4, kSearchOnly, false>(L, stats, stream);
-        if (g8)
-            o3 ? pairs_t<T, DIM, 8, O3, 4, kForces, FC>(L, stats, stream) : pairs_t<T, DIM, 8, 2, 4, kForces, FC>(L, stats, stream);
-        else
-            o3 ? pairs_t<T, DIM, 16, O3, 4, kForces, FC>(L, stats, stream)
-               : pairs_t<T, DIM, 16, 2, 4, kForces, FC>(L, stats, stream);
+        g8 ? pairs_t<T, DIM, 8, O, 4, kForces, FC>(L, stats, stream) : pairs_t<T, DIM, 16, O, 4, kForces, FC>(L, stats, stream);
     } else if (L.b.pair_sep == 16)
-        o3 ? pairs_t<T, DIM, 16, O3, 16, kFused, FC>(L, stats, stream) : pairs_t<T, DIM, 16, 2, 16, kFused, FC>(L, stats, stream);
-    else if (g8)
-        o3 ? pairs_t<T, DIM, 8, O3, 4, kFused, FC>(L, stats, stream) : pairs_t<T, DIM, 8, 2, 4, kFused, FC>(L, stats, stream);
+        pairs_t<T, DIM, 16, O, 16, kFused, FC>(L, stats, stream);
     else
-        o3 ? pairs_t<T, DIM, 16, O3, 4, kFused, FC>(L, stats, stream) : pairs_t<T, DIM, 16, 2, 4, kFused, FC>(L, stats, stream);
+        g8 ? pairs_t<T, DIM, 8, O, 4, kFused, FC>(L, stats, stream) : pairs_t<T, DIM, 16, O, 4, kFused, FC>(L, stats, stream);
 }
 
 template <typename T, int DIM>
@@ -1959,47 +2005,43 @@ size_t pair_kernel_lds(int precision, int tab_slots, int lanes, int sep, int sta
 
 namespace {
 template <typename T, int DIM, int STAGE, bool FC>
-hipError_t pair_occupancy(int *per_cu, size_t lds, int lanes, int waves, int sep)
+hipError_t pair_occupancy(int *per_cu, size_t lds, int lanes, int sep)
 {
     const int t = 64 * kWaves;
     auto occ = [&](auto kernel) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kernel, t, lds); };
-    constexpr int O3 = FC ? 2 : 3;  // the FC feature stage is compiled for 2 wavefronts per SIMD only
+    constexpr int O = FC ? 2 : 3;
     if constexpr (STAGE == kSearchOnly) {
         return occ(k_pairs<T, DIM, 16, false, kSearchOcc, 4, kSearchOnly, false>);
     } else {
         if constexpr (STAGE == kFused)
-            if (sep == 16)
-                return waves == 3 ? occ(k_pairs<T, DIM, 16, false, O3, 16, STAGE, FC>)
-                                  : occ(k_pairs<T, DIM, 16, false, 2, 16, STAGE, FC>);
-        if (lanes == 8)
-            return waves == 3 ? occ(k_pairs<T, DIM, 8, false, O3, 4, STAGE, FC>) : occ(k_pairs<T, DIM, 8, false, 2, 4, STAGE, FC>);
-        return waves == 3 ? occ(k_pairs<T, DIM, 16, false, O3, 4, STAGE, FC>) : occ(k_pairs<T, DIM, 16, false, 2, 4, STAGE, FC>);
+            if (sep == 16) return occ(k_pairs<T, DIM, 16, false, O, 16, STAGE, FC>);
+        return lanes == 8 ? occ(k_pairs<T, DIM, 8, false, O, 4, STAGE, FC>) : occ(k_pairs<T, DIM, 16, false, O, 4, STAGE, FC>);
     }
 }
 
 template <typename T, int DIM>
-hipError_t pair_occupancy_stage(int *per_cu, size_t lds, int lanes, int waves, int sep, int stage, int fc)
+hipError_t pair_occupancy_stage(int *per_cu, size_t lds, int lanes, int sep, int stage, int fc)
 {
-    if (stage == kSearchOnly) return pair_occupancy<T, DIM, kSearchOnly, false>(per_cu, lds, lanes, waves, sep);
+    if (stage == kSearchOnly) return pair_occupancy<T, DIM, kSearchOnly, false>(per_cu, lds, lanes, sep);
     if (stage == kForces)
-        return fc ? pair_occupancy<T, DIM, kForces, true>(per_cu, lds, lanes, waves, sep)
-                  : pair_occupancy<T, DIM, kForces, false>(per_cu, lds, lanes, waves, sep);
-    return fc ? pair_occupancy<T, DIM, kFused, true>(per_cu, lds, lanes, waves, sep)
-              : pair_occupancy<T, DIM, kFused, false>(per_cu, lds, lanes, waves, sep);
+        return fc ? pair_occupancy<T, DIM, kForces, true>(per_cu, lds, lanes, sep)
+                  : pair_occupancy<T, DIM, kForces, false>(per_cu, lds, lanes, sep);
+    return fc ? pair_occupancy<T, DIM, kFused, true>(per_cu, lds, lanes, sep)
+              : pair_occupancy<T, DIM, kFused, false>(per_cu, lds, lanes, sep);
 }
 }  // namespace
 
-int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int waves, int sep, int stage, int fc)
+int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int sep, int stage, int fc)
 {
     const size_t lds = pair_kernel_lds(precision, tab_slots, lanes, sep, stage, fc);
     int per_cu = 0, cus = 0, dev = 0;
     hipError_t e;
     if (precision == DEM_FP32)
-        e = dim == 3 ? pair_occupancy_stage<float, 3>(&per_cu, lds, lanes, waves, sep, stage, fc)
-                     : pair_occupancy_stage<float, 2>(&per_cu, lds, lanes, waves, sep, stage, fc);
+        e = dim == 3 ? pair_occupancy_stage<float, 3>(&per_cu, lds, lanes, sep, stage, fc)
+                     : pair_occupancy_stage<float, 2>(&per_cu, lds, lanes, sep, stage, fc);
     else
-        e = dim == 3 ? pair_occupancy_stage<double, 3>(&per_cu, lds, lanes, waves, sep, stage, fc)
-                     : pair_occupancy_stage<double, 2>(&per_cu, lds, lanes, waves, sep, stage, fc);
+        e = dim == 3 ? pair_occupancy_stage<double, 3>(&per_cu, lds, lanes, sep, stage, fc)
+                     : pair_occupancy_stage<double, 2>(&per_cu, lds, lanes, sep, stage, fc);
     if (e != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 512;

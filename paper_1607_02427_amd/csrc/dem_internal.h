@@ -123,7 +123,7 @@ __device__ inline unsigned slot_stamp(const SlotRec<double> &w) { return (unsign
 __device__ inline void set_stamp(SlotRec<float> &w, unsigned s) { w.pad0 = __uint_as_float(s); }
 __device__ inline void set_stamp(SlotRec<double> &w, unsigned s) { w.pad0 = __longlong_as_double((long long)s); }
 
-// Body-frame feature tables of one shape in precision T, staged in LDS.
+// Body-frame feature tables of one shape, as the host builds them (FP64).
 // Edges carry their vector, midpoint, half length and 1/|edge|^2; faces
 // their outward unit normal n and offset o (n.x = o on the plane), a
 // bounding circle (centroid, radius), the in-plane inward normal and offset
@@ -134,35 +134,70 @@ __device__ inline void set_stamp(SlotRec<double> &w, unsigned s) { w.pad0 = __lo
 // max over vertices of sn.v, so every point of the inner body satisfies
 // sn.x <= so.
 constexpr int kMaxSep = DEM_MAX_EDGES > DEM_MAX_FACES ? DEM_MAX_EDGES : DEM_MAX_FACES;
-template <typename T>
-struct alignas(16) ShapeTab {
+struct HostShape {
     int nv, ne, nf;
     int fc_g;                    // shape-local feature cells: fc_g cells per axis
-    T r, R;
-    T fc_lo, fc_ih;              // covering [fc_lo, -fc_lo] per axis, 1 / cell width
-    T v[DEM_MAX_VERTS][3];
+    double r, R;
+    double fc_lo, fc_ih;         // covering [fc_lo, -fc_lo] per axis, 1 / cell width
+    double v[DEM_MAX_VERTS][3];
     int e[DEM_MAX_EDGES][2];
-    T ed[DEM_MAX_EDGES][3];      // edge vector b - a
-    T em[DEM_MAX_EDGES][3];      // edge midpoint
-    T eh[DEM_MAX_EDGES];         // half length
-    T el2[DEM_MAX_EDGES];        // |b - a|^2
-    T einv[DEM_MAX_EDGES];       // 1 / |b - a|^2
+    double ed[DEM_MAX_EDGES][3]; // edge vector b - a
+    double em[DEM_MAX_EDGES][3]; // edge midpoint
+    double eh[DEM_MAX_EDGES];    // half length
+    double el2[DEM_MAX_EDGES];   // |b - a|^2
+    double einv[DEM_MAX_EDGES];  // 1 / |b - a|^2
     int foff[DEM_MAX_FACES + 1];
     int floop[DEM_MAX_LOOP];
     int fconvex[DEM_MAX_FACES];
-    T fn[DEM_MAX_FACES][3];
-    T fo[DEM_MAX_FACES];
-    T fc[DEM_MAX_FACES][3];      // centroid of the loop vertices
-    T frad[DEM_MAX_FACES];       // max distance from fc to a loop vertex
-    T fe1[DEM_MAX_FACES][3];     // face axis 1; axis 2 = n x axis 1; origin = first loop vertex
-    T lnrm[DEM_MAX_LOOP][3];     // inward in-plane normal of loop edge k -> k+1
-    T loff[DEM_MAX_LOOP];        // lnrm . b_k
-    T linv[DEM_MAX_LOOP];        // 1 / |b_{k+1} - b_k|^2
-    T lxy[DEM_MAX_LOOP][2];      // face coordinates of loop vertex k
-    int nsep, pad3[3];
-    T sn[kMaxSep][3];            // supporting-plane normals
-    T so[kMaxSep];               // and offsets
+    double fn[DEM_MAX_FACES][3];
+    double fo[DEM_MAX_FACES];
+    double fc[DEM_MAX_FACES][3]; // centroid of the loop vertices
+    double frad[DEM_MAX_FACES];  // max distance from fc to a loop vertex
+    double fe1[DEM_MAX_FACES][3];// face axis 1; axis 2 = n x axis 1; origin = first loop vertex
+    double lnrm[DEM_MAX_LOOP][3];// inward in-plane normal of loop edge k -> k+1
+    double loff[DEM_MAX_LOOP];   // lnrm . b_k
+    double linv[DEM_MAX_LOOP];   // 1 / |b_{k+1} - b_k|^2
+    double lxy[DEM_MAX_LOOP][2]; // face coordinates of loop vertex k
+    int nsep;
+    double sn[kMaxSep][3];       // supporting-plane normals
+    double so[kMaxSep];          // and offsets
 };
+
+// The same tables in precision T as the kernels read them, from LDS (and
+// from global memory for the FP64 redo): every vector with the scalar that
+// is read beside it in one 16-byte (FP64: 32-byte) word, so a feature is
+// one or two ds_read_b128 instead of four to eight 4-byte reads, and the
+// end points of edges and loop edges stored by value, so no read waits on
+// an index read before it.
+template <typename T>
+struct alignas(16) Vec4 {
+    T x, y, z, w;
+};
+template <typename T>
+struct alignas(16) ShapeTab {
+    int nv, ne, nf;
+    int fc_g;
+    T r, R;
+    T fc_lo, fc_ih;
+    int nsep, pad[3];
+    Vec4<T> v[DEM_MAX_VERTS];    // vertex, 0
+    Vec4<T> ea[DEM_MAX_EDGES];   // first end point, |b - a|^2
+    Vec4<T> ed[DEM_MAX_EDGES];   // b - a, 1 / |b - a|^2
+    Vec4<T> em[DEM_MAX_EDGES];   // midpoint, half length
+    Vec4<T> fn[DEM_MAX_FACES];   // normal, offset
+    Vec4<T> fc[DEM_MAX_FACES];   // centroid, bounding radius
+    Vec4<T> fe1[DEM_MAX_FACES];  // face axis 1, 0
+    Vec4<T> lv[DEM_MAX_LOOP];    // loop vertex k, 1 / |loop edge k -> k+1|^2
+    Vec4<T> ln[DEM_MAX_LOOP];    // inward in-plane normal, offset
+    Vec4<T> sp[kMaxSep];         // supporting plane: normal, offset
+    T lxy[DEM_MAX_LOOP][2];
+    int e[DEM_MAX_EDGES][2];     // end points by index (into the pair's transformed vertices)
+    int floop[DEM_MAX_LOOP];     // loop vertices by index
+    int fi[DEM_MAX_FACES];       // first loop entry | one past the last << 8 | convex << 16
+};
+__host__ __device__ inline int face_first(int fi) { return fi & 255; }
+__host__ __device__ inline int face_end(int fi) { return (fi >> 8) & 255; }
+__host__ __device__ inline bool face_convex(int fi) { return (fi >> 16) != 0; }
 
 static_assert(sizeof(ShapeTab<float>) % 16 == 0 && sizeof(ShapeTab<double>) % 16 == 0, "tables are copied in 16-byte words");
 
@@ -431,7 +466,7 @@ __device__ inline void cell_insert(const SysParams &p, const ListPtrs &l, int i,
 // Dynamic LDS of the pair kernel, and how many of its blocks the device
 // holds at once.
 size_t pair_kernel_lds(int precision, int tab_slots, int lanes, int sep, int stage, int fc);
-int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int waves, int sep, int stage, int fc);
+int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int sep, int stage, int fc);
 
 // Per-particle records (position, rotation, shape id) from the state arrays.
 void launch_rotations(const Launch &L, hipStream_t stream);
