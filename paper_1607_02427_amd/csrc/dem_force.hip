@@ -1464,16 +1464,30 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
         }
     }
     if (COUNT && stats) {
+        // The counters go to one of kStatBanks copies by workgroup, one line
+        // each, added up when they are read; the workgroup's wavefronts are
+        // summed in LDS first and a zero is not added.  One copy alone
+        // serialised 8 atomics per wavefront on one line across the XCDs
+        // (5003 FP64 L-prisms: 295 us per counted launch against 68
+        // uncounted; 72 with the banks).
         const unsigned cnt[8] = {c_pairs.get(), c_feat.get(), c_in.get(), c_near.get(), c_ref.get(), c_ee.get(),
                                  c_sep.get(), c_pv.get()};
         const int slot[8] = {ST_PAIRS, ST_FEATURES, ST_INCUT, ST_NEAR, ST_REFINED, ST_EENEAR, ST_SEPARATED, ST_PLANETESTS};
+        unsigned *sum = reinterpret_cast<unsigned *>(smem);  // the tables are done with
+        __syncthreads();
+        if (threadIdx.x < 8) sum[threadIdx.x] = 0u;
+        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            unsigned long long w = cnt[k];
-            for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off, 64);
-            if (lane == 0) atomicAdd(&stats[slot[k]], w);
+        for (int k = 0; k < 8; ++k)
+            if (cnt[k] != 0u) atomicAdd(&sum[k], cnt[k]);
+        __syncthreads();
+        unsigned long long *bank = stats + (size_t)(blockIdx.x % kStatBanks) * kStatStride;
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (sum[k] != 0u) atomicAdd(&bank[slot[k]], (unsigned long long)sum[k]);
+            if (blockIdx.x == 0) atomicAdd(&bank[ST_LAUNCHES], 1ull);
         }
-        if (lane == 0 && blockIdx.x == 0 && wid == 0) atomicAdd(&stats[ST_LAUNCHES], 1ull);
     }
 }
 

@@ -102,6 +102,9 @@ enum Stat {
     ST_PAIRS = 0, ST_FEATURES = 1, ST_INCUT = 2, ST_LAUNCHES = 3, ST_NEAR = 4, ST_REFINED = 5, ST_EENEAR = 6,
     ST_SEPARATED = 7, ST_PLANETESTS = 8, ST_COUNT = 9
 };
+// Copies of the counters, each on a line of its own (workgroup b of a
+// counted launch adds to copy b % kStatBanks).
+constexpr int kStatBanks = 256, kStatStride = 16;
 
 // One row-slot record, for slot k of particle i's neighbour row at
 // rec[k * N + i]: the force on i (space frame) and the pair energy U_ij,

@@ -122,6 +122,7 @@ namespace {
 
 std::string g_err;
 constexpr int64_t kUnbounded = (int64_t)1 << 62;
+constexpr size_t kStatBytes = sizeof(unsigned long long) * kStatBanks * kStatStride;
 
 
 dem_status fail(dem_system *h, dem_status s, const char *fmt, ...)
@@ -796,7 +797,7 @@ dem_status alloc_core(dem_system *h, int Ncap, int Ccap, int Scap, int Rcap)
               hipMalloc(&h->thermo, sizeof(double) * TH_COUNT * Rcap) == hipSuccess &&
               hipMalloc(&h->budget, sizeof(int64_t) * Rcap) == hipSuccess &&
               hipMalloc(&h->steps, sizeof(int64_t) * Rcap) == hipSuccess &&
-              hipMalloc(&h->stats, sizeof(unsigned long long) * ST_COUNT) == hipSuccess &&
+              hipMalloc(&h->stats, kStatBytes) == hipSuccess &&
               hipMalloc(&h->lst.flags, sizeof(int32_t) * FLAG_COUNT * Rcap) == hipSuccess &&
               hipMalloc(&h->lst.gflags, sizeof(int32_t) * G_COUNT) == hipSuccess &&
               hipMalloc(&h->lst.tile_start, sizeof(int32_t) * (Rcap + 1)) == hipSuccess &&
@@ -844,7 +845,7 @@ dem_status alloc_core(dem_system *h, int Ncap, int Ccap, int Scap, int Rcap)
     HIPCHK(h, hipMemsetAsync(h->lst.pstart, 0, sizeof(int32_t) * N, h->stream));
     HIPCHK(h, hipMemsetAsync(h->lst.ptot, 0, sizeof(int32_t) * (N / lb_rows_per_group + 1), h->stream));
     HIPCHK(h, hipMemsetAsync(h->lst.pcell, 0, sizeof(int32_t) * N, h->stream));
-    HIPCHK(h, hipMemsetAsync(h->stats, 0, sizeof(unsigned long long) * ST_COUNT, h->stream));
+    HIPCHK(h, hipMemsetAsync(h->stats, 0, kStatBytes, h->stream));
     HIPCHK(h, hipMemsetAsync(h->ke_part, 0, sizeof(double) * kKePer * nch, h->stream));
     HIPCHK(h, hipMemsetAsync(h->budget, 0, sizeof(int64_t) * Rcap, h->stream));
     HIPCHK(h, hipMemsetAsync(h->steps, 0, sizeof(int64_t) * Rcap, h->stream));
@@ -1367,7 +1368,7 @@ size_t dem_footprint_bytes(const dem_params *p)
     const size_t maxp = n * (size_t)cap / 2;
     return sizeof(int32_t) * (n * (size_t)cap + 4 * n + ncell * (1 + kCellCap) + 8 * maxp + nch + 2 * FLAG_COUNT + G_COUNT + 2 +
                               split_words(1)) +
-           sizeof(double) * (3 * n + (kKePer + 12) * nch + TH_COUNT + 2) + sizeof(unsigned long long) * ST_COUNT +
+           sizeof(double) * (3 * n + (kKePer + 12) * nch + TH_COUNT + 2) + kStatBytes +
            (partrec_bytes(p->precision) + (p->precision == DEM_FP32 ? sizeof(PartRec64) : 0)) * n +
            sizeof(uint2) * kFcCells * DEM_MAX_SHAPES +
            rec_bytes(p->precision) * (size_t)cap * n + sizeof(uint32_t) * (size_t)slot_words(cap) * n + sizeof(SysParams) + 2 * DEM_MAX_SHAPES * sizeof(ShapeTab<double>) + 256;
@@ -1707,11 +1708,15 @@ dem_status dem_list_info(dem_handle h, double *r_list, int32_t *n_cells, int32_t
 dem_status dem_force_stats(dem_handle h, int64_t *out, int32_t reset)
 {
     if (!h || !out) return fail(h, DEM_E_ARG, "null argument");
-    unsigned long long v[ST_COUNT];
-    HIPCHK(h, hipMemcpyAsync(v, h->stats, sizeof v, hipMemcpyDeviceToHost, h->stream));
+    std::vector<unsigned long long> v((size_t)kStatBanks * kStatStride);
+    HIPCHK(h, hipMemcpyAsync(v.data(), h->stats, kStatBytes, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
-    for (int k = 0; k < ST_COUNT; ++k) out[k] = (int64_t)v[k];
-    if (reset) HIPCHK(h, hipMemsetAsync(h->stats, 0, sizeof v, h->stream));
+    for (int k = 0; k < ST_COUNT; ++k) {
+        unsigned long long sum = 0;
+        for (int b = 0; b < kStatBanks; ++b) sum += v[(size_t)b * kStatStride + k];
+        out[k] = (int64_t)sum;
+    }
+    if (reset) HIPCHK(h, hipMemsetAsync(h->stats, 0, kStatBytes, h->stream));
     return DEM_OK;
 }
 
