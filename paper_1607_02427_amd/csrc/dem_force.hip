@@ -40,6 +40,7 @@
 // cutoff; closest points ill-conditioned, error ~ eps / sin^2; a torque that
 // is a small fraction of |lever| |f|).
 #include <algorithm>
+#include <type_traits>
 
 #include "dem_internal.h"
 #include "dem_listbuild.h"
@@ -171,10 +172,9 @@ __device__ inline V3<T> face_point(const ShapeTab<T> &S, int f, int fi, V3<T> p)
     return q;
 }
 
-__device__ inline double min_image(double d, double L) { return d - L * rint(d / L); }
-// The same for |d| < L (positions in [0, L)) without a division; it differs
-// from min_image only where |d| is within rounding of L/2, far beyond any
-// interaction.
+// Minimum image of d = x_j - x_i, |d| <= L (positions in [0, L]): d - L rint(d / L)
+// without its division, from which it differs only where |d| is within
+// rounding of L/2, far beyond any interaction.
 __device__ inline double min_image_near(double d, double L)
 {
     const double h = 0.5 * L;
@@ -241,7 +241,7 @@ struct alignas(16) PairLds {
 // PairLds): the cell masks of i's edges (edges of j within reach of each,
 // 3D), and the prefix of the problem counts over the near entries (i's
 // vertices, j's vertices, i's edges), which numbers the pair's problems.
-struct PairFc {
+struct alignas(16) PairFc {
     unsigned eib[DEM_MAX_EDGES];
     unsigned short pf[2 * DEM_MAX_VERTS + DEM_MAX_EDGES + 2];
 };
@@ -624,31 +624,55 @@ __device__ int refine_pair(const double *box, double eps, double par_s2, const P
 }
 
 // The current replica of a pair-kernel block, staged in LDS beside its
-// shape tables.
+// shape tables: SysParams' block from box to wide, then its lists.
 struct alignas(16) RepLds {
-    double box[3];
-    double R[DEM_MAX_SHAPES], rad[DEM_MAX_SHAPES];
-    double eps, par_s2;
+    double box[3], eps, par_s2;
+    double R[DEM_MAX_SHAPES], rad[DEM_MAX_SHAPES], wide;
     int r, sbase, np, poff, first_tile, ncmp, last, pad;
 };
+static_assert(offsetof(RepLds, r) == kPairConst * sizeof(double), "copied from SysParams as it is");
 
-// Stages replica r: its shape tables and parameters.  Every thread of the
-// block calls it together.  UNITS: the block walks force units of the
-// replica's compacted pairs (split form) instead of its pair tiles.
-template <typename T, bool UNITS = false>
+// What a workgroup reads of replica r before it can request anything else.
+struct RepHead {
+    int np, first, poff, sbase, n_shapes;
+};
+template <bool UNITS>
+__device__ inline RepHead rep_head(const SysParams *reps, const ListPtrs &l, int r)
+{
+    return {l.flags[r * FLAG_COUNT + FLAG_NPAIRS], UNITS ? l.cunit[r] : l.tile_start[r], reps[r].poff, reps[r].sbase,
+            reps[r].n_shapes};
+}
+
+// Stages replica r: its shape tables and parameters, and the pair entries of
+// `tile`, the first tile the block takes of it, into each wavefront's entry
+// slots (nxt, kPP of them).  Every thread of the block calls it together.
+// All of it is requested at once, so a block waits for one round trip
+// before its first particle records.  UNITS: the block walks force units of
+// the replica's compacted pairs (split form) instead of its pair tiles, and
+// reads its entries itself.
+template <typename T, bool UNITS, int kPP>
 __device__ void stage_replica(const SysParams *reps, const ListPtrs &l, const ShapeTab<T> *gtab, ShapeTab<T> *tab,
-                              RepLds &rl, int r)
+                              RepLds &rl, int r, const RepHead &hd, int tile, int4 *nxt)
 {
     __syncthreads();
-    const SysParams &p = reps[r];
-    // 16-byte words (the tables are 16-byte aligned and sized), up to four
-    // loads per thread in flight before their stores
-    constexpr int kU = 4;
-    const int n16 = p.n_shapes * (int)(sizeof(ShapeTab<T>) / 16);
-    const uint4 *src = reinterpret_cast<const uint4 *>(gtab + p.sbase);
-    uint4 *dst = reinterpret_cast<uint4 *>(tab);
     int tid = threadIdx.x;  // (formed here, not held across the caller's loop)
     asm volatile("" : "+v"(tid));
+    int4 ent = make_int4(0, 0, 0, 0);
+    const bool fetch = !UNITS && (tid & 63) < kPP;
+    if (fetch) {  // (entries past the last repeat it; a replica with a tile has a pair)
+        const int q = ((tile - hd.first) * kWaves + (tid >> 6)) * kPP + (tid & 63);
+        ent = l.pairs[hd.poff + (q < hd.np ? q : hd.np - 1)];
+    }
+    constexpr int kC = kPairConst / 2;
+    const bool cst = tid >= 64 * kWaves - kC;
+    uint4 c = make_uint4(0, 0, 0, 0);
+    if (cst) c = reinterpret_cast<const uint4 *>(reps[r].box)[tid - (64 * kWaves - kC)];
+    // 16-byte words (the tables are 16-byte aligned and sized), up to two
+    // loads per thread in flight before their stores
+    constexpr int kU = 2;
+    const int n16 = hd.n_shapes * (int)(sizeof(ShapeTab<T>) / 16);
+    const uint4 *src = reinterpret_cast<const uint4 *>(gtab + hd.sbase);
+    uint4 *dst = reinterpret_cast<uint4 *>(tab);
     for (int w0 = tid; w0 < n16; w0 += kU * blockDim.x) {
         uint4 v[kU];
 #pragma unroll
@@ -662,19 +686,14 @@ __device__ void stage_replica(const SysParams *reps, const ListPtrs &l, const Sh
             if (w < n16) dst[w] = v[u];
         }
     }
+    if (fetch) nxt[tid & 63] = ent;
+    if (cst) reinterpret_cast<uint4 *>(rl.box)[tid - (64 * kWaves - kC)] = c;
     if (threadIdx.x == 0) {  // (one thread: the LDS addresses stay scalar)
-        for (int k = 0; k < DEM_MAX_SHAPES; ++k) {
-            rl.R[k] = p.R[k];
-            rl.rad[k] = p.rad[k];
-        }
-        for (int a = 0; a < 3; ++a) rl.box[a] = p.box[a];
-        rl.eps = p.eps;
-        rl.par_s2 = p.par_s2;
         rl.r = r;
-        rl.sbase = p.sbase;
-        rl.np = l.flags[r * FLAG_COUNT + FLAG_NPAIRS];
-        rl.poff = p.poff;
-        rl.first_tile = UNITS ? l.cunit[r] : l.tile_start[r];
+        rl.sbase = hd.sbase;
+        rl.np = hd.np;
+        rl.poff = hd.poff;
+        rl.first_tile = hd.first;
         rl.ncmp = UNITS ? l.ccount[r] : 0;
     }
     __syncthreads();
@@ -783,11 +802,20 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
 
     const int lane = __lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the pair entries of this wavefront's next separation tile
+    // (the search kernel has no feature stage: its slots follow the scan's words)
+    int4 *nxt = (kSearch ? reinterpret_cast<int4 *>(reinterpret_cast<int *>(pls) + 64 * kWaves)
+                         : reinterpret_cast<int4 *>(reinterpret_cast<unsigned char *>(pfc) +
+                                                    (FC ? kWaves * kGroups * sizeof(PairFc) : 0))) +
+                wid * kPairsPerWave;
     const int grp = lane / kGL, sub = lane % kGL;
     const unsigned long long gmask = ((kGL == 64) ? ~0ull : ((1ull << kGL) - 1)) << (kGL * grp);
     PairLds<T> &W = pls[wid * kGroups + grp];
     QEnt<T> *qb = qall + wid * kQCap;
     const size_t N = (size_t)b.N;
+    // requested with the tile count, not after it: a single system's values,
+    // and a batch's first guess
+    RepHead hd = rep_head<kForce>(reps, l, 0);
     const int ntiles = l.tile_start[b.nrep];
     const unsigned stamp = (unsigned)l.gflags[G_STAMP];
     const int G = gridDim.x, per = G >> 3;
@@ -825,7 +853,8 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
         }
         r = lo;
         r_end = first[r + 1];
-        stage_replica<T, kForce>(reps, l, gtab, tab, rl, r);
+        if (b.nrep > 1) hd = rep_head<kForce>(reps, l, r);
+        stage_replica<T, kForce, kPairsPerWave>(reps, l, gtab, tab, rl, r, hd, t0, nxt);
     }
     int head = 0, tail = 0;  // queue positions, the same in every lane of the wave
     int tt = t0;
@@ -1227,7 +1256,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 ++r;
                 r_end = first[r + 1];
             } while (tt >= r_end);
-            stage_replica<T, kForce>(reps, l, gtab, tab, rl, r);
+            stage_replica<T, kForce, kPairsPerWave>(reps, l, gtab, tab, rl, r, rep_head<kForce>(reps, l, r), tt, nxt);
         }
         if constexpr (kForce) {
             // ---- unit tt: this wave's kGroups compacted pairs, one lane each ----
@@ -1245,9 +1274,9 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     Ri.m[k] = ri.R[k];
                     Rj.m[k] = rj.R[k];
                 }
-                const double dx = min_image(rj.x - ri.x, rl.box[0]);
-                const double dy = min_image(rj.y - ri.y, rl.box[1]);
-                const double dz = (DIM == 3) ? min_image(rj.z - ri.z, rl.box[2]) : 0.0;
+                const double dx = min_image_near(rj.x - ri.x, rl.box[0]);
+                const double dy = min_image_near(rj.y - ri.y, rl.box[1]);
+                const double dz = (DIM == 3) ? min_image_near(rj.z - ri.z, rl.box[2]) : 0.0;
                 const M3<T> Rr = rel_rotation(Ri, Rj);
                 const V3<T> t = mulT(Ri, v3<T>((T)dx, (T)dy, (T)dz));
                 QEnt<T> &e = qb[lane];
@@ -1277,32 +1306,32 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
         asm volatile("" : "+v"(lane1));
         const int grp1 = lane1 / kSepLanes, sub1 = lane1 % kSepLanes;
         const int q = (tt - rl.first_tile) * kTile + wid * kPairsPerWave + grp1;
-        const bool active = q < rl.np;
-        // two dependent round trips: the pair entry, then both particle
-        // records (position, rotation and shape in one line each)
-        int4 ent = make_int4(0, 0, 0, 0);
-        if (active) ent = l.pairs[rl.poff + q];
+        // The entry was fetched while the tile before this one was worked
+        // on (or while the tables were staged), so a tile waits for one
+        // round trip, the particle records (position, rotation and shape in
+        // one line each), not two; lanes past the replica's last pair work
+        // on that pair and drop it.
+        const int4 ent = nxt[grp1];
         const int i = ent.x, j = ent.y;
-        int si = 0, sj = 0;
-        double dx = 0.0, dy = 0.0, dz = 0.0;
-        bool live = false;
-        M3<T> Ri, Rj;
-        for (int k = 0; k < 9; ++k) Ri.m[k] = Rj.m[k] = T(0);
-        if (active) {
-            const PartRec<T> ri = prec[i];
-            const PartRec<T> rj = prec[j];
-            for (int k = 0; k < 9; ++k) {
-                Ri.m[k] = ri.R[k];
-                Rj.m[k] = rj.R[k];
-            }
-            dx = min_image(rj.x - ri.x, rl.box[0]);
-            dy = min_image(rj.y - ri.y, rl.box[1]);
-            dz = (DIM == 3) ? min_image(rj.z - ri.z, rl.box[2]) : 0.0;
-            si = ri.sid;
-            sj = rj.sid;
-            const double bound = rl.R[si] + rl.R[sj] + kWcaCut * (rl.rad[si] + rl.rad[sj]);
-            live = dx * dx + dy * dy + dz * dz < bound * bound;
+        const PartRec<T> ri = prec[i];
+        const PartRec<T> rj = prec[j];
+        const bool more = !kForce && tt + 1 < t1 && tt + 1 < r_end;
+        int4 ent1 = make_int4(0, 0, 0, 0);
+        if (more && lane1 < kPairsPerWave) {
+            const int q1 = (tt + 1 - rl.first_tile) * kTile + wid * kPairsPerWave + lane1;
+            ent1 = l.pairs[rl.poff + (q1 < rl.np ? q1 : rl.np - 1)];
         }
+        M3<T> Ri, Rj;
+        for (int k = 0; k < 9; ++k) {
+            Ri.m[k] = ri.R[k];
+            Rj.m[k] = rj.R[k];
+        }
+        const double dx = min_image_near(rj.x - ri.x, rl.box[0]);
+        const double dy = min_image_near(rj.y - ri.y, rl.box[1]);
+        const double dz = (DIM == 3) ? min_image_near(rj.z - ri.z, rl.box[2]) : 0.0;
+        const int si = ri.sid, sj = rj.sid;
+        const double bound = rl.R[si] + rl.R[sj] + kWcaCut * (rl.rad[si] + rl.rad[sj]);
+        bool live = q < rl.np && dx * dx + dy * dy + dz * dz < bound * bound;
         if (live && tab[si].ne == 0 && tab[sj].ne == 0 && tab[si].nf == 0 && tab[sj].nf == 0) {
             // two points (spheres, disks): the central WCA term of their
             // centres, in FP64, written here; no separation test, no
@@ -1342,59 +1371,59 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
         if (__ballot(live) != 0) {
             const ShapeTab<T> &Si = tab[si];
             const ShapeTab<T> &Sj = tab[sj];
-            M3<T> Rr;
-            V3<T> t = v3<T>(0, 0, 0);
-            T rc = T(0), Bi = T(0), Bj = T(0);
-            for (int k = 0; k < 9; ++k) Rr.m[k] = T(0);
-            if (live) {
-                Rr = rel_rotation(Ri, Rj);
-                t = mulT(Ri, v3<T>((T)dx, (T)dy, (T)dz));
-                rc = (T)(kWcaCut * (rl.rad[si] + rl.rad[sj]));
-                Bi = (T)rl.R[si] + rc;
-                Bj = (T)rl.R[sj] + rc;
-            }
+            const M3<T> Rr = rel_rotation(Ri, Rj);
+            const V3<T> t = mulT(Ri, v3<T>((T)dx, (T)dy, (T)dz));
+            const T rc = (T)(kWcaCut * (rl.rad[si] + rl.rad[sj]));
+            const T Bi = (T)rl.R[si] + rc, Bj = (T)rl.R[sj] + rc;
             // separation beyond which no feature pair can be inside the
             // cutoff, with room for the rounding of the transformed vertices
             const T thr = rc * T(1.0001) + T(1e-5) * (Bi + Bj);
-            V3<T> wj[kVP], wi[kVP];  // this lane's vertices: j's in i's frame, i's in j's frame
-            bool hj[kVP], hi[kVP];
-#pragma unroll
-            for (int p = 0; p < kVP; ++p) {
-                const int k = p * kSepLanes + sub1;
-                hj[p] = live && k < Sj.nv;
-                hi[p] = live && k < Si.nv;
-                wj[p] = wi[p] = v3<T>(0, 0, 0);
-                if (hj[p]) wj[p] = t + mul(Rr, xyz(Sj.v[k]));
-                if (hi[p]) wi[p] = mulT(Rr, xyz(Si.v[k]) - t);
-            }
             // bit p of bi (bj): every vertex of j (i) this lane holds lies
             // more than thr beyond supporting plane p of i (j); no early exit
             // and one group reduction at the end, so the plane loads of
-            // successive planes overlap
+            // successive planes overlap.  VP vertices of each body per lane,
+            // as few as the replica's shapes need: with VP for
+            // DEM_MAX_VERTS throughout, half of the plane tests of bodies
+            // with 8 vertices or fewer were made on empty slots.
             unsigned bi = 0, bj = 0;
-            const int nsi = live ? Si.nsep : 0, nsj = live ? Sj.nsep : 0;
-#pragma unroll 2
-            for (int p = 0; p < nsi; ++p) {
-                const Vec4<T> pl = Si.sp[p];
-                bool all = true;
+            auto planes = [&](auto vp) {
+                constexpr int VP = decltype(vp)::value;
+                V3<T> wj[VP], wi[VP];  // this lane's vertices: j's in i's frame, i's in j's frame
+                bool hj[VP], hi[VP];
 #pragma unroll
-                for (int v = 0; v < kVP; ++v) {
-                    all &= !hj[v] || plane_gap(pl, wj[v]) > thr;
-                    c_pv.add(hj[v] ? 1 : 0);
+                for (int p = 0; p < VP; ++p) {
+                    const int k = p * kSepLanes + sub1;
+                    hj[p] = live && k < Sj.nv;
+                    hi[p] = live && k < Si.nv;
+                    wj[p] = t + mul(Rr, xyz(Sj.v[k]));
+                    wi[p] = mulT(Rr, xyz(Si.v[k]) - t);
                 }
-                bi |= (all ? 1u : 0u) << p;
-            }
+                const int nsi = live ? Si.nsep : 0, nsj = live ? Sj.nsep : 0;
 #pragma unroll 2
-            for (int p = 0; p < nsj; ++p) {
-                const Vec4<T> pl = Sj.sp[p];
-                bool all = true;
+                for (int p = 0; p < nsi; ++p) {
+                    const Vec4<T> pl = Si.sp[p];
+                    bool all = true;
 #pragma unroll
-                for (int v = 0; v < kVP; ++v) {
-                    all &= !hi[v] || plane_gap(pl, wi[v]) > thr;
-                    c_pv.add(hi[v] ? 1 : 0);
+                    for (int v = 0; v < VP; ++v) {
+                        all &= !hj[v] || plane_gap(pl, wj[v]) > thr;
+                        c_pv.add(hj[v] ? 1 : 0);
+                    }
+                    bi |= (all ? 1u : 0u) << p;
                 }
-                bj |= (all ? 1u : 0u) << p;
-            }
+#pragma unroll 2
+                for (int p = 0; p < nsj; ++p) {
+                    const Vec4<T> pl = Sj.sp[p];
+                    bool all = true;
+#pragma unroll
+                    for (int v = 0; v < VP; ++v) {
+                        all &= !hi[v] || plane_gap(pl, wi[v]) > thr;
+                        c_pv.add(hi[v] ? 1 : 0);
+                    }
+                    bj |= (all ? 1u : 0u) << p;
+                }
+            };
+            if (kSepLanes == 4 && rl.wide == 0.0) planes(std::integral_constant<int, kSepLanes == 4 ? 2 : 1>());
+            else planes(std::integral_constant<int, kVP>());
             for (int off = 1; off < kSepLanes; off <<= 1) {
                 bi &= __shfl_xor(bi, off, kSepLanes);
                 bj &= __shfl_xor(bj, off, kSepLanes);
@@ -1433,6 +1462,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             }
             tail += __popcll(m);
         }
+        if (more && lane1 < kPairsPerWave) nxt[lane1] = ent1;
         wave_sync_lds();  // the queue entries are visible to every lane
         ++tt;
     }
@@ -2011,9 +2041,10 @@ size_t pair_kernel_lds(int precision, int tab_slots, int lanes, int sep, int sta
     const size_t pl = precision == DEM_FP32 ? sizeof(PairLds<float>) : sizeof(PairLds<double>);
     const size_t qe = precision == DEM_FP32 ? sizeof(QEnt<float>) : sizeof(QEnt<double>);
     const size_t acc = precision == DEM_FP32 ? sizeof(Acc<float>) : sizeof(Acc<double>);
+    const size_t en = kWaves * (64 / sep) * sizeof(int4);  // entry slots
     if (stage == kSearchOnly)  // tables, replica, and the last workgroup's scan
-        return (size_t)tab_slots * w + sizeof(RepLds) + sizeof(int) * 64 * kWaves;
-    return (size_t)tab_slots * w + sizeof(RepLds) + kWaves * (64 / lanes) * pl + kWaves * queue_slots(sep, lanes) * qe +
+        return en + (size_t)tab_slots * w + sizeof(RepLds) + sizeof(int) * 64 * kWaves;
+    return en + (size_t)tab_slots * w + sizeof(RepLds) + kWaves * (64 / lanes) * pl + kWaves * queue_slots(sep, lanes) * qe +
            (lanes == 16 ? kWaves * 64 * acc : 0) + (fc ? kWaves * (64 / lanes) * sizeof(PairFc) : 0);
 }
 

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "dem.h"
@@ -208,7 +209,7 @@ static_assert(sizeof(ShapeTab<float>) % 16 == 0 && sizeof(ShapeTab<double>) % 16
 // of one replica.  Indices into batch arrays are global particle slots;
 // replica r owns slots [off, off + n), cells [coff, coff + ncell] and pair
 // slots [poff, poff + pcap).
-struct SysParams {
+struct alignas(16) SysParams {
     int n, dim, n_shapes, live;
     int off;                     // first particle slot (a multiple of kChunk)
     int coff;                    // first cell slot (ncell + 1 entries of cell_start)
@@ -219,11 +220,16 @@ struct SysParams {
     int use_cells;               // 1 if every periodic axis has >= 3 cells
     int ensemble;
     int rid;                     // replica slot
+    // what the pair kernel needs of its replica, in this order and on a
+    // 16-byte boundary: its workgroups copy the block as it is (RepLds)
     double box[3];
+    double eps, par_s2;
+    double R[DEM_MAX_SHAPES];    // circumradius about the body origin
+    double rad[DEM_MAX_SHAPES];  // rounding radius
+    double wide;                 // 1 if some shape has more than 8 vertices, else 0
     double cellw[3];             // box / nc
     double rl2;                  // r_list^2
     double disp2;                // (rebuild_frac * skin)^2
-    double eps, par_s2;
     double dt, kT, g, Qm;
     // DEM_NPT (Sec. IV.C): target pressure, barostat mass W = (N_f + d) kT
     // tau_P^2, alpha = 1 + d / N_f with N_f = d (n - 1); the box at the last
@@ -236,9 +242,12 @@ struct SysParams {
     int nc0[3], pad_npt;
     double mass[DEM_MAX_SHAPES];
     double inertia[DEM_MAX_SHAPES][3];
-    double R[DEM_MAX_SHAPES];    // circumradius about the body origin
-    double rad[DEM_MAX_SHAPES];  // rounding radius
 };
+static_assert(offsetof(SysParams, box) % 16 == 0, "the pair kernel copies box .. wide in 16-byte words");
+constexpr int kPairConst = 6 + 2 * DEM_MAX_SHAPES;  // doubles from box to wide
+static_assert(offsetof(SysParams, wide) + sizeof(double) == offsetof(SysParams, box) + kPairConst * sizeof(double),
+              "box .. wide are contiguous");
+static_assert(kPairConst % 2 == 0, "whole 16-byte words");
 
 // Batch-wide parameters, passed by value to every kernel.
 struct BatchParams {

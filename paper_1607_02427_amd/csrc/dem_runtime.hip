@@ -1000,6 +1000,7 @@ dem_status describe_replica(dem_system *h, const dem_params &p, Replica &R, std:
         sp.mass[s] = p.shapes[s].mass;
         for (int a = 0; a < 3; ++a) sp.inertia[s][a] = (p.dim == 2 && a < 2) ? 0.0 : p.shapes[s].inertia[a];
         sp.R[s] = tabs[s].R;
+        if (tabs[s].nv > 8) sp.wide = 1.0;
         sp.rad[s] = p.shapes[s].rounding_radius;
         Rmax = std::max(Rmax, tabs[s].R);
         rmax = std::max(rmax, p.shapes[s].rounding_radius);
