@@ -1530,41 +1530,6 @@ __device__ inline void body_torque(const double q[4], double tx, double ty, doub
     out[2] = R[2] * tx + R[5] * ty + R[8] * tz;
 }
 
-template <int NT>
-__device__ inline double block_sum(double v, double *sh)
-{
-    if constexpr (NT == 64) {
-        // one wavefront: the same pairs as the tree below (lane t adds
-        // lane t + off), through lane shuffles instead of LDS and barriers
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        return __shfl(v, 0, 64);
-    } else {
-        const int t = threadIdx.x;
-        sh[t] = v;
-        __syncthreads();
-        for (int off = NT / 2; off > 0; off >>= 1) {
-            if (t < off) sh[t] += sh[t + off];
-            __syncthreads();
-        }
-        const double r = sh[0];
-        __syncthreads();
-        return r;
-    }
-}
-
-// Nose-Hoover half step of length dt/2 on xi and eta (one variable for
-// translation and rotation); returns the velocity scale and updates K.
-__device__ inline double nh_half(const SysParams &p, double &xi, double &eta, double &K)
-{
-    const double h = 0.5 * p.dt;
-    xi += 0.5 * h * (2.0 * K - p.g * p.kT) / p.Qm;
-    const double sc = exp(-xi * h);
-    K *= sc * sc;
-    eta += xi * h;
-    xi += 0.5 * h * (2.0 * K - p.g * p.kT) / p.Qm;
-    return sc;
-}
-
 // Per-particle sums of the row-slot records, optionally fused with the
 // closing kick.  One block per chunk, so a block belongs to one replica.
 // Each particle's row is split over kGatherLanes lanes (lane l takes slots
@@ -1624,23 +1589,40 @@ __device__ void step_rows(const BatchParams &b, const SysParams *reps, const Sta
     }
 }
 
+// A replica's step is done: its budget and count, and its rebuild flags
+// moved on to the next step.
+__device__ inline void step_done(int32_t *fl, int32_t *gflags, int built, int64_t *budget, int64_t *steps)
+{
+    *budget -= 1;
+    *steps += 1;
+    if (built != 0) {  // this step's lists are built: count them
+        fl[FLAG_REBUILD] = 0;
+        fl[FLAG_NBUILDS] += 1;
+        atomicSub(&gflags[G_ANY], 1);
+    }
+    if (fl[FLAG_TRIGGER] != 0) {  // the next step rebuilds
+        fl[FLAG_TRIGGER] = 0;
+        fl[FLAG_REBUILD] = 1;
+        atomicAdd(&gflags[G_ANY], 1);
+    }
+}
+
 template <typename T, int DIM, bool KICK>
 __global__ void __launch_bounds__(kGatherBlock) k_gather(BatchParams b, const SysParams *reps, StatePtrs s, OutPtrs o,
                                                       ListPtrs l, const SlotRec<T> *__restrict__ rec, double *ke_part,
                                                       double *thermo, int64_t *budget, int64_t *steps)
 {
-    __shared__ double sh[kGatherBlock];
     const int G = KICK ? pad8(b.nchunk) : (int)gridDim.x;  // chunk workgroups
     if (KICK && (int)blockIdx.x >= G) {
         __shared__ int rbuf[lb::kNbrPer * kRowMax];
-        if (l.gflags[G_ANY] != 0) step_rows<DIM>(b, reps, s, l, budget, rbuf, G);
+        if (l.gflags[G_NOW] != 0) step_rows<DIM>(b, reps, s, l, budget, rbuf, G);
         return;
     }
     constexpr int kB = gather_batch<T>();
     const int sub = threadIdx.x % kGatherLanes;
     const int cb = xcd_block(blockIdx.x, G);  // this block's chunk
     const int i = cb * kGatherPer + threadIdx.x / kGatherLanes;
-    if (KICK && blockIdx.x == 0 && threadIdx.x == 0) l.gflags[G_FILL] = l.gflags[G_ANY];  // for the replica tail
+    if (KICK && blockIdx.x == 0 && threadIdx.x == 0) l.gflags[G_FILL] = l.gflags[G_NOW];  // whether pair entries are to be written
     // what depends on the slot alone is requested with the replica's
     // parameters instead of after them (the state only within the length
     // of its arrays).  The records are those of the rows the pair kernel
@@ -1668,20 +1650,37 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather(BatchParams b, const Sy
         }
     }
     const unsigned stamp = (unsigned)l.gflags[G_STAMP];  // records of this evaluation only
-    const int r = cb < b.nchunk ? l.chunk_rep[cb] : -1;
+    const int r = chunk_replica(b, l.chunk_rep, cb);
     if (r < 0) return;
     const SysParams &p = reps[r];
+    const bool active = KICK && l.flags[r * FLAG_COUNT + FLAG_ACTIVE] != 0;
     if (KICK && threadIdx.x == 0 && cb == p.off / kChunk) {
-        // whether the replica tail writes this step's new pair entries (the
-        // tail itself moves the rebuild flag on)
+        // one thread per replica: this step's build has its pair entries to
+        // write; folded, the step's bookkeeping too (nothing written here is
+        // read by another workgroup of this kernel)
         int32_t *fl = l.flags + r * FLAG_COUNT;
-        fl[FLAG_FILL] = (fl[FLAG_REBUILD] != 0 && budget[r] > 0) ? 1 : 0;
+        const int built = fl[FLAG_BUILD];
+        fl[FLAG_FILL] = built;
+        if (b.fold) {
+            double *th = thermo + r * TH_COUNT;
+            if (fl[FLAG_CLOSE] != 0) {
+                th[TH_XI] = th[TH_S_XI];
+                th[TH_ETA] = th[TH_S_ETA];
+                th[TH_SB] = th[TH_S_SB];
+                th[TH_SA] = th[TH_S_SA];
+                th[TH_XI_B] = th[TH_S_XI_B];
+                th[TH_ETA_B] = th[TH_S_ETA_B];
+                th[TH_OPEN] = 1.0;
+            }
+            fl[FLAG_PEND] = active && p.ensemble == DEM_NVT ? 1 : 0;
+            if (active) step_done(fl, l.gflags, built, &budget[r], &steps[r]);
+        }
     }
-    if (KICK && budget[r] <= 0) return;
+    if (KICK && !active) return;
     const bool npt = KICK && p.ensemble == DEM_NPT;
     const bool nvt = KICK && (p.ensemble == DEM_NVT || npt);
     const size_t N = (size_t)b.N;
-    const bool mine = i < p.off + p.n;
+    const bool mine = i >= p.off && i < p.off + p.n;
     double acc[16];
     for (int c = 0; c < 16; ++c) acc[c] = 0.0;  // F[3], T[3], U, W[9]
     if (mine) {
@@ -1764,9 +1763,10 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather(BatchParams b, const Sy
         }
     }
     if (!nvt) return;
-    kt = block_sum<kGatherBlock>(kt, sh);
-    kr = block_sum<kGatherBlock>(kr, sh);
-    if (npt) tw = block_sum<kGatherBlock>(tw, sh);
+    static_assert(kGatherBlock == 64, "one wavefront per workgroup");
+    kt = wave_sum(kt);
+    kr = wave_sum(kr);
+    if (npt) tw = wave_sum(tw);
     if (threadIdx.x == 0) {
         ke_part[kKePer * cb] = kt;
         ke_part[kKePer * cb + 1] = kr;
@@ -1774,45 +1774,22 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather(BatchParams b, const Sy
     }
 }
 
-// The end of a step for each replica (one block per replica slot, after
-// k_gather): the thermostat's closing half step and the next step's
-// opening half step from the kinetic energy after the closing kick (the
-// gather's partial sums per chunk, added in chunk order), the step budget
-// and count, and the list-rebuild transitions: this step's build is
-// counted, and a trigger raised during the step schedules a build for the
-// next step.  A kernel of its own, so the partial sums are visible without
-// a device-wide fence in every gather block.  Workgroups beyond the
-// replica slots carry the end of the step's list build: the tile plan (the
-// first of them) and the pair entries of every chunk of a replica that
-// rebuilds (FLAG_FILL, which the tail workgroups do not touch), one chunk
-// per workgroup at a time; the cells are emptied for the next build.
+// The end of a step for each replica where the steps are not folded (one
+// block per replica slot, after k_gather): the thermostat's closing half
+// step and the next step's opening half step from the kinetic energy after
+// the closing kick (the gather's partial sums per chunk, added in chunk
+// order), the step budget and count, and the list-rebuild transitions.  A
+// kernel of its own, so the partial sums are visible without a device-wide
+// fence in every gather block.  Workgroups beyond the replica slots carry
+// the end of the step's list build (lb::fill_step).
 __global__ void __launch_bounds__(kGatherBlock) k_replica_tail(BatchParams b, SysParams *reps, ListPtrs l,
                                                                const double *ke_part, double *thermo, int64_t *budget,
                                                                int64_t *steps)
 {
-    __shared__ double sh[kGatherBlock];
     if ((int)blockIdx.x >= b.nrep) {
         static_assert(kGatherBlock == kChunk, "one wavefront per chunk");
         __shared__ int part[kGatherBlock];
-        if (l.gflags[G_FILL] == 0) return;
-        const int fb = (int)blockIdx.x - b.nrep, nfb = (int)gridDim.x - b.nrep;
-        if (fb == 0)
-            lb::plan<kGatherBlock>(b, reps, l, part, [&](int r) {
-                return reps[r].n > 0 && l.flags[r * FLAG_COUNT + FLAG_FILL] != 0;
-            });
-        // the replicas that rebuild, 64 at a time; their chunks dealt over
-        // the fill workgroups from a replica-dependent start
-        for (int r0 = 0; r0 < b.nrep; r0 += 64) {
-            const int rl = r0 + (int)__lane_id();
-            const bool bld = rl < b.nrep && reps[rl].live && reps[rl].n > 0 && l.flags[rl * FLAG_COUNT + FLAG_FILL] != 0;
-            for (unsigned long long m = __ballot(bld); m != 0ull; m &= m - 1ull) {
-                const int r = r0 + __builtin_ctzll(m);
-                const SysParams &p = reps[r];
-                const int c0 = p.off / kChunk, nc = (p.n + kChunk - 1) / kChunk;
-                for (int k = (fb + nfb - (int)(((long long)r * 977) % nfb)) % nfb; k < nc; k += nfb)
-                    lb::fill_chunk(b, p, l, c0 + k, false, true);
-            }
-        }
+        lb::fill_step(b, reps, l, (int)blockIdx.x - b.nrep, (int)gridDim.x - b.nrep, part);
         return;
     }
     const int r = blockIdx.x;
@@ -1821,7 +1798,7 @@ __global__ void __launch_bounds__(kGatherBlock) k_replica_tail(BatchParams b, Sy
     // the slot's step values are requested together with its parameters
     // (the thermostat slots exist for every replica slot)
     const int64_t left = budget[r];
-    const int32_t rebuilt = fl[FLAG_REBUILD], trigger = fl[FLAG_TRIGGER];
+    const int32_t rebuilt = fl[FLAG_REBUILD];
     const double xi0 = th[TH_XI], eta0 = th[TH_ETA];
     SysParams &p = reps[r];
     if (!p.live || p.n == 0 || left <= 0) return;
@@ -1839,9 +1816,9 @@ __global__ void __launch_bounds__(kGatherBlock) k_replica_tail(BatchParams b, Sy
             ar += ke_part[kKePer * (c0 + c) + 1];
             aw += ke_part[kKePer * (c0 + c) + 2];
         }
-        double Kt2 = 2.0 * block_sum<kGatherBlock>(at, sh);
-        const double Kr2 = 2.0 * block_sum<kGatherBlock>(ar, sh);
-        const double trW = block_sum<kGatherBlock>(aw, sh);
+        double Kt2 = 2.0 * wave_sum(at);
+        const double Kr2 = 2.0 * wave_sum(ar);
+        const double trW = wave_sum(aw);
         if (threadIdx.x == 0) {
             double xi = xi0, eta = eta0, veps = th[TH_VEPS];
             baro_half(p, Kt2, trW, veps);
@@ -1872,42 +1849,19 @@ __global__ void __launch_bounds__(kGatherBlock) k_replica_tail(BatchParams b, Sy
         }
     }
     if (p.ensemble == DEM_NVT) {
-        const int nblk = (p.n + kChunk - 1) / kChunk;
-        const int c0 = p.off / kChunk;
-        double acc2 = 0.0;
-        // unrolled so that many loads are in flight at once (large
-        // replicas have thousands of chunks); the sums keep their order
-#pragma unroll 8
-        for (int c = threadIdx.x; c < nblk; c += blockDim.x)
-            acc2 += ke_part[kKePer * (c0 + c)] + ke_part[kKePer * (c0 + c) + 1];
-        double K = block_sum<kGatherBlock>(acc2, sh);
+        const double K = kinetic_total(p, ke_part);
         if (threadIdx.x == 0) {
-            double xi = xi0, eta = eta0;
-            const double sb = nh_half(p, xi, eta, K);  // closes this step
-            th[TH_XI_B] = xi;
-            th[TH_ETA_B] = eta;
-            th[TH_SB] = sb;
-            const double sa = nh_half(p, xi, eta, K);  // opens the next step
-            th[TH_XI] = xi;
-            th[TH_ETA] = eta;
-            th[TH_SA] = sa;
+            const NhStep s = nh_step(p, xi0, eta0, 0.0, 0.0, K, true);
+            th[TH_XI_B] = s.xi_b;
+            th[TH_ETA_B] = s.eta_b;
+            th[TH_SB] = s.sb;
+            th[TH_XI] = s.xi;
+            th[TH_ETA] = s.eta;
+            th[TH_SA] = s.sa;
             th[TH_OPEN] = 1.0;
         }
     }
-    if (threadIdx.x == 0) {
-        budget[r] = left - 1;
-        steps[r] += 1;
-        if (rebuilt != 0) {  // this step's lists are built: count them
-            fl[FLAG_REBUILD] = 0;
-            fl[FLAG_NBUILDS] += 1;
-            atomicSub(&l.gflags[G_ANY], 1);
-        }
-        if (trigger != 0) {  // the next step rebuilds
-            fl[FLAG_TRIGGER] = 0;
-            fl[FLAG_REBUILD] = 1;
-            atomicAdd(&l.gflags[G_ANY], 1);
-        }
-    }
+    if (threadIdx.x == 0) step_done(fl, l.gflags, rebuilt, &budget[r], &steps[r]);
 }
 
 template <typename T>
@@ -1989,8 +1943,9 @@ void gather_t(const Launch &L, bool kick, hipStream_t stream)
     if (kick) {
         k_gather<T, DIM, true><<<pad8(L.b.nchunk) + row_workgroups(L.b), kGatherBlock, 0, stream>>>(
             L.b, L.reps, L.s, L.o, L.l, rec, L.ke_part, L.thermo, L.budget, L.steps);
-        k_replica_tail<<<L.b.nrep + std::min(L.b.nchunk, 1024), kGatherBlock, 0, stream>>>(
-            L.b, const_cast<SysParams *>(L.reps), L.l, L.ke_part, L.thermo, L.budget, L.steps);
+        if (!L.b.fold)
+            k_replica_tail<<<L.b.nrep + std::min(L.b.nchunk, kFillWorkgroups), kGatherBlock, 0, stream>>>(
+                L.b, const_cast<SysParams *>(L.reps), L.l, L.ke_part, L.thermo, L.budget, L.steps);
     }
     else
         k_gather<T, DIM, false><<<pad8(L.b.nchunk), kGatherBlock, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, rec, L.ke_part,

@@ -13,13 +13,15 @@
 //   xi += h/2 (2K - g kT)/Q;  (v, L) *= exp(-xi h);  eta += xi h;
 //   xi += h/2 (2K - g kT)/Q,
 // with g = d N + d_rot N - d and Q = g kT tau_T^2.  The closing half step
-// of a step and the opening half step of the next are computed together by
-// k_replica_tail, one workgroup per replica after the force gather
-// (dem_force.hip); their velocity factors are applied by the next
-// kick-drift, and at the end
-// of a call k_scale applies the closing factor alone, so a captured step
-// needs no extra pass over the particles.
+// of a step and the opening half step of the next are computed together
+// from the gather's kinetic partials, by the next kick-drift (folded steps)
+// or by k_replica_tail (dem_force.hip); their velocity factors are applied
+// by that kick-drift, and at the end of a call k_close applies the closing
+// factor alone, so a captured step needs no extra pass over the particles.
+#include <algorithm>
+
 #include "dem_internal.h"
+#include "dem_listbuild.h"
 
 namespace dem {
 namespace {
@@ -95,109 +97,98 @@ __device__ inline double block_sum(double v, double *sh)
     return r;
 }
 
-// Nose-Hoover half step on xi, eta; returns the velocity scale, updates K.
-__device__ inline double nh_half(const SysParams &p, double &xi, double &eta, double &K)
-{
-    const double h = 0.5 * p.dt;
-    xi += 0.5 * h * (2.0 * K - p.g * p.kT) / p.Qm;
-    const double sc = exp(-xi * h);
-    K *= sc * sc;
-    eta += xi * h;
-    xi += 0.5 * h * (2.0 * K - p.g * p.kT) / p.Qm;
-    return sc;
-}
-
-// Replica of the wave's particles (chunks never straddle replicas), or -1.
-__device__ inline int wave_replica(const BatchParams &b, const ListPtrs &l, int i)
-{
-    const int c = i / kChunk;
-    return __builtin_amdgcn_readfirstlane(c < b.nchunk ? l.chunk_rep[c] : -1);
-}
-
-// Opening half step of a closed replica's next step, one workgroup per
-// replica, from its kinetic partials (one per chunk, summed in order).
-__global__ void __launch_bounds__(kBlock) k_nh_begin(BatchParams b, const SysParams *reps, const double *ke_part,
+// Opening half step of a closed replica's next step, one wavefront per
+// replica, from its kinetic partials, where the steps are not folded (a
+// folded step's kick-drift forms its own); then the box of an NPT replica
+// moves on to the box of its next step (TH_GROW times the box of the
+// positions; k_commit moves it back at the end of the call).
+__global__ void __launch_bounds__(kChunk) k_nh_begin(BatchParams b, SysParams *reps, ListPtrs l, const double *ke_part,
                                                         double *thermo, const int64_t *budget)
 {
-    __shared__ double sh[kBlock];
-    const SysParams &p = reps[blockIdx.x];
+    SysParams &p = reps[blockIdx.x];
     double *th = thermo + blockIdx.x * TH_COUNT;
-    if (!p.live || p.n == 0 || (p.ensemble != DEM_NVT && p.ensemble != DEM_NPT) || budget[blockIdx.x] <= 0 ||
-        th[TH_OPEN] != 0.0)
-        return;
-    const int c0 = p.off / kChunk, nc = (p.n + kChunk - 1) / kChunk;
+    if (!p.live || p.n == 0 || (p.ensemble != DEM_NVT && p.ensemble != DEM_NPT) || budget[blockIdx.x] <= 0) return;
+    const bool closed = th[TH_OPEN] == 0.0;
     if (p.ensemble == DEM_NPT) {
-        // thermostat half step, then barostat half step (from K_trans after
-        // it, the virial of the current forces and the current box)
-        double at = 0.0, ar = 0.0, aw = 0.0;
-        for (int c = threadIdx.x; c < nc; c += blockDim.x) {
-            at += ke_part[kKePer * (c0 + c)];
-            ar += ke_part[kKePer * (c0 + c) + 1];
-            aw += ke_part[kKePer * (c0 + c) + 2];
+        double grow = th[TH_GROW];
+        if (closed) {
+            // thermostat half step, then barostat half step (from K_trans
+            // after it, the virial of the current forces and the current box)
+            const int c0 = p.off / kChunk, nc = (p.n + kChunk - 1) / kChunk;
+            double at = 0.0, ar = 0.0, aw = 0.0;
+            for (int c = threadIdx.x; c < nc; c += blockDim.x) {
+                at += ke_part[kKePer * (c0 + c)];
+                ar += ke_part[kKePer * (c0 + c) + 1];
+                aw += ke_part[kKePer * (c0 + c) + 2];
+            }
+            double Kt2 = 2.0 * wave_sum(at);
+            const double Kr2 = 2.0 * wave_sum(ar);
+            const double trW = wave_sum(aw);
+            if (threadIdx.x == 0) {
+                double xi = th[TH_XI], eta = th[TH_ETA], veps = th[TH_VEPS];
+                double K2 = Kt2 + Kr2;
+                const double sa = nh_half_npt(p, xi, eta, K2, veps);
+                Kt2 *= sa * sa;
+                baro_half(p, Kt2, trW, veps);
+                th[TH_XI] = xi;
+                th[TH_ETA] = eta;
+                th[TH_VEPS] = veps;
+                th[TH_SB] = 1.0;
+                th[TH_SA] = sa;
+                th[TH_OPEN] = 1.0;
+                npt_factors(p, veps, th);
+                grow = th[TH_GROW];
+            }
         }
-        double Kt2 = 2.0 * block_sum<kBlock>(at, sh);
-        const double Kr2 = 2.0 * block_sum<kBlock>(ar, sh);
-        const double trW = block_sum<kBlock>(aw, sh);
-        if (threadIdx.x != 0) return;
-        double xi = th[TH_XI], eta = th[TH_ETA], veps = th[TH_VEPS];
-        double K2 = Kt2 + Kr2;
-        const double sa = nh_half_npt(p, xi, eta, K2, veps);
-        Kt2 *= sa * sa;
-        baro_half(p, Kt2, trW, veps);
-        th[TH_XI] = xi;
-        th[TH_ETA] = eta;
-        th[TH_VEPS] = veps;
-        th[TH_SB] = 1.0;
-        th[TH_SA] = sa;
-        th[TH_OPEN] = 1.0;
-        npt_factors(p, veps, th);
+        if (threadIdx.x == 0) {
+            const double box[3] = {th[TH_BOXN] * grow, th[TH_BOXN + 1] * grow, th[TH_BOXN + 2] * grow};
+            set_box(p, box, l.flags + blockIdx.x * FLAG_COUNT);
+        }
         return;
     }
-    double acc = 0.0;
-    for (int c = threadIdx.x; c < nc; c += blockDim.x)
-        acc += ke_part[kKePer * (c0 + c)] + ke_part[kKePer * (c0 + c) + 1];
-    double K = block_sum<kBlock>(acc, sh);
+    if (!closed) return;
+    const double K = kinetic_total(p, ke_part);
     if (threadIdx.x != 0) return;
-    double xi = th[TH_XI], eta = th[TH_ETA];
-    const double sa = nh_half(p, xi, eta, K);
-    th[TH_XI] = xi;
-    th[TH_ETA] = eta;
+    const NhStep s = nh_step(p, th[TH_XI], th[TH_ETA], 0.0, 0.0, K, false);
+    th[TH_XI] = s.xi;
+    th[TH_ETA] = s.eta;
     th[TH_SB] = 1.0;
-    th[TH_SA] = sa;
+    th[TH_SA] = s.sa;
     th[TH_OPEN] = 1.0;
 }
 
-// Start of a call: an NPT replica's box moves on to the box of its next
-// step (TH_GROW times the box of the positions); end of a call: back to the
-// box of the positions, which the tail of every step keeps in TH_BOXN.
-__global__ void k_box_open(int nrep, SysParams *reps, ListPtrs l, const double *thermo, const int64_t *budget)
+// End of a call, per chunk: the velocities take the pending closing factor,
+// which folded steps form here first (the last step's partials; staged for
+// k_commit).  Folded, workgroups beyond the chunks write the pair entries
+// of a build in the last step.
+__global__ void __launch_bounds__(kChunk) k_close(BatchParams b, const SysParams *reps, StatePtrs s, ListPtrs l,
+                                                     const double *ke_part, double *thermo)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrep) return;
-    SysParams &p = reps[r];
-    const double *th = thermo + r * TH_COUNT;
-    if (!p.live || p.ensemble != DEM_NPT || budget[r] <= 0) return;
-    const double box[3] = {th[TH_BOXN] * th[TH_GROW], th[TH_BOXN + 1] * th[TH_GROW], th[TH_BOXN + 2] * th[TH_GROW]};
-    set_box(p, box, l.flags + r * FLAG_COUNT);
-}
-
-__global__ void k_box_close(int nrep, SysParams *reps, ListPtrs l, const double *thermo)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrep) return;
-    SysParams &p = reps[r];
-    if (!p.live || p.ensemble != DEM_NPT) return;
-    set_box(p, thermo + r * TH_COUNT + TH_BOXN, l.flags + r * FLAG_COUNT);
-}
-
-// End of a call: the velocities take the pending closing factor.
-__global__ void k_scale(BatchParams b, const SysParams *reps, StatePtrs s, ListPtrs l, const double *thermo)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int r = wave_replica(b, l, i);
-    if (r < 0 || i >= reps[r].off + reps[r].n) return;
-    const double sc = thermo[r * TH_COUNT + TH_SB];
-    if ((reps[r].ensemble != DEM_NVT && reps[r].ensemble != DEM_NPT) || sc == 1.0) return;
+    const int G = pad8(b.nchunk);
+    if ((int)blockIdx.x >= G) {
+        __shared__ int part[kChunk];
+        lb::fill_step(b, reps, l, (int)blockIdx.x - G, (int)gridDim.x - G, part);
+        return;
+    }
+    const int c = xcd_block(blockIdx.x, G), i = c * kChunk + threadIdx.x;
+    const int r = chunk_replica(b, l.chunk_rep, c);
+    if (r < 0) return;
+    const SysParams &p = reps[r];
+    if (p.ensemble != DEM_NVT && p.ensemble != DEM_NPT) return;
+    double *th = thermo + r * TH_COUNT;
+    double sc = th[TH_SB];
+    if (b.fold && l.flags[r * FLAG_COUNT + FLAG_PEND] != 0) {
+        const NhStep n = nh_step(p, th[TH_XI], th[TH_ETA], th[TH_XI_B], th[TH_ETA_B], kinetic_total(p, ke_part), true);
+        sc = n.sb;
+        if (threadIdx.x == 0 && c == p.off / kChunk) {
+            th[TH_S_XI] = n.xi;
+            th[TH_S_ETA] = n.eta;
+            th[TH_S_SA] = n.sa;
+            th[TH_S_XI_B] = n.xi_b;
+            th[TH_S_ETA_B] = n.eta_b;
+        }
+    }
+    if (i < p.off || i >= p.off + p.n || sc == 1.0) return;
     s.vx[i] *= sc;
     s.vy[i] *= sc;
     s.vz[i] *= sc;
@@ -206,19 +197,51 @@ __global__ void k_scale(BatchParams b, const SysParams *reps, StatePtrs s, ListP
     s.Lz[i] *= sc;
 }
 
-__global__ void k_nh_close(int nrep, double *thermo)
+// End of a call, per replica: the staged thermostat words, the closing
+// factor applied, nothing left to fill, and an NPT replica's box back to
+// the box of its positions, which the tail of every step keeps in TH_BOXN.
+__global__ void k_commit(BatchParams b, SysParams *reps, ListPtrs l, double *thermo)
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < nrep) thermo[r * TH_COUNT + TH_SB] = 1.0;
+    if (r == 0) l.gflags[G_FILL] = 0;
+    if (r >= b.nrep) return;
+    int32_t *fl = l.flags + r * FLAG_COUNT;
+    double *th = thermo + r * TH_COUNT;
+    if (fl[FLAG_PEND] != 0) {
+        th[TH_XI] = th[TH_S_XI];
+        th[TH_ETA] = th[TH_S_ETA];
+        th[TH_SA] = th[TH_S_SA];
+        th[TH_XI_B] = th[TH_S_XI_B];
+        th[TH_ETA_B] = th[TH_S_ETA_B];
+        fl[FLAG_PEND] = 0;
+    }
+    th[TH_SB] = 1.0;
+    fl[FLAG_FILL] = 0;
+    SysParams &p = reps[r];
+    if (p.live && p.ensemble == DEM_NPT) set_box(p, th + TH_BOXN, fl);
 }
 
 template <typename T, int DIM>
 __global__ void __launch_bounds__(kChunk) k_kick_drift(BatchParams b, const SysParams *reps, StatePtrs s, OutPtrs o,
-                                                          ListPtrs l, const double *thermo, const int64_t *budget,
-                                                          void *rot, PartRec64 *rec64)
+                                                          ListPtrs l, const double *ke_part, double *thermo,
+                                                          const int64_t *budget, void *rot, PartRec64 *rec64)
 {
-    const int i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (i == 0) l.gflags[G_STAMP] += 1;  // this step's force evaluation
+    const int G = pad8(b.nchunk);  // chunk workgroups
+    if ((int)blockIdx.x >= G) {
+        // folded steps: the pair entries of the build of the step before
+        // (its cells and offsets are not touched by a chunk workgroup: no
+        // replica rebuilds in two steps running, as a step that rebuilds
+        // raises no trigger)
+        __shared__ int part[kChunk];
+        lb::fill_step(b, reps, l, (int)blockIdx.x - G, (int)gridDim.x - G, part);
+        return;
+    }
+    const int cb = xcd_block(blockIdx.x, G);  // this block's chunk
+    const int i = cb * kChunk + threadIdx.x;
+    if (i == 0) {
+        l.gflags[G_STAMP] += 1;  // this step's force evaluation
+        l.gflags[G_NOW] = l.gflags[G_ANY];
+    }
     // the particle's own values are requested with the replica's parameters
     // instead of after them (within the length of the state arrays)
     double q[4] = {1.0, 0.0, 0.0, 0.0}, v0[3] = {0.0, 0.0, 0.0}, L0[3] = {0.0, 0.0, 0.0};
@@ -254,23 +277,49 @@ __global__ void __launch_bounds__(kChunk) k_kick_drift(BatchParams b, const SysP
     double xl[3] = {0.0, 0.0, 0.0};  // position at the last list build (the library's N slots)
     if (i < b.N)
         for (int a = 0; a < DIM; ++a) xl[a] = l.xlast[(size_t)a * b.N + i];
-    const int r = wave_replica(b, l, i);
+    int r = chunk_replica(b, l.chunk_rep, cb);
     if (r < 0) return;
+    r = __builtin_amdgcn_readfirstlane(r);
     // the replica's per-step values are requested together with its
     // parameters, not one round trip after another (this kernel writes
-    // none of them; the thermostat slots exist for every replica)
+    // none that another workgroup reads; the thermostat slots exist for
+    // every replica)
     const int64_t left = budget[r];
-    const double *thr = thermo + r * TH_COUNT;
-    const double th_sb = thr[TH_SB], th_sa = thr[TH_SA];
-    const int32_t rebuild = l.flags[r * FLAG_COUNT + FLAG_REBUILD];
+    double *thr = thermo + r * TH_COUNT;
+    int32_t *fl = l.flags + r * FLAG_COUNT;
+    double sb = thr[TH_SB], sa = thr[TH_SA];
+    const double xi0 = thr[TH_XI], eta0 = thr[TH_ETA], xib0 = thr[TH_XI_B], etab0 = thr[TH_ETA_B], open = thr[TH_OPEN];
+    const int32_t rebuild = fl[FLAG_REBUILD], pend = fl[FLAG_PEND];
     const SysParams &p = reps[r];
-    if (i >= p.off + p.n || left <= 0) return;
     // pending thermostat factors: the closing half step of the last step,
-    // then the opening half step of this one (1 and 1 without a thermostat)
+    // then the opening half step of this one (1 and 1 without a thermostat).
+    // Folded steps form them here, the same in every workgroup of the
+    // replica, from the partials of the step before (or, for the first step
+    // of a closed replica, of k_kinetic)
     const bool npt = p.ensemble == DEM_NPT;
-    const bool nvt = p.ensemble == DEM_NVT || npt;
-    const double sb = nvt ? th_sb : 1.0;
-    const double sa = nvt ? th_sa : 1.0;
+    const bool lead = threadIdx.x == 0 && cb == p.off / kChunk;
+    const bool close = b.fold && pend != 0;
+    const bool form = close || (b.fold && p.ensemble == DEM_NVT && left > 0 && open == 0.0);
+    if (form) {
+        const NhStep n = nh_step(p, xi0, eta0, xib0, etab0, kinetic_total(p, ke_part), close);
+        sb = n.sb;
+        sa = n.sa;
+        if (lead) {  // for the gather to commit
+            thr[TH_S_XI] = n.xi;
+            thr[TH_S_ETA] = n.eta;
+            thr[TH_S_SB] = n.sb;
+            thr[TH_S_SA] = n.sa;
+            thr[TH_S_XI_B] = n.xi_b;
+            thr[TH_S_ETA_B] = n.eta_b;
+        }
+    }
+    if (lead) {
+        fl[FLAG_CLOSE] = form ? 1 : 0;
+        fl[FLAG_ACTIVE] = left > 0 ? 1 : 0;
+        fl[FLAG_BUILD] = rebuild != 0 && left > 0 ? 1 : 0;
+    }
+    if (i < p.off || i >= p.off + p.n || left <= 0) return;
+    if (p.ensemble != DEM_NVT && !npt) sb = sa = 1.0;
     const double hm = 0.5 * p.dt / p.mass[sid];
     const double I[3] = {p.inertia[sid][0], p.inertia[sid][1], p.inertia[sid][2]};
     double v[3] = {(v0[0] * sb) * sa + hm * F0[0], (v0[1] * sb) * sa + hm * F0[1], 0.0};
@@ -391,18 +440,19 @@ __global__ void __launch_bounds__(kChunk) k_kick_drift(BatchParams b, const SysP
         atomicOr(&l.flags[r * FLAG_COUNT + FLAG_NONFINITE], 1);
 }
 
-// Per-chunk kinetic partials of the current state, with the particle-to-
-// block mapping of the gather (one chunk per block).
+// Per-chunk kinetic partials of the current state of the replicas whose
+// next step has yet to be opened, with the particle-to-block mapping of the
+// gather (one chunk per block).
 __global__ void __launch_bounds__(kGatherBlock) k_kinetic(BatchParams b, const SysParams *reps, StatePtrs s, OutPtrs o,
-                                                       ListPtrs l, double *ke_part)
+                                                       ListPtrs l, const double *thermo, double *ke_part)
 {
-    __shared__ double sh[kGatherBlock];
-    const int r = l.chunk_rep[blockIdx.x];
+    const int r = chunk_replica(b, l.chunk_rep, blockIdx.x);
     if (r < 0) return;
     const SysParams &p = reps[r];
+    if ((p.ensemble != DEM_NVT && p.ensemble != DEM_NPT) || thermo[r * TH_COUNT + TH_OPEN] != 0.0) return;
     const int i = blockIdx.x * kGatherPer + threadIdx.x / kGatherLanes;
     double kt = 0.0, kr = 0.0, tw = 0.0;
-    if (i < p.off + p.n && (threadIdx.x % kGatherLanes) == 0) {
+    if (i >= p.off && i < p.off + p.n && (threadIdx.x % kGatherLanes) == 0) {
         const int sid = s.sid[i];
         const double m = p.mass[sid];
         kt = 0.5 * m * (s.vx[i] * s.vx[i] + s.vy[i] * s.vy[i] + s.vz[i] * s.vz[i]);
@@ -412,9 +462,9 @@ __global__ void __launch_bounds__(kGatherBlock) k_kinetic(BatchParams b, const S
         if (p.ensemble == DEM_NPT)
             tw = o.W[i] + o.W[(size_t)4 * b.wstride + i] + (p.dim == 3 ? o.W[(size_t)8 * b.wstride + i] : 0.0);
     }
-    kt = block_sum<kGatherBlock>(kt, sh);
-    kr = block_sum<kGatherBlock>(kr, sh);
-    tw = block_sum<kGatherBlock>(tw, sh);
+    kt = wave_sum(kt);
+    kr = wave_sum(kr);
+    tw = wave_sum(tw);
     if (threadIdx.x == 0) {
         ke_part[kKePer * blockIdx.x] = kt;
         ke_part[kKePer * blockIdx.x + 1] = kr;
@@ -452,21 +502,23 @@ __global__ void __launch_bounds__(kChunk) k_energy_partials(BatchParams b, const
 
 }  // namespace
 
-void launch_nh_begin(const Launch &L, hipStream_t stream)
+void launch_begin(const Launch &L, hipStream_t stream)
 {
-    if (L.b.nrep == 0) return;
-    k_nh_begin<<<L.b.nrep, kBlock, 0, stream>>>(L.b, L.reps, L.ke_part, L.thermo, L.budget);
-    k_box_open<<<blocks_for(L.b.nrep), kBlock, 0, stream>>>(L.b.nrep, const_cast<SysParams *>(L.reps), L.l, L.thermo,
-                                                          L.budget);
+    if (L.b.nrep == 0 || L.b.nchunk == 0 || !L.b.thermal) return;
+    k_kinetic<<<L.b.nchunk, kGatherBlock, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, L.thermo, L.ke_part);
+    if (!L.b.fold)
+        k_nh_begin<<<L.b.nrep, kChunk, 0, stream>>>(L.b, const_cast<SysParams *>(L.reps), L.l, L.ke_part, L.thermo, L.budget);
 }
 
-void launch_nh_end(const Launch &L, hipStream_t stream)
+// workgroups of a folded step's kernels that write pair entries
+static int fill_workgroups(const BatchParams &b) { return b.fold ? std::min(b.nchunk, kFillWorkgroups) : 0; }
+
+void launch_end(const Launch &L, hipStream_t stream)
 {
     if (L.b.nrep == 0) return;
-    const int nr = (L.b.nrep + kBlock - 1) / kBlock;
-    if (L.b.nchunk > 0) k_scale<<<blocks_for(L.b.nchunk * kChunk), kBlock, 0, stream>>>(L.b, L.reps, L.s, L.l, L.thermo);
-    k_nh_close<<<nr, kBlock, 0, stream>>>(L.b.nrep, L.thermo);
-    k_box_close<<<nr, kBlock, 0, stream>>>(L.b.nrep, const_cast<SysParams *>(L.reps), L.l, L.thermo);
+    if (L.b.nchunk > 0 && (L.b.thermal || L.b.fold))
+        k_close<<<pad8(L.b.nchunk) + fill_workgroups(L.b), kChunk, 0, stream>>>(L.b, L.reps, L.s, L.l, L.ke_part, L.thermo);
+    k_commit<<<(L.b.nrep + kBlock - 1) / kBlock, kBlock, 0, stream>>>(L.b, const_cast<SysParams *>(L.reps), L.l, L.thermo);
 }
 
 template <typename T>
@@ -474,12 +526,12 @@ void kick_drift_t(const Launch &L, hipStream_t stream)
 {
     // one wavefront (one chunk) per block: the chunks spread over as many
     // CUs as there are chunks
-    const int nb = pad8(L.b.nchunk);
+    const int nb = pad8(L.b.nchunk) + fill_workgroups(L.b);
     if (L.b.dim == 3)
-        k_kick_drift<T, 3><<<nb, kChunk, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, L.thermo, L.budget, L.f.rot,
+        k_kick_drift<T, 3><<<nb, kChunk, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, L.ke_part, L.thermo, L.budget, L.f.rot,
                                                        L.f.rec64);
     else
-        k_kick_drift<T, 2><<<nb, kChunk, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, L.thermo, L.budget, L.f.rot,
+        k_kick_drift<T, 2><<<nb, kChunk, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, L.ke_part, L.thermo, L.budget, L.f.rot,
                                                        L.f.rec64);
 }
 
@@ -488,12 +540,6 @@ void launch_kick_drift(const Launch &L, hipStream_t stream)
     if (L.b.nchunk == 0) return;
     if (L.precision == DEM_FP32) kick_drift_t<float>(L, stream);
     else kick_drift_t<double>(L, stream);
-}
-
-void launch_kinetic(const Launch &L, hipStream_t stream)
-{
-    if (L.b.nchunk == 0) return;
-    k_kinetic<<<L.b.nchunk, kGatherBlock, 0, stream>>>(L.b, L.reps, L.s, L.o, L.l, L.ke_part);
 }
 
 void launch_energy_partials(const Launch &L, double *part, hipStream_t stream)

@@ -54,19 +54,40 @@ constexpr int kSearchOcc = 4;  // wavefronts per SIMD of the search kernel
 // FLAG_REBUILD: the current step rebuilds them (from the positions after
 // its drift; the new lists serve from the next step on).  FLAG_NPAIRS: pair
 // entries of the lists in use; FLAG_NEWPAIRS: those of the build under way.
-// FLAG_FILL: the current step's build writes its pair entries (a copy of
-// FLAG_REBUILD taken by the gather, for the extra workgroups of the replica
-// tail, while the tail itself moves FLAG_REBUILD on to the next step).
+// The words of one step, written by one thread per replica in the
+// kick-drift for the gather, which moves the words above on to the next
+// step while its other workgroups read these: FLAG_ACTIVE (the replica has
+// steps left), FLAG_BUILD (and rebuilds its lists), FLAG_CLOSE (its
+// thermostat slot holds staged values to commit).  FLAG_FILL: the step's
+// build still has its pair entries to write (the gather's copy of
+// FLAG_BUILD, for the next kick-drift, or the replica tail).  FLAG_PEND: the
+// step's closing and the next step's opening thermostat half steps are
+// still to be computed from its kinetic partials.
 enum Flag {
-    FLAG_REBUILD = 0, FLAG_NBUILDS = 1, FLAG_MAXROW = 2, FLAG_NONFINITE = 3, FLAG_NPAIRS = 4,
-    FLAG_TRIGGER = 6, FLAG_CELLOVF = 7, FLAG_NEWPAIRS = 9, FLAG_FILL = 10, FLAG_BOXSMALL = 11, FLAG_COUNT = 16
+    FLAG_REBUILD = 0, FLAG_NBUILDS = 1, FLAG_MAXROW = 2, FLAG_NONFINITE = 3, FLAG_NPAIRS = 4, FLAG_CLOSE = 5,
+    FLAG_TRIGGER = 6, FLAG_CELLOVF = 7, FLAG_PEND = 8, FLAG_NEWPAIRS = 9, FLAG_FILL = 10, FLAG_BOXSMALL = 11,
+    FLAG_ACTIVE = 12, FLAG_BUILD = 13, FLAG_COUNT = 16
 };
 // Batch-wide words.  G_ANY: how many replicas rebuild their lists in the
-// current step (the list workgroups of the step kernels return at once
-// when none does); G_FILL: its copy taken by the gather, for the replica
-// tail.  G_STAMP: number of the current force evaluation (bumped before
-// every launch of the pair kernel in a step or a force computation).
-enum GWord { G_ANY = 0, G_STAMP = 1, G_FILL = 2, G_COUNT = 4 };
+// current step; G_NOW: its copy taken by the kick-drift, for the gather (the
+// list workgroups of the step kernels return at once when it is zero);
+// G_FILL: that copy taken by the gather, for the workgroups that write the
+// pair entries.  G_STAMP: number of the current force evaluation (bumped
+// before every launch of the pair kernel in a step or a force computation).
+enum GWord { G_ANY = 0, G_STAMP = 1, G_FILL = 2, G_NOW = 3, G_COUNT = 4 };
+// A step is kick-drift, pairs, gather, and the replica tail's work.  Folded
+// (BatchParams::fold), the kick-drift of the next step carries that work:
+// every workgroup sums its replica's kinetic partials and forms the same
+// thermostat factors, one of them stages the new thermostat words, and the
+// gather commits them and moves the step counts and rebuild flags on; so a
+// step is three kernels instead of four (per step: 4096 FP64 cubes 38.7 ->
+// 35.5 us, 1024 FP64 squares 19.2 -> 18.1 us, 64,000 spheres, 1000 chunks,
+// 48.6 -> 46.3 us, 262,144 octahedra, 4096 chunks, 570 -> 566 us).  Not
+// folded under the barostat, whose box every kernel reads while the tail
+// moves it, nor when a replica has more than kFoldChunks chunks: each of its
+// workgroups reads all of its partials, which grows as the square and no
+// longer gains at 4096.
+constexpr int kFoldChunks = 4096;
 // Particles one cell can hold, and the longest neighbour row.
 constexpr int kCellCap = 64;
 constexpr int kRowMax = 128;
@@ -88,8 +109,11 @@ constexpr int lb_rows_per_group = 4;
 // TH_DAMP = exp(-alpha v_eps h/2), TH_FK = (h/2) exp(-alpha v_eps h/4)
 // sinhc(alpha v_eps h/4), TH_GROW = exp(v_eps h), TH_VFAC = h exp(v_eps h/2)
 // sinhc(v_eps h/2) (sinhc(u) = sinh(u) / u).
+// TH_S_*: staged values of a folded step (written by the kick-drift,
+// committed by the gather).
 enum Thermo {
-    TH_XI = 0, TH_ETA = 1, TH_SB = 2, TH_SA = 3, TH_XI_B = 4, TH_ETA_B = 5, TH_OPEN = 6,
+    TH_XI = 0, TH_ETA = 1, TH_SB = 2, TH_SA = 3, TH_XI_B = 4, TH_ETA_B = 5, TH_OPEN = 6, TH_S_XI = 7,
+    TH_S_ETA = 14, TH_S_SB = 15, TH_S_SA = 19, TH_S_XI_B = 20, TH_S_ETA_B = 21,
     TH_VEPS = 8, TH_VEPS_B = 9, TH_DAMP = 10, TH_FK = 11, TH_GROW = 12, TH_VFAC = 13, TH_BOXN = 16, TH_COUNT = 24
 };
 // (TH_BOXN..TH_BOXN + 2: the box of the current positions.  Inside a call
@@ -268,7 +292,17 @@ struct BatchParams {
     int feature_cells;           // 1: the feature search reads the shape-local feature cells
     int search_blocks;           // grid of the search kernel of the split form
     int dim;
+    int fold;                    // 1: the kick-drift carries the replica tail of the step before
+    int thermal;                 // 1: some replica has a thermostat
 };
+constexpr int kFillWorkgroups = 1024;  // at most this many workgroups write a step's pair entries
+// Replica of chunk c, or -1; the only replica of a batch of one is known
+// without a look at the table (its callers check the particle range).
+__device__ inline int chunk_replica(const BatchParams &b, const int32_t *chunk_rep, int c)
+{
+    if (c >= b.nchunk) return -1;
+    return b.nrep == 1 ? 0 : chunk_rep[c];
+}
 
 struct StatePtrs {
     double *x, *y, *z, *qw, *qx, *qy, *qz, *vx, *vy, *vz, *Lx, *Ly, *Lz;
@@ -366,6 +400,58 @@ struct Launch {
     int64_t *budget;             // [replica] steps left; a replica with none left is held still
     int64_t *steps;              // [replica] steps done
 };
+
+// Sum over the 64 lanes of a one-wavefront workgroup, in every lane: the
+// pairs of a binary tree (lane t adds lane t + off).
+__device__ inline double wave_sum(double v)
+{
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    return __shfl(v, 0, 64);
+}
+
+// Nose-Hoover half step of length dt/2 on xi and eta (one variable for
+// translation and rotation); returns the velocity scale and updates K.
+// Rounded as written, so that every kernel that carries it gives the same
+// bits.
+__device__ inline double nh_half(const SysParams &p, double &xi, double &eta, double &K)
+{
+#pragma clang fp contract(off)
+    const double h = 0.5 * p.dt;
+    xi += 0.5 * h * (2.0 * K - p.g * p.kT) / p.Qm;
+    const double sc = exp(-xi * h);
+    K *= sc * sc;
+    eta += xi * h;
+    xi += 0.5 * h * (2.0 * K - p.g * p.kT) / p.Qm;
+    return sc;
+}
+
+// Kinetic energy of replica p (a thermostat's) from its chunks' partials, by
+// one wavefront, in chunk order.
+__device__ inline double kinetic_total(const SysParams &p, const double *ke_part)
+{
+    const int nblk = (p.n + kChunk - 1) / kChunk, c0 = p.off / kChunk;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int c = __lane_id(); c < nblk; c += 64) acc += ke_part[kKePer * (c0 + c)] + ke_part[kKePer * (c0 + c) + 1];
+    return wave_sum(acc);
+}
+
+// The thermostat words of a replica between two steps: the closing half
+// step of the step before (close) and the opening one of the next.
+struct NhStep {
+    double xi, eta, sb, sa, xi_b, eta_b;
+};
+__device__ inline NhStep nh_step(const SysParams &p, double xi, double eta, double xi_b, double eta_b, double K, bool close)
+{
+    NhStep s{xi, eta, 1.0, 1.0, xi_b, eta_b};
+    if (close) {
+        s.sb = nh_half(p, s.xi, s.eta, K);
+        s.xi_b = s.xi;
+        s.eta_b = s.eta;
+    }
+    s.sa = nh_half(p, s.xi, s.eta, K);
+    return s;
+}
 
 // ---- isothermal-isobaric steps (DEM_NPT, Sec. IV.C) ----------------------
 // The barostat follows the measure-preserving isotropic scheme the paper
@@ -493,14 +579,13 @@ void launch_pairs(const Launch &L, unsigned long long *stats, hipStream_t stream
 // the pair entries and the tile plan of the step's list build.
 void launch_gather(const Launch &L, bool kick, hipStream_t stream);
 
-// Integrator pieces.  With NVT the step tail after the gather applies the
-// closing half step of the step and the opening half step of the next one;
-// launch_nh_begin opens the first step of a closed replica,
-// launch_nh_end applies the pending closing factor to the velocities.
-void launch_nh_begin(const Launch &L, hipStream_t stream);
+// Integrator pieces.  launch_begin prepares the opening half step of a
+// closed replica's first step; launch_end closes a call: the last step's
+// tail if the steps are folded, the pending closing factor on the
+// velocities, and the box of the positions.
+void launch_begin(const Launch &L, hipStream_t stream);
 void launch_kick_drift(const Launch &L, hipStream_t stream);
-void launch_kinetic(const Launch &L, hipStream_t stream);
-void launch_nh_end(const Launch &L, hipStream_t stream);
+void launch_end(const Launch &L, hipStream_t stream);
 // Per-chunk partials of U, K_trans, K_rot and W (9): part[12 * chunk + c].
 void launch_energy_partials(const Launch &L, double *part, hipStream_t stream);
 void launch_energy_totals(const Launch &L, int c0, int nchunks, double *part, double *total, hipStream_t stream);

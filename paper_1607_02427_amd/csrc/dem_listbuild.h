@@ -55,7 +55,7 @@ __device__ inline unsigned long long lanes_below()
 __device__ inline bool building(int mode, int r, const SysParams &p, const int32_t *fl, const int64_t *budget)
 {
     if (!p.live) return false;
-    if (mode == LISTS_STEP) return fl[FLAG_REBUILD] != 0 && budget[r] > 0;
+    if (mode == LISTS_STEP) return fl[FLAG_BUILD] != 0;
     if (mode == LISTS_REFILL) return fl[FLAG_NBUILDS] > 0;
     return mode == LISTS_ALL || mode == r;
 }
@@ -270,6 +270,30 @@ __device__ void plan(const BatchParams &b, const SysParams *reps, const ListPtrs
     __syncthreads();
     const int total = block_scan<NT>(l.tile_start, l.tile_start, b.nrep, part);
     if (threadIdx.x == 0) l.tile_start[b.nrep] = total;
+}
+
+// The end of a step's list build, by workgroup fb of nfb (64 threads each):
+// the tile plan (the first of them) and the pair entries of every chunk of
+// the replicas with FLAG_FILL, one chunk per workgroup at a time; the cells
+// are emptied for the next build.  part: 64 ints of LDS.
+__device__ inline void fill_step(const BatchParams &b, const SysParams *reps, const ListPtrs &l, int fb, int nfb, int *part)
+{
+    if (l.gflags[G_FILL] == 0) return;
+    if (fb == 0)
+        plan<kChunk>(b, reps, l, part, [&](int r) { return reps[r].n > 0 && l.flags[r * FLAG_COUNT + FLAG_FILL] != 0; });
+    // the replicas that rebuild, 64 at a time; their chunks dealt over
+    // the fill workgroups from a replica-dependent start
+    for (int r0 = 0; r0 < b.nrep; r0 += 64) {
+        const int rl = r0 + (int)__lane_id();
+        const bool bld = rl < b.nrep && reps[rl].live && reps[rl].n > 0 && l.flags[rl * FLAG_COUNT + FLAG_FILL] != 0;
+        for (unsigned long long m = __ballot(bld); m != 0ull; m &= m - 1ull) {
+            const int r = r0 + __builtin_ctzll(m);
+            const SysParams &p = reps[r];
+            const int c0 = p.off / kChunk, nc = (p.n + kChunk - 1) / kChunk;
+            for (int k = (fb + nfb - (int)(((long long)r * 977) % nfb)) % nfb; k < nc; k += nfb)
+                fill_chunk(b, p, l, c0 + k, false, true);
+        }
+    }
 }
 
 }  // namespace lb

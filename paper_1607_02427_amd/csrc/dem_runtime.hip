@@ -638,12 +638,16 @@ void refresh_batch(dem_system *h)
     b.pair_split = h->pair_split;
     b.feature_cells = h->feature_cells;
     b.tile = pair_tile(h->pair_sep);
+    b.thermal = 0;
+    b.fold = 1;
     long long tiles = 0;
     for (size_t r = 0; r < h->reps.size(); ++r) {
         const Replica &R = h->reps[r];
         if (!R.live) continue;
         b.nrep = (int)r + 1;
         b.tab_slots = std::max(b.tab_slots, R.sp.n_shapes);
+        if (R.sp.ensemble != DEM_NVE) b.thermal = 1;
+        if (R.sp.ensemble == DEM_NPT || R.nchunks > kFoldChunks) b.fold = 0;
         tiles += tiles_of(R.sp.pcap, b.tile);
     }
     b.nchunk = h->chunks.high();
@@ -1316,13 +1320,11 @@ dem_status run_steps(dem_system *h, int64_t n_steps)
     dem_status st = ensure_graph(h);
     if (st != DEM_OK) return st;
     const Launch L = make_launch(h);
-    // opening half step of the first step, from the current kinetic energy
-    launch_kinetic(L, h->stream);
-    launch_nh_begin(L, h->stream);
+    launch_begin(L, h->stream);
     int64_t k = 0;
     for (; k + kGraphSteps <= n_steps; k += kGraphSteps) HIPCHK(h, hipGraphLaunch(h->gexec_multi, h->stream));
     for (; k < n_steps; ++k) HIPCHK(h, hipGraphLaunch(h->gexec, h->stream));
-    launch_nh_end(L, h->stream);
+    launch_end(L, h->stream);
     HIPCHK(h, hipGetLastError());
     return DEM_OK;
 }
