@@ -268,8 +268,8 @@ dem_status dem_time_forces(dem_handle h, int32_t reps, double *mean_ms);
  * the feature stage, so a 64-lane wavefront takes 8 or 4 pairs at a time;
  * the grid holds grid_factor (1 to 4) times as many workgroups as the
  * device keeps resident at once; waves_per_simd (2 or 3) is kept so that
- * calls stay valid: one build, for 3 resident wavefronts per SIMD, serves
- * both; and sep_lanes (4, or 16 with
+ * calls stay valid: one build serves both (3 resident wavefronts per SIMD
+ * in FP32, 2 in FP64); and sep_lanes (4, or 16 with
  * 16 lanes per pair) lanes take one pair in the separation stage, so a
  * wavefront settles 16 or 4 pairs at a time and a tile holds 64 or 16
  * pairs (16 spreads a small system over four times the wavefronts).

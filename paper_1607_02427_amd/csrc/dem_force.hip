@@ -1892,17 +1892,20 @@ void pairs_t(const Launch &L, unsigned long long *stats, hipStream_t stream);
 // stage, 16 lanes with the 16-lane one; in the split form, the search kernel
 // (4-lane separation stage, kSearchOcc wavefronts per SIMD) and then the
 // force kernel at 8 or 16 lanes.  Each feature stage with the supporting-
-// plane prefilter or with the shape-local feature cells (FC).  All are built
-// for 3 wavefronts per SIMD (168 registers), whether the shape asks for 2 or
-// 3: a build for 2 was no faster on any of twelve workloads (4096 FP64
-// cubes 24.0 us against 24.2-24.7, 16 lanes) and, where it takes more than
-// 168 registers, slower (8 lanes, 262,144 octahedra: 698 us against 536).
-// The FC feature stage does not fit 168 registers and is built for 2.
+// plane prefilter or with the shape-local feature cells (FC).
+// One build serves shapes that ask for 2 and for 3 wavefronts per SIMD.  In
+// FP32 it is for 3 (168 registers): a build for 2 was no faster on any of
+// eight workloads and, where it takes more than 168 registers, slower (8
+// lanes, 262,144 octahedra: 698 us against 536).  In FP64 it is for 2: the
+// LDS of a workgroup lets a CU hold two, whatever the registers.  So is the
+// FC feature stage, which does not fit 168 registers.
+template <typename T, bool FC>
+constexpr int pair_occ() { return FC || sizeof(T) == 8 ? 2 : 3; }
 template <typename T, int DIM, bool FC>
 void pairs_form(const Launch &L, unsigned long long *stats, hipStream_t stream)
 {
     const bool g8 = L.b.pair_lanes == 8;
-    constexpr int O = FC ? 2 : 3;
+    constexpr int O = pair_occ<T, FC>();
     if (L.b.pair_split) {
         pairs_t<T, DIM, 16, kSearchOcc, 4, kSearchOnly, false>(L, stats, stream);
         g8 ? pairs_t<T, DIM, 8, O, 4, kForces, FC>(L, stats, stream) : pairs_t<T, DIM, 16, O, 4, kForces, FC>(L, stats, stream);
@@ -2009,7 +2012,7 @@ hipError_t pair_occupancy(int *per_cu, size_t lds, int lanes, int sep)
 {
     const int t = 64 * kWaves;
     auto occ = [&](auto kernel) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kernel, t, lds); };
-    constexpr int O = FC ? 2 : 3;
+    constexpr int O = pair_occ<T, FC>();
     if constexpr (STAGE == kSearchOnly) {
         return occ(k_pairs<T, DIM, 16, false, kSearchOcc, 4, kSearchOnly, false>);
     } else {
