@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(kChunk) k_nh_begin(BatchParams b, SysParams *r
         return;
     }
     if (!closed) return;
-    const double K = kinetic_total(p, ke_part);
+    const double K = kinetic_total(p, ke_part, b.N);
     if (threadIdx.x != 0) return;
     const NhStep s = nh_step(p, th[TH_XI], th[TH_ETA], 0.0, 0.0, K, false);
     th[TH_XI] = s.xi;
@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(kChunk) k_close(BatchParams b, const SysParams
     double *th = thermo + r * TH_COUNT;
     double sc = th[TH_SB];
     if (b.fold && l.flags[r * FLAG_COUNT + FLAG_PEND] != 0) {
-        const NhStep n = nh_step(p, th[TH_XI], th[TH_ETA], th[TH_XI_B], th[TH_ETA_B], kinetic_total(p, ke_part), true);
+        const NhStep n = nh_step(p, th[TH_XI], th[TH_ETA], th[TH_XI_B], th[TH_ETA_B], kinetic_total(p, ke_part, b.N), true);
         sc = n.sb;
         if (threadIdx.x == 0 && c == p.off / kChunk) {
             th[TH_S_XI] = n.xi;
@@ -301,7 +301,7 @@ __global__ void __launch_bounds__(kChunk) k_kick_drift(BatchParams b, const SysP
     const bool close = b.fold && pend != 0;
     const bool form = close || (b.fold && p.ensemble == DEM_NVT && left > 0 && open == 0.0);
     if (form) {
-        const NhStep n = nh_step(p, xi0, eta0, xib0, etab0, kinetic_total(p, ke_part), close);
+        const NhStep n = nh_step(p, xi0, eta0, xib0, etab0, kinetic_total(p, ke_part, b.N), close);
         sb = n.sb;
         sa = n.sa;
         if (lead) {  // for the gather to commit
@@ -466,9 +466,7 @@ __global__ void __launch_bounds__(kGatherBlock) k_kinetic(BatchParams b, const S
     kr = wave_sum(kr);
     tw = wave_sum(tw);
     if (threadIdx.x == 0) {
-        ke_part[kKePer * blockIdx.x] = kt;
-        ke_part[kKePer * blockIdx.x + 1] = kr;
-        ke_part[kKePer * blockIdx.x + 2] = tw;
+        put_kinetic(ke_part, b.N, blockIdx.x, kt, kr, tw);
     }
 }
 

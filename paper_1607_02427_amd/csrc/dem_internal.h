@@ -425,14 +425,26 @@ __device__ inline double nh_half(const SysParams &p, double &xi, double &eta, do
     return sc;
 }
 
+// One chunk's partials: K_trans, K_rot and tr W, and K_trans + K_rot once
+// more in an array of its own behind them, so that a wavefront that sums a
+// whole replica's kinetic energy reads 8 contiguous bytes a chunk.
+__device__ inline void put_kinetic(double *ke_part, int N, int chunk, double kt, double kr, double tw)
+{
+    ke_part[kKePer * chunk] = kt;
+    ke_part[kKePer * chunk + 1] = kr;
+    ke_part[kKePer * chunk + 2] = tw;
+    ke_part[(size_t)kKePer * (N / kChunk) + chunk] = kt + kr;
+}
+
 // Kinetic energy of replica p (a thermostat's) from its chunks' partials, by
 // one wavefront, in chunk order.
-__device__ inline double kinetic_total(const SysParams &p, const double *ke_part)
+__device__ inline double kinetic_total(const SysParams &p, const double *ke_part, int N)
 {
-    const int nblk = (p.n + kChunk - 1) / kChunk, c0 = p.off / kChunk;
+    const int nblk = (p.n + kChunk - 1) / kChunk;
+    const double *k = ke_part + (size_t)kKePer * (N / kChunk) + p.off / kChunk;
     double acc = 0.0;
 #pragma unroll 8
-    for (int c = __lane_id(); c < nblk; c += 64) acc += ke_part[kKePer * (c0 + c)] + ke_part[kKePer * (c0 + c) + 1];
+    for (int c = __lane_id(); c < nblk; c += 64) acc += k[c];
     return wave_sum(acc);
 }
 

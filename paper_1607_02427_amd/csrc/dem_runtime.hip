@@ -113,8 +113,8 @@ struct dem_system {
     int64_t *budget = nullptr;   // [replica] steps left
     int64_t *steps = nullptr;    // [replica] steps done
     unsigned long long *stats = nullptr;
-    hipGraph_t graph = nullptr, graph_multi = nullptr;  // one step; kGraphSteps steps
-    hipGraphExec_t gexec = nullptr, gexec_multi = nullptr;
+    hipGraph_t graph = nullptr;  // kGraphSteps steps
+    hipGraphExec_t gexec = nullptr;
     std::string err;
 };
 
@@ -624,10 +624,8 @@ void drop_graph(dem_system *h)
 {
     if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
     if (h->graph) (void)hipGraphDestroy(h->graph);
-    if (h->gexec_multi) (void)hipGraphExecDestroy(h->gexec_multi);
-    if (h->graph_multi) (void)hipGraphDestroy(h->graph_multi);
-    h->gexec = h->gexec_multi = nullptr;
-    h->graph = h->graph_multi = nullptr;
+    h->gexec = nullptr;
+    h->graph = nullptr;
 }
 
 Launch make_launch(const dem_system *h)
@@ -824,7 +822,7 @@ dem_status alloc_core(dem_system *h, int Ncap, int Ccap, int Scap, int Rcap)
               hipMalloc(&h->tab64, sizeof(ShapeTab<double>) * Scap) == hipSuccess &&
               hipMalloc(&h->tab32, sizeof(ShapeTab<float>) * Scap) == hipSuccess &&
               hipMalloc(&h->fcells, sizeof(uint2) * kFcCells * Scap) == hipSuccess &&
-              hipMalloc(&h->ke_part, sizeof(double) * kKePer * nch) == hipSuccess &&
+              hipMalloc(&h->ke_part, sizeof(double) * (kKePer + 1) * nch) == hipSuccess &&
               hipMalloc(&h->e_part, sizeof(double) * 12 * nch) == hipSuccess &&
               hipMalloc(&h->thermo, sizeof(double) * TH_COUNT * Rcap) == hipSuccess &&
               hipMalloc(&h->budget, sizeof(int64_t) * Rcap) == hipSuccess &&
@@ -878,7 +876,7 @@ dem_status alloc_core(dem_system *h, int Ncap, int Ccap, int Scap, int Rcap)
     HIPCHK(h, hipMemsetAsync(h->lst.ptot, 0, sizeof(int32_t) * (N / lb_rows_per_group + 1), h->stream));
     HIPCHK(h, hipMemsetAsync(h->lst.pcell, 0, sizeof(int32_t) * N, h->stream));
     HIPCHK(h, hipMemsetAsync(h->stats, 0, kStatBytes, h->stream));
-    HIPCHK(h, hipMemsetAsync(h->ke_part, 0, sizeof(double) * kKePer * nch, h->stream));
+    HIPCHK(h, hipMemsetAsync(h->ke_part, 0, sizeof(double) * (kKePer + 1) * nch, h->stream));
     HIPCHK(h, hipMemsetAsync(h->budget, 0, sizeof(int64_t) * Rcap, h->stream));
     HIPCHK(h, hipMemsetAsync(h->steps, 0, sizeof(int64_t) * Rcap, h->stream));
     return DEM_OK;
@@ -931,9 +929,12 @@ void enqueue_step(dem_system *h, hipStream_t s)
     launch_gather(L, true, s);
 }
 
-// Steps per launch of the long graph: consecutive graph launches leave a
-// gap of several microseconds on the device, which a chain of steps in one
-// graph does not.
+// Steps per graph.  Consecutive graph launches leave a gap of about 8 us on
+// the device, which a chain of steps in one graph does not, and a kernel
+// launched on the stream follows its predecessor about 0.5 us later than a
+// graph's node; so the steps that do not fill a graph are launched on the
+// stream, and a call shorter than a graph captures none.  Graphs of 16 steps
+// gained 0-1% on calls of 64 steps and cost 50-140 us more to instantiate.
 constexpr int kGraphSteps = 8;
 
 dem_status capture_steps(dem_system *h, int steps, hipGraph_t *graph, hipGraphExec_t *exec)
@@ -950,11 +951,9 @@ dem_status capture_steps(dem_system *h, int steps, hipGraph_t *graph, hipGraphEx
 
 dem_status ensure_graph(dem_system *h)
 {
-    if (h->gexec && h->gexec_multi) return DEM_OK;
+    if (h->gexec) return DEM_OK;
     drop_graph(h);
-    dem_status st = capture_steps(h, 1, &h->graph, &h->gexec);
-    if (st == DEM_OK) st = capture_steps(h, kGraphSteps, &h->graph_multi, &h->gexec_multi);
-    return st;
+    return capture_steps(h, kGraphSteps, &h->graph, &h->gexec);
 }
 
 // Builds the lists of replica `only` (all live replicas if LISTS_ALL) from
@@ -1345,13 +1344,13 @@ dem_status run_steps(dem_system *h, int64_t n_steps)
         HIPCHK(h, hipGetLastError());
         return DEM_OK;
     }
-    dem_status st = ensure_graph(h);
-    if (st != DEM_OK) return st;
+    if (n_steps >= kGraphSteps)
+        if (dem_status st = ensure_graph(h); st != DEM_OK) return st;
     const Launch L = make_launch(h);
     launch_begin(L, h->stream);
     int64_t k = 0;
-    for (; k + kGraphSteps <= n_steps; k += kGraphSteps) HIPCHK(h, hipGraphLaunch(h->gexec_multi, h->stream));
-    for (; k < n_steps; ++k) HIPCHK(h, hipGraphLaunch(h->gexec, h->stream));
+    for (; k + kGraphSteps <= n_steps; k += kGraphSteps) HIPCHK(h, hipGraphLaunch(h->gexec, h->stream));
+    for (; k < n_steps; ++k) enqueue_step(h, h->stream);
     launch_end(L, h->stream);
     HIPCHK(h, hipGetLastError());
     return DEM_OK;
@@ -1399,7 +1398,7 @@ size_t dem_footprint_bytes(const dem_params *p)
     const size_t maxp = n * (size_t)cap / 2;
     return sizeof(int32_t) * (n * (size_t)cap + 4 * n + ncell * (1 + kCellCap) + 8 * maxp + nch + 2 * FLAG_COUNT + G_COUNT + 2 +
                               split_words(1)) +
-           sizeof(double) * (3 * n + (kKePer + 12) * nch + TH_COUNT + 2) + kStatBytes +
+           sizeof(double) * (3 * n + (kKePer + 13) * nch + TH_COUNT + 2) + kStatBytes +
            (partrec_bytes(p->precision) + (p->precision == DEM_FP32 ? sizeof(PartRec64) : 0)) * n +
            sizeof(uint2) * kFcCells * DEM_MAX_SHAPES +
            rec_bytes(p->precision) * (size_t)cap * n + sizeof(uint32_t) * (size_t)slot_words(cap) * n + sizeof(SysParams) + 2 * DEM_MAX_SHAPES * sizeof(ShapeTab<double>) + 256;
