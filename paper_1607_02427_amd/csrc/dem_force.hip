@@ -137,7 +137,7 @@ __device__ inline V3<T> face_point(const ShapeTab<T> &S, int f, int fi, V3<T> p)
             }
         }
     } else {
-        const V3<T> e1 = xyz(S.fe1[f]);
+        const V3<T> e1 = v3<T>(S.fe1[f][0], S.fe1[f][1], S.fe1[f][2]);
         const V3<T> e2 = cross(n, e1);
         const V3<T> o = xyz(S.lv[k0]);
         const T px = dot(p - o, e1), py = dot(p - o, e2);
@@ -232,9 +232,10 @@ struct alignas(16) PairLds {
     unsigned char ei_near[DEM_MAX_EDGES], ej_near[DEM_MAX_EDGES];
     unsigned char fi_near[DEM_MAX_FACES], fj_near[DEM_MAX_FACES];
     unsigned short queue[kQueue];
-    // the pair's problem counts and queue length, for the lanes of other
-    // groups that solve its problems in the pooled solve (16 lanes per pair)
-    int nA, nB, nfj, nfi, nej, cnt;
+    // the pair's list lengths, for the lanes of other groups that cull its
+    // problems
+    int nA, nB, nfj, nfi, nej;
+    float inv_fj, inv_fi, inv_ej;
 };
 
 // Feature-cell form of the feature search (one per lane group, beside its
@@ -494,6 +495,48 @@ __device__ inline int add_wca(Acc<T> &A, V3<T> P, V3<T> rho, V3<T> t, T sig2, T 
     return 1;
 }
 
+// The wavefront's groups' counts n (scalar: the same in every lane), laid end
+// to end: their total, and which group item c falls in and where that
+// group's items begin.
+template <int N>
+struct Spans {
+    int n[N];
+    __device__ explicit Spans(const int (&count)[N])
+    {
+#pragma unroll
+        for (int h = 0; h < N; ++h) n[h] = __builtin_amdgcn_readfirstlane(count[h]);
+    }
+    __device__ int total() const
+    {
+        int t = 0;
+#pragma unroll
+        for (int h = 0; h < N; ++h) t += n[h];
+        return t;
+    }
+    __device__ void find(int c, int &g, int &begin) const
+    {
+        int run = 0;
+        g = begin = 0;
+#pragma unroll
+        for (int h = 1; h < N; ++h) {
+            run += n[h - 1];
+            const bool past = c >= run;
+            g = past ? h : g;
+            begin = past ? run : begin;
+        }
+    }
+    __device__ int begin_of(int g) const
+    {
+        int run = 0, o = 0;
+#pragma unroll
+        for (int h = 1; h < N; ++h) {
+            run += n[h - 1];
+            o = g >= h ? run : o;
+        }
+        return o;
+    }
+};
+
 // Sum over the GL lanes of a group of the lanes' two partial sums (a, b):
 // partial sum s of the kVirt canonical ones is a of lane s (s < GL) or b of
 // lane s - GL; the tree pairs s with s + 8 first, then halves.
@@ -710,12 +753,13 @@ __device__ inline M3<T> rel_rotation(const M3<T> &Ri, const M3<T> &Rj)
     return Rr;
 }
 
-// A live pair that no supporting plane separates, parked in its wave's LDS
-// queue until the wave holds one for each of its groups.
+// The pair that a lane group works on in the feature stage (in LDS; lanes of
+// other groups that take its problems read it too).
 template <typename T>
-struct alignas(16) QEnt {
+struct alignas(16) PairGeo {
     int4 ent;    // i, j, slot of j in row i, slot of i in row j (-1: none)
-    int si, sj, pad0, pad1;
+    int si, sj;
+    T rc, sig2;  // cutoff and sigma^2 of the pair
     T Rr[9];     // R_i^T R_j: j's body frame in i's
     T t[3];      // R_i^T d: j's centre in i's frame
     T Ri[9];     // R_i, body to space
@@ -723,10 +767,38 @@ struct alignas(16) QEnt {
 };
 // The separation stage takes SL lanes per pair, so a wavefront settles
 // 64 / SL pairs at a time whatever the feature stage's lane count; a tile
-// is kPairWaves * 64 / SL pairs.
-// queue slots per wave: one separation tile adds at most 64 / SL
-// entries to fewer than one per feature-stage group already waiting
+// is kPairWaves * 64 / SL pairs.  The pairs it keeps wait in the
+// wavefront's LDS queue until it holds one for each of its groups: one
+// separation tile adds at most 64 / SL entries to fewer than one per
+// feature-stage group already waiting.
 constexpr int queue_slots(int sep, int lanes) { return 64 / sep + 64 / lanes; }
+// What waits in the queue: the pair with its transform (PairGeo), so a
+// feature round starts without a round trip (0.8 to 1.1 us of a small
+// system's launch), with 16 lanes per pair and for planar shapes in FP32;
+// otherwise the pair's entry alone, and the round loads the two records
+// again and forms the transform anew, which leaves the LDS for the pooled
+// solve (8 lanes in 3D) or for a second workgroup per CU (FP64).  The force
+// kernel of the split form reads entries.
+template <typename T>
+__host__ __device__ constexpr bool parked(int dim, int lanes, int stage)
+{
+    return sizeof(T) == 4 && stage == kFused && (lanes == 16 || dim == 2);
+}
+// Per wavefront: problems of each group's pair, and those its queue holds.
+template <int kGroups>
+struct alignas(16) WaveCtl {
+    int tot[kGroups], cnt[kGroups];
+};
+// Whether the wavefront's 64 lanes share the solves of all its pairs (their
+// results pass through LDS), and how many results LDS holds at a time: half
+// a wavefront's with 8 lanes in FP64, so that two workgroups still share a
+// CU.  Not with 8 lanes in 2D, where pairs have few problems.
+__host__ __device__ constexpr bool pooled(int dim, int lanes) { return lanes == 16 || dim == 3; }
+template <typename T>
+__host__ __device__ constexpr int pool_results(int lanes)
+{
+    return lanes == 8 && sizeof(T) == 8 ? 32 : 64;
+}
 
 // One block of 4 waves takes a contiguous range of tiles (64 or 16 pairs
 // of one replica each; wave w takes pairs (64 / SL) w .. (64 / SL)(w + 1)
@@ -792,13 +864,19 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     ShapeTab<T> *tab = reinterpret_cast<ShapeTab<T> *>(smem);
     RepLds &rl = *reinterpret_cast<RepLds *>(smem + orl);
     PairLds<T> *pls = reinterpret_cast<PairLds<T> *>(smem + orl + sizeof(RepLds));
-    QEnt<T> *qall = reinterpret_cast<QEnt<T> *>(smem + orl + sizeof(RepLds) + kWaves * kGroups * sizeof(PairLds<T>));
-    // results of one pooled solve step, one per lane (16 lanes per pair only)
-    constexpr bool kPool = kGL == 16;
-    Acc<T> *pres = reinterpret_cast<Acc<T> *>(reinterpret_cast<unsigned char *>(qall) + kWaves * kQCap * sizeof(QEnt<T>));
+    PairGeo<T> *geo = reinterpret_cast<PairGeo<T> *>(pls + kWaves * kGroups);
+    constexpr bool kPark = parked<T>(DIM, GL, STAGE);
+    constexpr int kGeo = kPark ? kQCap : kGroups;  // pairs with transforms per wavefront
+    constexpr int kEnt = kPark ? 0 : kQCap;        // entries without
+    WaveCtl<kGroups> *ctl = reinterpret_cast<WaveCtl<kGroups> *>(geo + kWaves * kGeo);
+    int4 *qall = reinterpret_cast<int4 *>(ctl + kWaves);
+    // results of one pooled solve step, one per lane
+    constexpr bool kPool = pooled(DIM, GL);
+    constexpr int kRes = pool_results<T>(GL);
+    Acc<T> *pres = reinterpret_cast<Acc<T> *>(qall + kWaves * kEnt);
     // the feature-cell form's per-group prefix and edge masks
     PairFc *pfc = reinterpret_cast<PairFc *>(reinterpret_cast<unsigned char *>(pres) +
-                                             (kPool ? kWaves * 64 * sizeof(Acc<T>) : 0));
+                                             (kPool ? kWaves * kRes * sizeof(Acc<T>) : 0));
 
     const int lane = __lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -811,7 +889,9 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     const int grp = lane / kGL, sub = lane % kGL;
     const unsigned long long gmask = ((kGL == 64) ? ~0ull : ((1ull << kGL) - 1)) << (kGL * grp);
     PairLds<T> &W = pls[wid * kGroups + grp];
-    QEnt<T> *qb = qall + wid * kQCap;
+    int4 *qb = qall + wid * kEnt;
+    WaveCtl<kGroups> &wc = ctl[wid];
+    PairGeo<T> *wgeo = geo + wid * kGeo;
     const size_t N = (size_t)b.N;
     // requested with the tile count, not after it: a single system's values,
     // and a batch's first guess
@@ -866,33 +946,72 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             // ---- second stage: group g takes queue entry head + g ----
             const int take = pending < kGroups ? pending : kGroups;
             const bool live = grp < take;
-            // the entry stays in LDS for the whole round (nothing is queued
-            // before the next separation tile): the transform is read from
-            // there where it is used, which keeps registers free for the
-            // solves and the FP64 redo
-            const QEnt<T> &qe = qb[(head + grp) % kQCap];
-            const M3<T> &Rr = *reinterpret_cast<const M3<T> *>(qe.Rr);
-            int si = 0, sj = 0;
-            V3<T> t = v3<T>(0, 0, 0);
-            if (live) {
-                si = qe.si;
-                sj = qe.sj;
-                t = v3<T>(qe.t[0], qe.t[1], qe.t[2]);
-            }
             const int h0 = head;  // the round's first entry
             head += take;
-            const ShapeTab<T> &Si = tab[si];
-            const ShapeTab<T> &Sj = tab[sj];
-            const T par_s2 = (T)rl.par_s2;
-            const T eps = (T)rl.eps;
+            auto geo_of = [&](int g) -> PairGeo<T> & { return wgeo[kPark ? (h0 + g) % kQCap : g]; };
+            PairGeo<T> &G = geo_of(grp);
+            const M3<T> &Rr = *reinterpret_cast<const M3<T> *>(G.Rr);
+            int4 ent = make_int4(0, 0, 0, 0);
+            int si = 0, sj = 0;
+            V3<T> t = v3<T>(0, 0, 0);
             T sig2 = T(0), rc = T(0), Bi = T(0), Bj = T(0);
-            if (live) {
+            if constexpr (kPark) {
+                if (live) {
+                    si = G.si;
+                    sj = G.sj;
+                    t = v3<T>(G.t[0], G.t[1], G.t[2]);
+                    rc = G.rc;
+                    sig2 = G.sig2;
+                    Bi = (T)rl.R[si] + rc;
+                    Bj = (T)rl.R[sj] + rc;
+                }
+            } else {
+                // (groups without a pair repeat the last one's loads and drop it)
+                ent = qb[(h0 + (live ? grp : take - 1)) % kQCap];
+                const PartRec<T> ri = prec[ent.x];
+                const PartRec<T> rj = prec[ent.y];
+                M3<T> Ri, Rj;
+                for (int k = 0; k < 9; ++k) {
+                    Ri.m[k] = ri.R[k];
+                    Rj.m[k] = rj.R[k];
+                }
+                const double dx = min_image_near(rj.x - ri.x, rl.box[0]);
+                const double dy = min_image_near(rj.y - ri.y, rl.box[1]);
+                const double dz = (DIM == 3) ? min_image_near(rj.z - ri.z, rl.box[2]) : 0.0;
+                si = ri.sid;
+                sj = rj.sid;
+                const M3<T> Rrel = rel_rotation(Ri, Rj);
+                t = mulT(Ri, v3<T>((T)dx, (T)dy, (T)dz));
                 const double sigd = rl.rad[si] + rl.rad[sj];
                 sig2 = (T)(sigd * sigd);
                 rc = (T)(kWcaCut * sigd);
                 Bi = (T)rl.R[si] + rc;
                 Bj = (T)rl.R[sj] + rc;
+                if (sub == 0) {
+                    // the transform is read from LDS where it is used, which
+                    // keeps registers free for the solves and the FP64 redo
+                    G.ent = ent;
+                    G.si = si;
+                    G.sj = sj;
+                    G.rc = rc;
+                    G.sig2 = sig2;
+                    for (int k = 0; k < 9; ++k) {
+                        G.Rr[k] = Rrel.m[k];
+                        G.Ri[k] = Ri.m[k];
+                    }
+                    G.t[0] = t.x;
+                    G.t[1] = t.y;
+                    G.t[2] = t.z;
+                    G.d[0] = (T)dx;
+                    G.d[1] = (T)dy;
+                    G.d[2] = (T)dz;
+                }
+                wave_sync_lds();
             }
+            const ShapeTab<T> &Si = tab[si];
+            const ShapeTab<T> &Sj = tab[sj];
+            const T par_s2 = (T)rl.par_s2;
+            const T eps = (T)rl.eps;
             const T rc2 = rc * rc;
             const T rcm = rc * T(1.0001);  // the cull keeps pairs FP32 may place just outside the cutoff
 
@@ -1071,24 +1190,82 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             Acc<T> A0, A1;  // partial sums kVirt-canonical: sub and sub + GL
             A0.F = A0.Ti = A0.Tj = A1.F = A1.Ti = A1.Tj = v3<T>(0, 0, 0);
             A0.U = A1.U = T(0);
+            // Where some pair has more problems than two steps of its own
+            // group would cull (and none so many that its queue could fill
+            // up before its last candidate), the problems of all the
+            // wavefront's pairs are shared out over its 64 lanes: lane c
+            // takes the c-th of the pairs' concatenated problems, so the
+            // cull takes as many steps as the problems need and not as the
+            // busiest pair's; survivors are appended to their pair's queue
+            // in problem order.  With fewer, sharing costs more than the
+            // steps it saves (216 cubes, 16 lanes: 0.9 us of 14).
+            const bool share = __ballot(total > 2 * kGL) != 0 && __ballot(total > kQueue - kVirt) == 0;
             int count = 0;
             for (int qb = 0;; qb += kGL) {
-                const int q = qb + sub;
-                const bool has = q < total;
-                const bool last = __ballot(has) == 0;
-                if (!last) {
-                    const int qc = has ? (FC ? P.fc_code(q) : P.pack(q)) : 0;
-                    const bool keep = has && P.candidate(qc, rcm);
-                    const unsigned long long m = __ballot(keep);
-                    if (keep) W.queue[count + popc_below(m & gmask)] = (unsigned short)qc;
-                    count += __popcll(m & gmask);
+                bool last = share;
+                if (share) {
+                    if (sub == 0) {
+                        W.nA = P.nA;
+                        W.nB = P.nB;
+                        W.nfj = P.nfj;
+                        W.nfi = P.nfi;
+                        W.nej = P.nej;
+                        W.inv_fj = P.inv_fj;
+                        W.inv_fi = P.inv_fi;
+                        W.inv_ej = P.inv_ej;
+                        wc.tot[grp] = total;
+                        wc.cnt[grp] = 0;
+                    }
+                    wave_sync_lds();
+                    const Spans<kGroups> probs(wc.tot);
+                    const int nprob = probs.total();
+                    for (int c0 = 0; c0 < nprob; c0 += 64) {
+                        const int c = c0 + lane;
+                        const bool has = c < nprob;
+                        int g, og;
+                        probs.find(c, g, og);
+                        PairLds<T> &Wg = pls[wid * kGroups + g];
+                        const PairGeo<T> &Gg = geo_of(g);
+                        const Problem<T, DIM, FC> Pg{tab[Gg.si], tab[Gg.sj], Wg,
+                                                     *reinterpret_cast<const M3<T> *>(Gg.Rr), t, Wg.nA, Wg.nB, Wg.nfj,
+                                                     Wg.nfi, Wg.nej, Wg.inv_fj, Wg.inv_fi, Wg.inv_ej,
+                                                     &pfc[FC ? wid * kGroups + g : 0]};
+                        int qc = 0;
+                        bool keep = false;
+                        if (has) {
+                            qc = FC ? Pg.fc_code(c - og) : Pg.pack(c - og);
+                            keep = Pg.candidate(qc, Gg.rc * T(1.0001));
+                        }
+                        // survivors of this pair in earlier steps, in this
+                        // step below this lane, and in this step altogether
+                        const unsigned long long m = __ballot(keep);
+                        const int s0 = og > c0 ? og - c0 : 0;  // the pair's first lane
+                        const unsigned long long mg = m & (~0ull << s0);
+                        const int before = wc.cnt[g] + popc_below(mg);
+                        if (keep) Wg.queue[before] = (unsigned short)qc;
+                        // (the pair's last lane of this step leaves its count)
+                        if (has && (lane == 63 || c + 1 == og + wc.tot[g])) wc.cnt[g] = before + (keep ? 1 : 0);
+                        wave_sync_lds();
+                    }
+                    count = wc.cnt[grp];
+                } else {
+                    const int q = qb + sub;
+                    const bool has = q < total;
+                    last = __ballot(has) == 0;
+                    if (!last) {
+                        const int qc = has ? (FC ? P.fc_code(q) : P.pack(q)) : 0;
+                        const bool keep = has && P.candidate(qc, rcm);
+                        const unsigned long long m = __ballot(keep);
+                        if (keep) W.queue[count + popc_below(m & gmask)] = (unsigned short)qc;
+                        count += __popcll(m & gmask);
+                    }
                 }
                 // rounds end at the same problems for any lane count and any
                 // other pairs in the wavefront: a pair's queue is checked
                 // after each kVirt of its candidates, and only a pair whose
                 // queue is nearly full (or every pair, after its last
                 // candidate) solves it at that point
-                const bool full = (qb + kGL) % kVirt == 0 && count > kQueue - kVirt;
+                const bool full = !share && (qb + kGL) % kVirt == 0 && count > kQueue - kVirt;
                 if (last || __ballot(full) != 0) {
                     const bool mine = last || full;  // this pair solves its queue now
                     wave_sync_lds();
@@ -1101,77 +1278,67 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                         // group) and is added there in problem order, the
                         // order of the unpooled steps, so every pair shape
                         // gives the same bits.
-                        if (sub == 0) {
-                            W.nA = P.nA;
-                            W.nB = P.nB;
-                            W.nfj = P.nfj;
-                            W.nfi = P.nfi;
-                            W.nej = P.nej;
-                            W.cnt = mine ? count : 0;
-                        }
+                        if (sub == 0) wc.cnt[grp] = mine ? count : 0;
                         wave_sync_lds();
-                        int offs[kGroups + 1];
-                        offs[0] = 0;
-#pragma unroll
-                        for (int h = 0; h < kGroups; ++h) offs[h + 1] = offs[h] + pls[wid * kGroups + h].cnt;
-                        Acc<T> *res = pres + wid * 64;
-                        for (int c0 = 0; c0 < offs[kGroups]; c0 += 64) {
+                        const Spans<kGroups> left(wc.cnt);
+                        const int nleft = left.total();
+                        const int o_lo = left.begin_of(grp), o_hi = o_lo + wc.cnt[grp];  // this lane's own pair
+                        Acc<T> *res = pres + wid * kRes;
+                        for (int c0 = 0; c0 < nleft; c0 += 64) {
                             const int c = c0 + lane;
                             Acc<T> A;
                             A.F = A.Ti = A.Tj = v3<T>(0, 0, 0);
                             A.U = T(0);
-                            if (c < offs[kGroups]) {
-                                int g = 0;
-#pragma unroll
-                                for (int h = 1; h < kGroups; ++h) g += c >= offs[h] ? 1 : 0;
+                            if (c < nleft) {
+                                int g, og;
+                                left.find(c, g, og);
                                 const PairLds<T> &Wg = pls[wid * kGroups + g];
-                                const QEnt<T> &qg = qall[wid * kQCap + (h0 + g) % kQCap];
-                                const int gi = qg.si, gj = qg.sj;
+                                const PairGeo<T> &Gg = geo_of(g);
+                                const int gi = Gg.si, gj = Gg.sj;
                                 const ShapeTab<T> &Sgi = tab[gi];
                                 const ShapeTab<T> &Sgj = tab[gj];
-                                const V3<T> tg = v3<T>(qg.t[0], qg.t[1], qg.t[2]);
-                                const Problem<T, DIM, FC> Pg{Sgi, Sgj, Wg, *reinterpret_cast<const M3<T> *>(qg.Rr), tg,
-                                                             Wg.nA, Wg.nB, Wg.nfj, Wg.nfi, Wg.nej,
-                                                             1.0f / (float)(Wg.nfj > 0 ? Wg.nfj : 1),
-                                                             1.0f / (float)(Wg.nfi > 0 ? Wg.nfi : 1),
-                                                             1.0f / (float)(Wg.nej > 0 ? Wg.nej : 1)};
-                                const double sigd = rl.rad[gi] + rl.rad[gj];
-                                const T gsig2 = (T)(sigd * sigd);
-                                const T grc = (T)(kWcaCut * sigd);
+                                const V3<T> tg = v3<T>(Gg.t[0], Gg.t[1], Gg.t[2]);
+                                const Problem<T, DIM, FC> Pg{Sgi, Sgj, Wg, *reinterpret_cast<const M3<T> *>(Gg.Rr), tg,
+                                                             0, 0, 1, 1, 1, 1.f, 1.f, 1.f};
+                                const T gsig2 = Gg.sig2, grc = Gg.rc;
                                 const T grc2 = grc * grc;
                                 V3<T> Pt, rho;
                                 T sin2;
                                 int e, gf;
-                                const int fam = Pg.solve(Wg.queue[c - offs[g]], par_s2, Pt, rho, sin2, e, gf);
+                                const int fam = Pg.solve(Wg.queue[c - og], par_s2, Pt, rho, sin2, e, gf);
                                 c_near.add(fam < 2 ? 1 : 0);
                                 c_ee.add(fam == 2 ? 1 : 0);
                                 const T r2 = dot(rho, rho);
                                 const bool redo = fp32_unresolved<T, DIM>(fam, r2, grc2, grc, sin2, Pt, rho, tg);
                                 if (redo) {
                                     c_ref.add(1);
-                                    c_in.add(refine_pair<T, DIM>(rl.box, rl.eps, rl.par_s2, rec64[qg.ent.x], rec64[qg.ent.y],
+                                    c_in.add(refine_pair<T, DIM>(rl.box, rl.eps, rl.par_s2, rec64[Gg.ent.x], rec64[Gg.ent.y],
                                                                 Sgi, Sgj, gtab64[rl.sbase + gi], gtab64[rl.sbase + gj], fam,
-                                                                e, gf, sigd, A));
+                                                                e, gf, rl.rad[gi] + rl.rad[gj], A));
                                 } else {
                                     c_in.add(add_wca(A, Pt, rho, tg, gsig2, grc2, eps));
                                 }
                             }
-                            res[lane] = A;
-                            wave_sync_lds();
-                            // this lane's partial sum: problems sub, sub + 16, ...
-                            // of its pair that fall in this step
-                            const int lo = offs[grp] > c0 ? offs[grp] : c0;
-                            const int hi = offs[grp + 1] < c0 + 64 ? offs[grp + 1] : c0 + 64;
-                            int k = lo - offs[grp];
-                            k += (sub - k % kVirt + kVirt) % kVirt;
-                            for (; offs[grp] + k < hi; k += kVirt) {
-                                const Acc<T> &B = res[offs[grp] + k - c0];
-                                A0.F = A0.F + B.F;
-                                A0.Ti = A0.Ti + B.Ti;
-                                A0.Tj = A0.Tj + B.Tj;
-                                A0.U += B.U;
+                            // this lane's partial sums: problems k of its pair
+                            // with k mod 16 = sub (8 lanes: and sub + 8) that
+                            // fall in this step, kRes of the step at a time
+#pragma unroll
+                            for (int p0 = 0; p0 < 64; p0 += kRes) {
+                                if (kRes == 64 || (lane & ~(kRes - 1)) == p0) res[lane & (kRes - 1)] = A;
+                                wave_sync_lds();
+                                const int b0 = c0 + p0, hi = o_hi < b0 + kRes ? o_hi : b0 + kRes;
+                                int k = (o_lo > b0 ? o_lo : b0) - o_lo;
+                                k += (sub - k % kGL + kGL) % kGL;
+                                for (; o_lo + k < hi; k += kGL) {
+                                    const Acc<T> &B = res[o_lo + k - b0];
+                                    Acc<T> &S = (kSets == 1 || k % kVirt < kGL) ? A0 : A1;
+                                    S.F = S.F + B.F;
+                                    S.Ti = S.Ti + B.Ti;
+                                    S.Tj = S.Tj + B.Tj;
+                                    S.U += B.U;
+                                }
+                                wave_sync_lds();
                             }
-                            wave_sync_lds();
                         }
                     } else
                     for (int m = 0;; ++m) {
@@ -1192,7 +1359,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                             const bool redo = fp32_unresolved<T, DIM>(fam, r2, rc2, rc, sin2, Pt, rho, t);
                             if (redo) {
                                 c_ref.add(1);
-                                c_in.add(refine_pair<T, DIM>(rl.box, rl.eps, rl.par_s2, rec64[qe.ent.x], rec64[qe.ent.y], Si, Sj,
+                                c_in.add(refine_pair<T, DIM>(rl.box, rl.eps, rl.par_s2, rec64[G.ent.x], rec64[G.ent.y], Si, Sj,
                                                             gtab64[rl.sbase + si], gtab64[rl.sbase + sj], fam, e, g, rl.rad[si] + rl.rad[sj], A));
                             } else {
                                 c_in.add(add_wca(A, Pt, rho, t, sig2, rc2, eps));
@@ -1219,11 +1386,11 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     J2 = group_sum<kGL>(A0.Tj.z, A1.Tj.z);
             const T U = group_sum<kGL>(A0.U, A1.U);
             if (live && sub < 2) {  // lane 0 writes i's slot, lane 1 j's
-                const int4 ent = qe.ent;
+                const int4 ent = G.ent;
                 const int i = ent.x, j = ent.y;
                 M3<T> Ri;
-                for (int k = 0; k < 9; ++k) Ri.m[k] = qe.Ri[k];
-                const V3<T> dv = v3<T>(qe.d[0], qe.d[1], qe.d[2]);
+                for (int k = 0; k < 9; ++k) Ri.m[k] = G.Ri[k];
+                const V3<T> dv = v3<T>(G.d[0], G.d[1], G.d[2]);
                 const V3<T> Fs = mul(Ri, v3<T>(F0, F1, F2));
                 const bool js = sub == 1;
                 const V3<T> Ts = mul(Ri, js ? v3<T>(J0, J1, J2) : v3<T>(I0, I1, I2));
@@ -1265,35 +1432,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             const int left = __builtin_amdgcn_readfirstlane(rl.ncmp) - base;
             const int n = left < 0 ? 0 : (left > kGroups ? kGroups : left);
             head = tail = 0;  // the queue is empty between units
-            if (lane < n) {
-                const int4 ent = l.cpairs[rl.poff + base + lane];
-                const PartRec<T> ri = prec[ent.x];
-                const PartRec<T> rj = prec[ent.y];
-                M3<T> Ri, Rj;
-                for (int k = 0; k < 9; ++k) {
-                    Ri.m[k] = ri.R[k];
-                    Rj.m[k] = rj.R[k];
-                }
-                const double dx = min_image_near(rj.x - ri.x, rl.box[0]);
-                const double dy = min_image_near(rj.y - ri.y, rl.box[1]);
-                const double dz = (DIM == 3) ? min_image_near(rj.z - ri.z, rl.box[2]) : 0.0;
-                const M3<T> Rr = rel_rotation(Ri, Rj);
-                const V3<T> t = mulT(Ri, v3<T>((T)dx, (T)dy, (T)dz));
-                QEnt<T> &e = qb[lane];
-                e.ent = ent;
-                e.si = ri.sid;
-                e.sj = rj.sid;
-                for (int k = 0; k < 9; ++k) {
-                    e.Rr[k] = Rr.m[k];
-                    e.Ri[k] = Ri.m[k];
-                }
-                e.t[0] = t.x;
-                e.t[1] = t.y;
-                e.t[2] = t.z;
-                e.d[0] = (T)dx;
-                e.d[1] = (T)dy;
-                e.d[2] = (T)dz;
-            }
+            if (lane < n) qb[lane] = l.cpairs[rl.poff + base + lane];
             tail = n;
             wave_sync_lds();
             ++tt;
@@ -1445,20 +1584,28 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     if (need && sub1 == 0) l.cpairs[rl.poff + at + popc_below(m)] = ent;
                 }
             } else if (need && sub1 == 0) {
-                QEnt<T> &e = qb[(tail + popc_below(m)) % kQCap];
-                e.ent = ent;
-                e.si = si;
-                e.sj = sj;
-                for (int k = 0; k < 9; ++k) {
-                    e.Rr[k] = Rr.m[k];
-                    e.Ri[k] = Ri.m[k];
+                const int at = (tail + popc_below(m)) % kQCap;
+                if constexpr (kPark) {
+                    PairGeo<T> &e = wgeo[at];
+                    const double sigd = rl.rad[si] + rl.rad[sj];
+                    e.ent = ent;
+                    e.si = si;
+                    e.sj = sj;
+                    e.rc = rc;
+                    e.sig2 = (T)(sigd * sigd);
+                    for (int k = 0; k < 9; ++k) {
+                        e.Rr[k] = Rr.m[k];
+                        e.Ri[k] = Ri.m[k];
+                    }
+                    e.t[0] = t.x;
+                    e.t[1] = t.y;
+                    e.t[2] = t.z;
+                    e.d[0] = (T)dx;
+                    e.d[1] = (T)dy;
+                    e.d[2] = (T)dz;
+                } else {
+                    qb[at] = ent;
                 }
-                e.t[0] = t.x;
-                e.t[1] = t.y;
-                e.t[2] = t.z;
-                e.d[0] = (T)dx;
-                e.d[1] = (T)dy;
-                e.d[2] = (T)dz;
             }
             tail += __popcll(m);
         }
@@ -1949,7 +2096,7 @@ void pairs_shape(const Launch &L, unsigned long long *stats, hipStream_t stream)
 template <typename T, int DIM, int GL, int OCC, int SL, int STAGE, bool FC>
 void pairs_t(const Launch &L, unsigned long long *stats, hipStream_t stream)
 {
-    const size_t sh = pair_kernel_lds(sizeof(T) == 4 ? DEM_FP32 : DEM_FP64, L.b.tab_slots, GL, SL, STAGE, FC ? 1 : 0);
+    const size_t sh = pair_kernel_lds(sizeof(T) == 4 ? DEM_FP32 : DEM_FP64, DIM, L.b.tab_slots, GL, SL, STAGE, FC ? 1 : 0);
     const int grid = STAGE == kSearchOnly ? L.b.search_blocks : L.b.pair_blocks;
     const auto rot = reinterpret_cast<const PartRec<T> *>(L.f.rot);
     const auto rec = reinterpret_cast<SlotRec<T> *>(L.f.rec);
@@ -2017,17 +2164,24 @@ void launch_gather(const Launch &L, bool kick, hipStream_t stream)
     }
 }
 
-size_t pair_kernel_lds(int precision, int tab_slots, int lanes, int sep, int stage, int fc)
+size_t pair_kernel_lds(int precision, int dim, int tab_slots, int lanes, int sep, int stage, int fc)
 {
-    const size_t w = precision == DEM_FP32 ? sizeof(ShapeTab<float>) : sizeof(ShapeTab<double>);
-    const size_t pl = precision == DEM_FP32 ? sizeof(PairLds<float>) : sizeof(PairLds<double>);
-    const size_t qe = precision == DEM_FP32 ? sizeof(QEnt<float>) : sizeof(QEnt<double>);
-    const size_t acc = precision == DEM_FP32 ? sizeof(Acc<float>) : sizeof(Acc<double>);
+    const bool f32 = precision == DEM_FP32;
+    const int groups = 64 / lanes;
+    const size_t w = f32 ? sizeof(ShapeTab<float>) : sizeof(ShapeTab<double>);
+    const size_t pl = f32 ? sizeof(PairLds<float>) : sizeof(PairLds<double>);
+    const size_t pg = f32 ? sizeof(PairGeo<float>) : sizeof(PairGeo<double>);
+    const int slots = queue_slots(sep, lanes);
+    const bool park = f32 ? parked<float>(dim, lanes, stage) : parked<double>(dim, lanes, stage);
+    const size_t queue = park ? slots * pg : groups * pg + slots * sizeof(int4);
+    const size_t ctl = lanes == 8 ? sizeof(WaveCtl<8>) : sizeof(WaveCtl<4>);
+    const size_t acc = !pooled(dim, lanes) ? 0 : f32 ? pool_results<float>(lanes) * sizeof(Acc<float>)
+                                                      : pool_results<double>(lanes) * sizeof(Acc<double>);
     const size_t en = kWaves * (64 / sep) * sizeof(int4);  // entry slots
     if (stage == kSearchOnly)  // tables, replica, and the last workgroup's scan
         return en + (size_t)tab_slots * w + sizeof(RepLds) + sizeof(int) * 64 * kWaves;
-    return en + (size_t)tab_slots * w + sizeof(RepLds) + kWaves * (64 / lanes) * pl + kWaves * queue_slots(sep, lanes) * qe +
-           (lanes == 16 ? kWaves * 64 * acc : 0) + (fc ? kWaves * (64 / lanes) * sizeof(PairFc) : 0);
+    return en + (size_t)tab_slots * w + sizeof(RepLds) +
+           kWaves * (groups * pl + ctl + queue + acc + (fc ? groups * sizeof(PairFc) : 0));
 }
 
 namespace {
@@ -2060,7 +2214,7 @@ hipError_t pair_occupancy_stage(int *per_cu, size_t lds, int lanes, int sep, int
 
 int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int sep, int stage, int fc)
 {
-    const size_t lds = pair_kernel_lds(precision, tab_slots, lanes, sep, stage, fc);
+    const size_t lds = pair_kernel_lds(precision, dim, tab_slots, lanes, sep, stage, fc);
     int per_cu = 0, cus = 0, dev = 0;
     hipError_t e;
     if (precision == DEM_FP32)
@@ -2072,6 +2226,11 @@ int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int s
     if (e != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 512;
+    // LDS is handed out in granules of 1280 bytes (measured: three workgroups
+    // of 53,589 bytes share a CU, three of 54,101 do not), which the runtime's
+    // count leaves out; a grid of more blocks than fit would run in two rounds
+    const size_t granule = 1280, held = (size_t)163840 / ((lds + granule - 1) / granule * granule);
+    per_cu = std::min(per_cu, (int)held);
     return std::max(8, per_cu * cus);
 }
 

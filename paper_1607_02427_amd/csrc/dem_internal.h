@@ -214,14 +214,14 @@ struct alignas(16) ShapeTab {
     Vec4<T> em[DEM_MAX_EDGES];   // midpoint, half length
     Vec4<T> fn[DEM_MAX_FACES];   // normal, offset
     Vec4<T> fc[DEM_MAX_FACES];   // centroid, bounding radius
-    Vec4<T> fe1[DEM_MAX_FACES];  // face axis 1, 0
     Vec4<T> lv[DEM_MAX_LOOP];    // loop vertex k, 1 / |loop edge k -> k+1|^2
     Vec4<T> ln[DEM_MAX_LOOP];    // inward in-plane normal, offset
     Vec4<T> sp[kMaxSep];         // supporting plane: normal, offset
     T lxy[DEM_MAX_LOOP][2];
     int e[DEM_MAX_EDGES][2];     // end points by index (into the pair's transformed vertices)
-    int floop[DEM_MAX_LOOP];     // loop vertices by index
     int fi[DEM_MAX_FACES];       // first loop entry | one past the last << 8 | convex << 16
+    T fe1[DEM_MAX_FACES][3];     // face axis 1 (concave faces)
+    unsigned char floop[DEM_MAX_LOOP];  // loop vertices by index
 };
 __host__ __device__ inline int face_first(int fi) { return fi & 255; }
 __host__ __device__ inline int face_end(int fi) { return (fi >> 8) & 255; }
@@ -575,7 +575,7 @@ __device__ inline void cell_insert(const SysParams &p, const ListPtrs &l, int i,
 
 // Dynamic LDS of the pair kernel, and how many of its blocks the device
 // holds at once.
-size_t pair_kernel_lds(int precision, int tab_slots, int lanes, int sep, int stage, int fc);
+size_t pair_kernel_lds(int precision, int dim, int tab_slots, int lanes, int sep, int stage, int fc);
 int pair_blocks_resident(int precision, int dim, int tab_slots, int lanes, int sep, int stage, int fc);
 
 // Per-particle records (position, rotation, shape id) from the state arrays.

@@ -589,10 +589,10 @@ void pack_table(const HostShape &D, ShapeTab<T> &F)
         F.fi[f] = D.foff[f] | D.foff[f + 1] << 8 | D.fconvex[f] << 16;
         F.fn[f] = vec(D.fn[f], D.fo[f]);
         F.fc[f] = vec(D.fc[f], D.frad[f] * (f32 ? 1.0 + 1e-6 : 1.0));
-        F.fe1[f] = vec(D.fe1[f], 0.0);
+        for (int a = 0; a < 3; ++a) F.fe1[f][a] = (T)D.fe1[f][a];
     }
     for (int k = 0; D.nf > 0 && k < D.foff[D.nf]; ++k) {
-        F.floop[k] = D.floop[k];
+        F.floop[k] = (unsigned char)D.floop[k];
         F.lv[k] = vec(D.v[D.floop[k]], D.linv[k]);
         F.ln[k] = vec(D.lnrm[k], D.loff[k]);
         F.lxy[k][0] = (T)D.lxy[k][0];
