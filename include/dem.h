@@ -278,9 +278,10 @@ dem_status dem_time_forces(dem_handle h, int32_t reps, double *mean_ms);
  * kernel runs the separation stage alone at 4 wavefronts per SIMD and
  * compacts the pairs no supporting plane separates, per replica, into a
  * buffer as large as the pair entries; a force kernel then gives each
- * wavefront one feature round of those pairs (lanes_per_pair and
- * applies to it; grid_factor does not).  The default is
- * {16, 1, 2, 4, 0}.  The next dem_step captures its graph again.
+ * wavefront one feature round of those pairs (lanes_per_pair applies to it;
+ * grid_factor does not).  Until it is called (or dem_tune_pairs), the library
+ * picks a shape by the number of pair slots and by the bodies' features.
+ * The next dem_step captures its graph again.
  * DEM_E_ARG for other values. */
 enum { DEM_PAIR_SHAPES = 16 };
 dem_status dem_set_pair_shape(dem_handle h, int32_t lanes_per_pair, int32_t grid_factor, int32_t waves_per_simd,

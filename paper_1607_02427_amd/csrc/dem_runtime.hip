@@ -73,6 +73,7 @@ struct Replica {
     int chunk0 = 0, nchunks = 0;
     int cell0 = 0, ncells = 0;
     int shape0 = 0, nshapes = 0;
+    int edges = 0;               // of the shape that has the most
 };
 
 }  // namespace
@@ -88,6 +89,7 @@ struct dem_system {
     int pair_waves = kDefaultPairWaves;  // wavefronts per SIMD
     int pair_sep = kDefaultPairSep;      // and lanes per pair of its separation stage;
     int pair_split = 0;                  // 1: search and force kernels instead of one
+    bool pair_auto = true;               // the shape follows the rule of pick_shape until one is set or tuned
     int feature_cells = 0;               // 1: the feature search reads the shape-local cells
     BatchParams bp{};
     std::vector<Replica> reps;
@@ -652,9 +654,45 @@ Launch make_launch(const dem_system *h)
 
 int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 
+// The pair-kernel shape of a handle that nobody has set or tuned one for,
+// from the pair slots of its live replicas and their shapes.
+//  * Few slots: 16 lanes in both stages, a tile of 16 pairs, so that a
+//    wavefront holds few of the long feature chains that set a small
+//    system's time (216 cubes 14.6 us against 17.4 with 8 lanes and 20.7
+//    with 16 lanes and tiles of 64; 2000 cubes, 36,864 slots, 16.4 against
+//    17.0; 4096 cubes, 73,728 slots, 23.9 against 17.8).  In FP64 the lines
+//    cross earlier (2000 cubes 18.1 against 17.5).
+//  * Otherwise 8 lanes, whose rounds share their culls and solves over twice
+//    as many pairs (4096 cubes 17.8 us against 21.7 with 16 lanes, 64,000
+//    cubes 76 against 95, 20,000 pentagons 16.1 against 24.5),
+//  * but 16 for bodies whose features take 8 lanes many passes: more than 24
+//    edges (9001 icosahedra 26.3 against 27.9), and in FP64 more than 8
+//    vertices (5003 L-prisms on a contact lattice 69 against 96; as a fluid
+//    of 4096 they would gain from 8 lanes, 22.5 against 26.9).
+void pick_shape(dem_system *h)
+{
+    if (!h->pair_auto) return;
+    long long slots = 0;
+    bool wide = false, edged = false;
+    for (const Replica &R : h->reps) {
+        if (!R.live) continue;
+        slots += R.sp.pcap;
+        wide |= R.sp.wide != 0.0;
+        edged |= R.edges > 24;
+    }
+    const bool f32 = h->precision == DEM_FP32;
+    const bool few = slots <= (f32 ? 40960 : 32768);
+    h->pair_grid = 1;
+    h->pair_waves = kDefaultPairWaves;
+    h->pair_split = 0;
+    h->pair_sep = few ? 16 : 4;
+    h->pair_lanes = few || edged || (wide && !f32) ? 16 : 8;
+}
+
 // Batch-wide launch parameters from the replica table.
 void refresh_batch(dem_system *h)
 {
+    pick_shape(h);
     BatchParams &b = h->bp;
     b.nrep = 0;
     b.tab_slots = 1;
@@ -756,8 +794,13 @@ dem_status upload_tables(dem_system *h)
                                  hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     for (Replica &R : h->reps) R.on_device = R.live;
+    const int tile = h->bp.tile;
     refresh_batch(h);
     drop_graph(h);
+    if (h->bp.tile != tile && tile != 0) {  // the shape has followed the replicas: tiles of the new size
+        launch_lists(make_launch(h), LISTS_PLAN, h->stream);
+        HIPCHK(h, hipGetLastError());
+    }
     return DEM_OK;
 }
 
@@ -1032,6 +1075,7 @@ dem_status describe_replica(dem_system *h, const dem_params &p, Replica &R, std:
         for (int a = 0; a < 3; ++a) sp.inertia[s][a] = (p.dim == 2 && a < 2) ? 0.0 : p.shapes[s].inertia[a];
         sp.R[s] = tabs[s].R;
         if (tabs[s].nv > 8) sp.wide = 1.0;
+        R.edges = std::max(R.edges, tabs[s].ne);
         sp.rad[s] = p.shapes[s].rounding_radius;
         Rmax = std::max(Rmax, tabs[s].R);
         rmax = std::max(rmax, p.shapes[s].rounding_radius);
@@ -1925,9 +1969,10 @@ dem_status dem_set_pair_shape(dem_handle h, int32_t lanes_per_pair, int32_t grid
                     "pair shape: %d lanes per pair (8 or 16), grid factor %d (1 to 4), %d waves per SIMD (2 or 3), "
                     "%d separation lanes (4, or 16 with 16 lanes per pair), split %d (0, or 1 with 4 separation lanes)",
                     lanes_per_pair, grid_factor, waves_per_simd, sep_lanes, split);
-    if (lanes_per_pair == h->pair_lanes && grid_factor == h->pair_grid && waves_per_simd == h->pair_waves &&
+    if (!h->pair_auto && lanes_per_pair == h->pair_lanes && grid_factor == h->pair_grid && waves_per_simd == h->pair_waves &&
         sep_lanes == h->pair_sep && split == h->pair_split)
         return DEM_OK;
+    h->pair_auto = false;
     h->pair_lanes = lanes_per_pair;
     h->pair_grid = grid_factor;
     h->pair_waves = waves_per_simd;
