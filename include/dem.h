@@ -272,7 +272,10 @@ dem_status dem_time_forces(dem_handle h, int32_t reps, double *mean_ms);
  * in FP32, 2 in FP64); and sep_lanes (4, or 16 with
  * 16 lanes per pair) lanes take one pair in the separation stage, so a
  * wavefront settles 16 or 4 pairs at a time and a tile holds 64 or 16
- * pairs (16 spreads a small system over four times the wavefronts).
+ * pairs (16 spreads a small system over four times the wavefronts; with 4,
+ * and 8 lanes_per_pair, 3D systems of several million pair slots, or of half
+ * a million if every body is a single vertex, take one lane per pair, 64
+ * pairs per wavefront, on their own).
  * split (0 or 1, the latter with sep_lanes 4) separates the contact search
  * from the force evaluation, the two-step form Sec. V proposes: a search
  * kernel runs the separation stage alone at 4 wavefronts per SIMD and

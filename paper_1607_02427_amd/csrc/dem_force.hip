@@ -686,6 +686,24 @@ __device__ inline RepHead rep_head(const SysParams *reps, const ListPtrs &l, int
             reps[r].n_shapes};
 }
 
+// A pair entry in LDS: 16 bytes as it is in the pair list, or, with a lane per
+// pair in the separation stage (64 to a tile, 72 in a wavefront's queue), 8:
+// 24 bits for each particle slot and 8 for each row slot (255: none).
+template <int SL>
+using QueueEnt = std::conditional_t<SL == 1, unsigned long long, int4>;
+__device__ inline void put_ent(int4 &q, int4 e) { q = e; }
+__device__ inline int4 get_ent(int4 q) { return q; }
+__device__ inline void put_ent(unsigned long long &q, int4 e)
+{
+    q = (unsigned)(e.x & 0xffffff) | (unsigned)(e.z & 0xff) << 24 |
+        (unsigned long long)((unsigned)(e.y & 0xffffff) | (unsigned)(e.w & 0xff) << 24) << 32;
+}
+__device__ inline int4 get_ent(unsigned long long q)
+{
+    const unsigned a = (unsigned)q, b = (unsigned)(q >> 32);
+    const int z = (int)(a >> 24), w = (int)(b >> 24);
+    return make_int4((int)(a & 0xffffffu), (int)(b & 0xffffffu), z == 255 ? -1 : z, w == 255 ? -1 : w);
+}
 // Stages replica r: its shape tables and parameters, and the pair entries of
 // `tile`, the first tile the block takes of it, into each wavefront's entry
 // slots (nxt, kPP of them).  Every thread of the block calls it together.
@@ -693,9 +711,9 @@ __device__ inline RepHead rep_head(const SysParams *reps, const ListPtrs &l, int
 // before its first particle records.  UNITS: the block walks force units of
 // the replica's compacted pairs (split form) instead of its pair tiles, and
 // reads its entries itself.
-template <typename T, bool UNITS, int kPP>
+template <typename T, bool UNITS, int kPP, typename QE>
 __device__ void stage_replica(const SysParams *reps, const ListPtrs &l, const ShapeTab<T> *gtab, ShapeTab<T> *tab,
-                              RepLds &rl, int r, const RepHead &hd, int tile, int4 *nxt)
+                              RepLds &rl, int r, const RepHead &hd, int tile, QE *nxt)
 {
     __syncthreads();
     int tid = threadIdx.x;  // (formed here, not held across the caller's loop)
@@ -729,7 +747,7 @@ __device__ void stage_replica(const SysParams *reps, const ListPtrs &l, const Sh
             if (w < n16) dst[w] = v[u];
         }
     }
-    if (fetch) nxt[tid & 63] = ent;
+    if (fetch) put_ent(nxt[tid & 63], ent);
     if (cst) reinterpret_cast<uint4 *>(rl.box)[tid - (64 * kWaves - kC)] = c;
     if (threadIdx.x == 0) {  // (one thread: the LDS addresses stay scalar)
         rl.r = r;
@@ -780,9 +798,9 @@ constexpr int queue_slots(int sep, int lanes) { return 64 / sep + 64 / lanes; }
 // solve (8 lanes in 3D) or for a second workgroup per CU (FP64).  The force
 // kernel of the split form reads entries.
 template <typename T>
-__host__ __device__ constexpr bool parked(int dim, int lanes, int stage)
+__host__ __device__ constexpr bool parked(int dim, int lanes, int sep, int stage)
 {
-    return sizeof(T) == 4 && stage == kFused && (lanes == 16 || dim == 2);
+    return sizeof(T) == 4 && stage == kFused && sep != 1 && (lanes == 16 || dim == 2);
 }
 // Per wavefront: problems of each group's pair, and those its queue holds.
 template <int kGroups>
@@ -792,12 +810,13 @@ struct alignas(16) WaveCtl {
 // Whether the wavefront's 64 lanes share the solves of all its pairs (their
 // results pass through LDS), and how many results LDS holds at a time: half
 // a wavefront's with 8 lanes in FP64, so that two workgroups still share a
-// CU.  Not with 8 lanes in 2D, where pairs have few problems.
+// CU, and with a lane per pair in the separation stage, so that three do
+// (FP32).  Not with 8 lanes in 2D, where pairs have few problems.
 __host__ __device__ constexpr bool pooled(int dim, int lanes) { return lanes == 16 || dim == 3; }
 template <typename T>
-__host__ __device__ constexpr int pool_results(int lanes)
+__host__ __device__ constexpr int pool_results(int lanes, int sep)
 {
-    return lanes == 8 && sizeof(T) == 8 ? 32 : 64;
+    return lanes == 8 && (sizeof(T) == 8 || sep == 1) ? 32 : 64;
 }
 
 // One block of 4 waves takes a contiguous range of tiles (64 or 16 pairs
@@ -847,7 +866,8 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
 {
     static_assert(GL == 8 || GL == 16, "8 or 16 lanes per pair");
     static_assert(OCC >= 2 && OCC <= 4, "2 to 4 wavefronts per SIMD");
-    static_assert(SL == 4 || SL == 16, "4 or 16 lanes per pair in the separation stage");
+    static_assert(SL == 1 || SL == 4 || SL == 16, "1, 4 or 16 lanes per pair in the separation stage");
+    static_assert(SL != 1 || (GL == 8 && STAGE == kFused), "a lane per pair: with 8 lanes in the feature stage");
     static_assert(STAGE >= kFused && STAGE <= kForces, "fused, search or forces");
     constexpr bool kSearch = STAGE == kSearchOnly;  // first stage only: compact the pairs it keeps
     constexpr bool kForce = STAGE == kForces;       // second stage only, on the compacted pairs
@@ -865,14 +885,14 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     RepLds &rl = *reinterpret_cast<RepLds *>(smem + orl);
     PairLds<T> *pls = reinterpret_cast<PairLds<T> *>(smem + orl + sizeof(RepLds));
     PairGeo<T> *geo = reinterpret_cast<PairGeo<T> *>(pls + kWaves * kGroups);
-    constexpr bool kPark = parked<T>(DIM, GL, STAGE);
+    constexpr bool kPark = parked<T>(DIM, GL, SL, STAGE);
     constexpr int kGeo = kPark ? kQCap : kGroups;  // pairs with transforms per wavefront
     constexpr int kEnt = kPark ? 0 : kQCap;        // entries without
     WaveCtl<kGroups> *ctl = reinterpret_cast<WaveCtl<kGroups> *>(geo + kWaves * kGeo);
-    int4 *qall = reinterpret_cast<int4 *>(ctl + kWaves);
+    QueueEnt<SL> *qall = reinterpret_cast<QueueEnt<SL> *>(ctl + kWaves);
     // results of one pooled solve step, one per lane
     constexpr bool kPool = pooled(DIM, GL);
-    constexpr int kRes = pool_results<T>(GL);
+    constexpr int kRes = pool_results<T>(GL, SL);
     Acc<T> *pres = reinterpret_cast<Acc<T> *>(qall + kWaves * kEnt);
     // the feature-cell form's per-group prefix and edge masks
     PairFc *pfc = reinterpret_cast<PairFc *>(reinterpret_cast<unsigned char *>(pres) +
@@ -882,14 +902,14 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the pair entries of this wavefront's next separation tile
     // (the search kernel has no feature stage: its slots follow the scan's words)
-    int4 *nxt = (kSearch ? reinterpret_cast<int4 *>(reinterpret_cast<int *>(pls) + 64 * kWaves)
-                         : reinterpret_cast<int4 *>(reinterpret_cast<unsigned char *>(pfc) +
-                                                    (FC ? kWaves * kGroups * sizeof(PairFc) : 0))) +
-                wid * kPairsPerWave;
+    QueueEnt<SL> *nxt = (kSearch ? reinterpret_cast<QueueEnt<SL> *>(reinterpret_cast<int *>(pls) + 64 * kWaves)
+                                 : reinterpret_cast<QueueEnt<SL> *>(reinterpret_cast<unsigned char *>(pfc) +
+                                                                    (FC ? kWaves * kGroups * sizeof(PairFc) : 0))) +
+                        wid * kPairsPerWave;
     const int grp = lane / kGL, sub = lane % kGL;
     const unsigned long long gmask = ((kGL == 64) ? ~0ull : ((1ull << kGL) - 1)) << (kGL * grp);
     PairLds<T> &W = pls[wid * kGroups + grp];
-    int4 *qb = qall + wid * kEnt;
+    QueueEnt<SL> *qb = qall + wid * kEnt;
     WaveCtl<kGroups> &wc = ctl[wid];
     PairGeo<T> *wgeo = geo + wid * kGeo;
     const size_t N = (size_t)b.N;
@@ -967,7 +987,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 }
             } else {
                 // (groups without a pair repeat the last one's loads and drop it)
-                ent = qb[(h0 + (live ? grp : take - 1)) % kQCap];
+                ent = get_ent(qb[(h0 + (live ? grp : take - 1)) % kQCap]);
                 const PartRec<T> ri = prec[ent.x];
                 const PartRec<T> rj = prec[ent.y];
                 M3<T> Ri, Rj;
@@ -1432,7 +1452,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             const int left = __builtin_amdgcn_readfirstlane(rl.ncmp) - base;
             const int n = left < 0 ? 0 : (left > kGroups ? kGroups : left);
             head = tail = 0;  // the queue is empty between units
-            if (lane < n) qb[lane] = l.cpairs[rl.poff + base + lane];
+            if (lane < n) put_ent(qb[lane], l.cpairs[rl.poff + base + lane]);
             tail = n;
             wave_sync_lds();
             ++tt;
@@ -1450,7 +1470,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
         // round trip, the particle records (position, rotation and shape in
         // one line each), not two; lanes past the replica's last pair work
         // on that pair and drop it.
-        const int4 ent = nxt[grp1];
+        const int4 ent = get_ent(nxt[grp1]);
         const int i = ent.x, j = ent.y;
         const PartRec<T> ri = prec[i];
         const PartRec<T> rj = prec[j];
@@ -1481,27 +1501,29 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             const double sig = rl.rad[si] + rl.rad[sj], rc = kWcaCut * sig;
             const double r2 = dx * dx + dy * dy + dz * dz;
             c_in.add(sub1 == 0 && r2 < rc * rc ? 1 : 0);
-            if (sub1 < 2 && r2 < rc * rc) {  // lane 0 writes i's slot, lane 1 j's
+            if (sub1 < 2 && r2 < rc * rc) {  // lane 0 writes i's slot, lane 1 j's (a lane per pair: both)
                 const double ir2 = 1.0 / r2, s2 = sig * sig * ir2, s6 = s2 * s2 * s2, h = 2.0 * s6 - 1.0;
                 const double fr = 24.0 * rl.eps * s6 * h * ir2;  // force on i along x_i - x_j
-                const bool js = sub1 == 1;
-                const double sg = js ? 1.0 : -1.0;
-                SlotRec<T> w;
-                w.F[0] = (T)(sg * fr * dx);
-                w.F[1] = (T)(sg * fr * dy);
-                w.F[2] = (T)(sg * fr * dz);
-                w.U = (T)(rl.eps * h * h);
-                w.tq[0] = w.tq[1] = w.tq[2] = T(0);
-                w.d[0] = (T)(-sg * dx);
-                w.d[1] = (T)(-sg * dy);
-                w.d[2] = (T)(-sg * dz);
-                w.pad1 = T(0);
-                set_stamp(w, stamp);
-                const int slot = js ? ent.w : ent.z;
-                const int pi = js ? ent.y : ent.x;
-                if (slot >= 0) {
-                    rec[(size_t)slot * N + pi] = w;
-                    atomicOr(&l.smask[(size_t)(slot >> 5) * N + pi], 1u << (slot & 31));
+                for (int side = 0; side < (SL == 1 ? 2 : 1); ++side) {
+                    const bool js = SL == 1 ? side == 1 : sub1 == 1;
+                    const double sg = js ? 1.0 : -1.0;
+                    SlotRec<T> w;
+                    w.F[0] = (T)(sg * fr * dx);
+                    w.F[1] = (T)(sg * fr * dy);
+                    w.F[2] = (T)(sg * fr * dz);
+                    w.U = (T)(rl.eps * h * h);
+                    w.tq[0] = w.tq[1] = w.tq[2] = T(0);
+                    w.d[0] = (T)(-sg * dx);
+                    w.d[1] = (T)(-sg * dy);
+                    w.d[2] = (T)(-sg * dz);
+                    w.pad1 = T(0);
+                    set_stamp(w, stamp);
+                    const int slot = js ? ent.w : ent.z;
+                    const int pi = js ? ent.y : ent.x;
+                    if (slot >= 0) {
+                        rec[(size_t)slot * N + pi] = w;
+                        atomicOr(&l.smask[(size_t)(slot >> 5) * N + pi], 1u << (slot & 31));
+                    }
                 }
             }
             live = false;
@@ -1517,57 +1539,91 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             // separation beyond which no feature pair can be inside the
             // cutoff, with room for the rounding of the transformed vertices
             const T thr = rc * T(1.0001) + T(1e-5) * (Bi + Bj);
-            // bit p of bi (bj): every vertex of j (i) this lane holds lies
-            // more than thr beyond supporting plane p of i (j); no early exit
-            // and one group reduction at the end, so the plane loads of
-            // successive planes overlap.  VP vertices of each body per lane,
-            // as few as the replica's shapes need: with VP for
-            // DEM_MAX_VERTS throughout, half of the plane tests of bodies
-            // with 8 vertices or fewer were made on empty slots.
-            unsigned bi = 0, bj = 0;
-            auto planes = [&](auto vp) {
-                constexpr int VP = decltype(vp)::value;
-                V3<T> wj[VP], wi[VP];  // this lane's vertices: j's in i's frame, i's in j's frame
-                bool hj[VP], hi[VP];
-#pragma unroll
-                for (int p = 0; p < VP; ++p) {
-                    const int k = p * kSepLanes + sub1;
-                    hj[p] = live && k < Sj.nv;
-                    hi[p] = live && k < Si.nv;
-                    wj[p] = t + mul(Rr, xyz(Sj.v[k]));
-                    wi[p] = mulT(Rr, xyz(Si.v[k]) - t);
-                }
-                const int nsi = live ? Si.nsep : 0, nsj = live ? Sj.nsep : 0;
-#pragma unroll 2
-                for (int p = 0; p < nsi; ++p) {
-                    const Vec4<T> pl = Si.sp[p];
-                    bool all = true;
-#pragma unroll
-                    for (int v = 0; v < VP; ++v) {
-                        all &= !hj[v] || plane_gap(pl, wj[v]) > thr;
-                        c_pv.add(hj[v] ? 1 : 0);
+            bool sep;
+            if constexpr (kSepLanes == 1) {
+                // A lane takes the whole pair: each supporting plane's normal
+                // is carried into the other body's frame and the body's
+                // lowest vertex along it found, and only for the planes that
+                // can separate at all: the other body's centre must lie thr
+                // plus its inner radius beyond (one to three planes of an
+                // octahedron's eight).  Four lanes per pair repeat the
+                // transform and test every plane: 262,144 octahedra, 430
+                // instructions for 16 pairs against about 600 for 64.
+                sep = false;
+                auto side = [&](const ShapeTab<T> &A, const ShapeTab<T> &B, bool of_i, V3<T> c) {
+                    const T lim = thr + B.rin;
+                    unsigned cand = 0u;
+                    const int ns = live && !sep ? A.nsep : 0;
+#pragma unroll 4
+                    for (int p = 0; p < ns; ++p) cand |= (plane_gap(A.sp[p], c) > lim ? 1u : 0u) << p;
+                    while (__ballot(cand != 0u) != 0ull) {
+                        const int p = cand != 0u ? __builtin_ctz(cand) : 0;
+                        const Vec4<T> pl = A.sp[p];
+                        const V3<T> m = of_i ? mulT(Rr, xyz(pl)) : mul(Rr, xyz(pl));
+                        T lo = T(3.0e38);
+                        const int nv = cand != 0u ? B.nv : 0;
+#pragma unroll 4
+                        for (int v = 0; v < nv; ++v) lo = fmin(lo, dot(m, xyz(B.v[v])));
+                        c_pv.add(nv);
+                        sep |= cand != 0u && plane_gap(pl, c) + lo > thr;
+                        cand = sep ? 0u : cand & (cand - 1u);
                     }
-                    bi |= (all ? 1u : 0u) << p;
-                }
-#pragma unroll 2
-                for (int p = 0; p < nsj; ++p) {
-                    const Vec4<T> pl = Sj.sp[p];
-                    bool all = true;
+                };
+                side(Si, Sj, true, t);
+                side(Sj, Si, false, T(-1) * mulT(Rr, t));
+            } else {
+                // bit p of bi (bj): every vertex of j (i) this lane holds lies
+                // more than thr beyond supporting plane p of i (j); no early exit
+                // and one group reduction at the end, so the plane loads of
+                // successive planes overlap.  VP vertices of each body per lane,
+                // as few as the replica's shapes need: with VP for
+                // DEM_MAX_VERTS throughout, half of the plane tests of bodies
+                // with 8 vertices or fewer were made on empty slots.
+                unsigned bi = 0, bj = 0;
+                auto planes = [&](auto vp) {
+                    constexpr int VP = decltype(vp)::value;
+                    V3<T> wj[VP], wi[VP];  // this lane's vertices: j's in i's frame, i's in j's frame
+                    bool hj[VP], hi[VP];
 #pragma unroll
-                    for (int v = 0; v < VP; ++v) {
-                        all &= !hi[v] || plane_gap(pl, wi[v]) > thr;
-                        c_pv.add(hi[v] ? 1 : 0);
+                    for (int p = 0; p < VP; ++p) {
+                        const int k = p * kSepLanes + sub1;
+                        hj[p] = live && k < Sj.nv;
+                        hi[p] = live && k < Si.nv;
+                        wj[p] = t + mul(Rr, xyz(Sj.v[k]));
+                        wi[p] = mulT(Rr, xyz(Si.v[k]) - t);
                     }
-                    bj |= (all ? 1u : 0u) << p;
+                    const int nsi = live ? Si.nsep : 0, nsj = live ? Sj.nsep : 0;
+#pragma unroll 2
+                    for (int p = 0; p < nsi; ++p) {
+                        const Vec4<T> pl = Si.sp[p];
+                        bool all = true;
+#pragma unroll
+                        for (int v = 0; v < VP; ++v) {
+                            all &= !hj[v] || plane_gap(pl, wj[v]) > thr;
+                            c_pv.add(hj[v] ? 1 : 0);
+                        }
+                        bi |= (all ? 1u : 0u) << p;
+                    }
+#pragma unroll 2
+                    for (int p = 0; p < nsj; ++p) {
+                        const Vec4<T> pl = Sj.sp[p];
+                        bool all = true;
+#pragma unroll
+                        for (int v = 0; v < VP; ++v) {
+                            all &= !hi[v] || plane_gap(pl, wi[v]) > thr;
+                            c_pv.add(hi[v] ? 1 : 0);
+                        }
+                        bj |= (all ? 1u : 0u) << p;
+                    }
+                };
+                if (kSepLanes == 4 && rl.wide == 0.0) planes(std::integral_constant<int, kSepLanes == 4 ? 2 : 1>());
+                else planes(std::integral_constant<int, kVP>());
+                for (int off = 1; off < kSepLanes; off <<= 1) {
+                    bi &= __shfl_xor(bi, off, kSepLanes);
+                    bj &= __shfl_xor(bj, off, kSepLanes);
                 }
-            };
-            if (kSepLanes == 4 && rl.wide == 0.0) planes(std::integral_constant<int, kSepLanes == 4 ? 2 : 1>());
-            else planes(std::integral_constant<int, kVP>());
-            for (int off = 1; off < kSepLanes; off <<= 1) {
-                bi &= __shfl_xor(bi, off, kSepLanes);
-                bj &= __shfl_xor(bj, off, kSepLanes);
+                sep = (bi | bj) != 0;
             }
-            const bool sep = (bi | bj) != 0;
             need = live && !sep;
             if (sub1 == 0 && live) {
                 c_pairs.add(1);
@@ -1604,12 +1660,12 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     e.d[1] = (T)dy;
                     e.d[2] = (T)dz;
                 } else {
-                    qb[at] = ent;
+                    put_ent(qb[at], ent);
                 }
             }
             tail += __popcll(m);
         }
-        if (more && lane1 < kPairsPerWave) nxt[lane1] = ent1;
+        if (more && lane1 < kPairsPerWave) put_ent(nxt[lane1], ent1);
         wave_sync_lds();  // the queue entries are visible to every lane
         ++tt;
     }
@@ -2082,6 +2138,8 @@ void pairs_form(const Launch &L, unsigned long long *stats, hipStream_t stream)
         g8 ? pairs_t<T, DIM, 8, O, 4, kForces, FC>(L, stats, stream) : pairs_t<T, DIM, 16, O, 4, kForces, FC>(L, stats, stream);
     } else if (L.b.pair_sep == 16)
         pairs_t<T, DIM, 16, O, 16, kFused, FC>(L, stats, stream);
+    else if (!FC && DIM == 3 && L.b.pair_sep == 1)
+        pairs_t<T, 3, 8, O, 1, kFused, false>(L, stats, stream);
     else
         g8 ? pairs_t<T, DIM, 8, O, 4, kFused, FC>(L, stats, stream) : pairs_t<T, DIM, 16, O, 4, kFused, FC>(L, stats, stream);
 }
@@ -2171,13 +2229,14 @@ size_t pair_kernel_lds(int precision, int dim, int tab_slots, int lanes, int sep
     const size_t w = f32 ? sizeof(ShapeTab<float>) : sizeof(ShapeTab<double>);
     const size_t pl = f32 ? sizeof(PairLds<float>) : sizeof(PairLds<double>);
     const size_t pg = f32 ? sizeof(PairGeo<float>) : sizeof(PairGeo<double>);
+    const size_t qe = sep == 1 ? sizeof(QueueEnt<1>) : sizeof(QueueEnt<4>);
     const int slots = queue_slots(sep, lanes);
-    const bool park = f32 ? parked<float>(dim, lanes, stage) : parked<double>(dim, lanes, stage);
-    const size_t queue = park ? slots * pg : groups * pg + slots * sizeof(int4);
+    const bool park = f32 ? parked<float>(dim, lanes, sep, stage) : parked<double>(dim, lanes, sep, stage);
+    const size_t queue = park ? slots * pg : groups * pg + slots * qe;
     const size_t ctl = lanes == 8 ? sizeof(WaveCtl<8>) : sizeof(WaveCtl<4>);
-    const size_t acc = !pooled(dim, lanes) ? 0 : f32 ? pool_results<float>(lanes) * sizeof(Acc<float>)
-                                                      : pool_results<double>(lanes) * sizeof(Acc<double>);
-    const size_t en = kWaves * (64 / sep) * sizeof(int4);  // entry slots
+    const size_t acc = !pooled(dim, lanes) ? 0 : f32 ? pool_results<float>(lanes, sep) * sizeof(Acc<float>)
+                                                      : pool_results<double>(lanes, sep) * sizeof(Acc<double>);
+    const size_t en = kWaves * (64 / sep) * qe;  // entry slots
     if (stage == kSearchOnly)  // tables, replica, and the last workgroup's scan
         return en + (size_t)tab_slots * w + sizeof(RepLds) + sizeof(int) * 64 * kWaves;
     return en + (size_t)tab_slots * w + sizeof(RepLds) +
@@ -2195,7 +2254,10 @@ hipError_t pair_occupancy(int *per_cu, size_t lds, int lanes, int sep)
         return occ(k_pairs<T, DIM, 16, false, kSearchOcc, 4, kSearchOnly, false>);
     } else {
         if constexpr (STAGE == kFused)
+        {
             if (sep == 16) return occ(k_pairs<T, DIM, 16, false, O, 16, STAGE, FC>);
+            if (sep == 1 && !FC && DIM == 3) return occ(k_pairs<T, 3, 8, false, O, 1, STAGE, false>);
+        }
         return lanes == 8 ? occ(k_pairs<T, DIM, 8, false, O, 4, STAGE, FC>) : occ(k_pairs<T, DIM, 16, false, O, 4, STAGE, FC>);
     }
 }

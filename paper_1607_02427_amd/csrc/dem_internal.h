@@ -32,6 +32,21 @@ constexpr int kDefaultPairLanes = 16;
 constexpr int kDefaultPairWaves = 2;
 constexpr int kDefaultPairSep = 4;
 __host__ __device__ constexpr int pair_tile(int sep_lanes) { return kPairWaves * (64 / sep_lanes); }
+// From this many pair slots up, 3D systems with 8 lanes per pair and the
+// 4-lane separation stage run that stage with one lane per pair instead (64
+// pairs per wavefront, 256 per tile): a quarter of its instructions, but
+// tiles four times as long, of which a workgroup has to have several for the
+// last ones not to leave the chip idle.  Four lanes against one, in us:
+// 262,144 octahedra (6.8 million slots) 452 and 359, 131,072 L-prisms (3.1
+// million) 257 and 239, in FP64 384 and 349, 262,144 tetrahedra (7.3 million)
+// 604 and 533; but 131,072 cubes (2.4 million) 164 and 169, 64,000 tetrahedra
+// (1.8 million) 140 and 159, 32,768 octahedra (0.85 million) 76 and 82.
+// Bodies of one vertex have no feature stage to speak of, and gain earlier:
+// 30,000 spheres (0.54 million) 9.9 and 8.3, 64,000 (1.0 million) 15.3 and
+// 12.8; 20,000 (0.36 million) 8.3 and 8.6.  Polygons stay with four lanes
+// (262,144 squares 75 and 73, pentagons 91 and 92).
+constexpr long long kLanePairSlots = 3000000;
+constexpr long long kLanePointSlots = 500000;
 // Shape-local feature cells (Sec. V): a uniform grid over each shape's
 // body frame, kFcGrid3 cells per axis in 3D (kFcGrid2 in 2D), covering the
 // shape's circumradius plus its reach.  Cell c holds .x: the faces (3D) or
@@ -207,7 +222,9 @@ struct alignas(16) ShapeTab {
     int fc_g;
     T r, R;
     T fc_lo, fc_ih;
-    int nsep, pad[3];
+    int nsep, pad0;
+    T rin;                       // no direction has its lowest vertex nearer to the centre than this (0 if not convex)
+    T pad1;
     Vec4<T> v[DEM_MAX_VERTS];    // vertex, 0
     Vec4<T> ea[DEM_MAX_EDGES];   // first end point, |b - a|^2
     Vec4<T> ed[DEM_MAX_EDGES];   // b - a, 1 / |b - a|^2
@@ -286,7 +303,7 @@ struct BatchParams {
     int pair_blocks;             // grid of the pair kernel (a multiple of 8)
     int pair_lanes;              // lanes per particle pair in the pair kernel (8 or 16)
     int pair_waves;              // its wavefronts per SIMD (2 or 3)
-    int pair_sep;                // lanes per pair in its separation stage (4 or 16)
+    int pair_sep;                // lanes per pair in its separation stage (1, 4 or 16)
     int tile;                    // pairs per tile: pair_tile(pair_sep)
     int pair_split;              // 1: two kernels, contact search then contact forces
     int feature_cells;           // 1: the feature search reads the shape-local feature cells

@@ -578,6 +578,12 @@ void pack_table(const HostShape &D, ShapeTab<T> &F)
     F.fc_lo = (T)D.fc_lo;
     F.fc_ih = (T)D.fc_ih;
     F.nsep = D.nsep;
+    // the inner radius about the centre, of convex bodies (every face or edge
+    // a supporting plane), rounded down
+    double rin = 1e300;
+    for (int k = 0; k < D.nsep; ++k) rin = std::min(rin, D.so[k]);
+    const bool convex = D.nsep > 0 && D.nsep == (D.nf > 0 ? D.nf : D.ne);
+    F.rin = convex ? (T)(std::max(rin, 0.0) * (1.0 - 1e-5)) : T(0);
     auto vec = [](const double (&a)[3], double w) { return Vec4<T>{(T)a[0], (T)a[1], (T)a[2], (T)w}; };
     for (int k = 0; k < D.nv; ++k) F.v[k] = vec(D.v[k], 0.0);
     for (int k = 0; k < D.ne; ++k) {
@@ -689,6 +695,23 @@ void pick_shape(dem_system *h)
     h->pair_lanes = few || edged || (wide && !f32) ? 16 : 8;
 }
 
+// Whether the separation stage of a handle with four lanes per pair there
+// takes one instead (kLanePairSlots).  Its queue entries hold slots of 24 bits.
+bool lane_per_pair(const dem_system *h)
+{
+    if (h->dim != 3 || h->pair_sep != 4 || h->pair_lanes != 8 || h->pair_split || h->feature_cells ||
+        h->bp.N > 1 << 24)
+        return false;
+    long long slots = 0;
+    bool points = true;
+    for (const Replica &R : h->reps) {
+        if (!R.live) continue;
+        slots += R.sp.pcap;
+        points &= R.edges == 0;
+    }
+    return slots >= (points ? kLanePointSlots : kLanePairSlots);
+}
+
 // Batch-wide launch parameters from the replica table.
 void refresh_batch(dem_system *h)
 {
@@ -698,10 +721,10 @@ void refresh_batch(dem_system *h)
     b.tab_slots = 1;
     b.pair_lanes = h->pair_lanes;
     b.pair_waves = h->pair_waves;
-    b.pair_sep = h->pair_sep;
     b.pair_split = h->pair_split;
     b.feature_cells = h->feature_cells;
-    b.tile = pair_tile(h->pair_sep);
+    b.pair_sep = lane_per_pair(h) ? 1 : h->pair_sep;
+    b.tile = pair_tile(b.pair_sep);
     b.thermal = 0;
     b.fold = 1;
     long long tiles = 0;
@@ -1992,6 +2015,8 @@ dem_status dem_set_feature_cells(dem_handle h, int32_t on)
     if (on == h->feature_cells) return DEM_OK;
     h->feature_cells = on;
     refresh_batch(h);
+    launch_lists(make_launch(h), LISTS_PLAN, h->stream);  // (tiles may be of another size)
+    HIPCHK(h, hipGetLastError());
     drop_graph(h);
     return DEM_OK;
 }

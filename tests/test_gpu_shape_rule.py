@@ -55,3 +55,41 @@ def test_batch_moves_between_shapes(precision):
         assert np.array_equal(getattr(want[0], k), getattr(got[0], k)), k
     for k in want[1]:
         assert np.array_equal(want[1][k], got[1][k]), k
+
+
+def _mixed(n):
+    """Cubes and spheres, and L-prisms among them, on a contact lattice of L-prism spacing."""
+    s = _gas(I.lprism(), n)
+    s.shapes = [s.shapes[0], I.sphere(0.5), I.cube()]
+    s.shape_id = (np.arange(s.n) % 3).astype(np.int32)
+    return s
+
+
+# more pair slots than the limit from which a lane takes a whole pair in the
+# separation stage (3,000,000, and 500,000 for bodies of one vertex), against
+# four lanes per pair; the last tile ragged
+@pytest.mark.parametrize("make,precision,limit", [(lambda: _gas(I.cube(), 167003), "fp32", 3000000),
+                                                  (lambda: _gas(I.octahedron(), 191009), "fp64", 3000000),
+                                                  (lambda: _gas(I.sphere(0.5), 30011), "fp32", 500000),
+                                                  (lambda: _gas(I.lprism(), 126011), "fp32", 3000000),
+                                                  (lambda: _mixed(126001), "fp32", 3000000),
+                                                  (lambda: _mixed(126001), "fp64", 3000000)])
+def test_a_lane_per_pair_finds_what_four_find(make, precision, limit):
+    from paper_1607_02427_amd import dem
+    s = make()
+    with dem.DemSystem(s, precision) as g:
+        cap = g.list_info()[2]
+        assert (s.n + 63) // 64 * 64 * cap // 2 >= limit
+        got = []
+        for shape in ((8, 1, 2, 4), (16, 1, 2, 4), (8, 2, 2, 4)):
+            print(f"[lane per pair] {s.n} {precision} {shape}", flush=True)
+            g.set_pair_shape(*shape)
+            g.force_stats(reset=True)
+            g.compute_forces()
+            st = g.force_stats()
+            got.append((g.outputs(), {k: st[k] for k in ("pairs", "in_cutoff")}))
+        assert got[0][1]["in_cutoff"] > 0
+        for out, st in got[1:]:
+            assert st == got[0][1]
+            for k in out:
+                assert np.array_equal(out[k], got[0][0][k]), k
