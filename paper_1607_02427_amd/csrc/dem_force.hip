@@ -1775,9 +1775,9 @@ inline int row_workgroups(const BatchParams &b) { return pad8(std::min(b.nchunk 
 // replica-dependent workgroup so that small replicas spread out too.
 template <int DIM>
 __device__ void step_rows(const BatchParams &b, const SysParams *reps, const StatePtrs &s, const ListPtrs &l,
-                          const int64_t *budget, int *buf, int first)
+                          const int64_t *budget, lb::RowBuf &buf, int first)
 {
-    const int nrole = (int)gridDim.x - first, me = (int)blockIdx.x - first;
+    const int nrole = (int)gridDim.x - first, me = xcd_block((int)blockIdx.x - first, nrole);
     for (int r0 = 0; r0 < b.nrep; r0 += 64) {
         const int rl = r0 + (int)__lane_id();
         const bool bld = rl < b.nrep && lb::building(LISTS_STEP, rl, reps[rl], l.flags + rl * FLAG_COUNT, budget);
@@ -1818,7 +1818,7 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather(BatchParams b, const Sy
 {
     const int G = KICK ? pad8(b.nchunk) : (int)gridDim.x;  // chunk workgroups
     if (KICK && (int)blockIdx.x >= G) {
-        __shared__ int rbuf[lb::kNbrPer * kRowMax];
+        __shared__ lb::RowBuf rbuf;
         if (l.gflags[G_NOW] != 0) step_rows<DIM>(b, reps, s, l, budget, rbuf, G);
         return;
     }
@@ -2013,7 +2013,7 @@ __global__ void __launch_bounds__(kGatherBlock) k_replica_tail(BatchParams b, Sy
                                                                int64_t *steps)
 {
     if ((int)blockIdx.x >= b.nrep) {
-        static_assert(kGatherBlock == kChunk, "one wavefront per chunk");
+        static_assert(kGatherBlock == 64, "one wavefront per workgroup");
         __shared__ int part[kGatherBlock];
         lb::fill_step(b, reps, l, (int)blockIdx.x - b.nrep, (int)gridDim.x - b.nrep, part);
         return;
@@ -2176,7 +2176,7 @@ void gather_t(const Launch &L, bool kick, hipStream_t stream)
         k_gather<T, DIM, true><<<pad8(L.b.nchunk) + row_workgroups(L.b), kGatherBlock, 0, stream>>>(
             L.b, L.reps, L.s, L.o, L.l, rec, L.ke_part, L.thermo, L.budget, L.steps);
         if (!L.b.fold)
-            k_replica_tail<<<L.b.nrep + std::min(L.b.nchunk, kFillWorkgroups), kGatherBlock, 0, stream>>>(
+            k_replica_tail<<<L.b.nrep + std::min(L.b.nchunk * lb::kFillParts, kFillWorkgroups), kGatherBlock, 0, stream>>>(
                 L.b, const_cast<SysParams *>(L.reps), L.l, L.ke_part, L.thermo, L.budget, L.steps);
     }
     else

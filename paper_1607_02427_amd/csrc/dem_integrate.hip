@@ -400,11 +400,12 @@ __global__ void __launch_bounds__(kChunk) k_kick_drift(BatchParams b, const SysP
     s.image[3 * i + 2] = img[2];
     if (rebuild != 0) {
         // this step rebuilds the lists from the positions after this drift:
-        // the particle goes into its cell now (and the new pair total
-        // restarts for the row workgroups to add to); this step's forces
+        // the particle goes into its cell now (and the new pair totals
+        // restart for the row workgroups to add to); this step's forces
         // still use the lists in place, which the trigger of the previous
         // step has kept valid for these positions
         if (i == p.off) l.flags[r * FLAG_COUNT + FLAG_NEWPAIRS] = 0;
+        if (threadIdx.x == 0) l.ctot[cb] = 0;
         cell_insert(p, l, i, x[0], x[1], x[2]);
     } else {
         // The next step rebuilds them if the displacement since the last
@@ -509,7 +510,7 @@ void launch_begin(const Launch &L, hipStream_t stream)
 }
 
 // workgroups of a folded step's kernels that write pair entries
-static int fill_workgroups(const BatchParams &b) { return b.fold ? std::min(b.nchunk, kFillWorkgroups) : 0; }
+static int fill_workgroups(const BatchParams &b) { return b.fold ? std::min(b.nchunk * lb::kFillParts, kFillWorkgroups) : 0; }
 
 void launch_end(const Launch &L, hipStream_t stream)
 {

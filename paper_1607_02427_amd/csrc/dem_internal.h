@@ -107,8 +107,10 @@ constexpr int kFoldChunks = 4096;
 constexpr int kCellCap = 64;
 constexpr int kRowMax = 128;
 // Particles whose neighbour rows one wavefront builds at a time (16 lanes
-// each); the pair counts are totalled per such group (ListPtrs::ptot).
+// each), and what such a wavefront adds to its chunk's word of
+// ListPtrs::ctot besides its pairs (a chunk has kChunk * kRowMax at most).
 constexpr int lb_rows_per_group = 4;
+constexpr int kChunkPart = 1 << 16;
 // Per-replica thermostat words (double, thermo[r * TH_COUNT + w]).  Between
 // steps a replica is either closed (its velocities carry every half step
 // so far) or open: the closing half step of its last step has scaled the
@@ -343,7 +345,7 @@ struct ListPtrs {
     // half list of unordered pairs (i < j), rebuilt with the neighbour list
     int32_t *klo;                // [N] first row slot of i holding a j > i
     int32_t *pstart;             // [N] first pair index of i, local to its replica
-    int32_t *ptot;               // [N / 4] pairs owned by each group of 4 particles (a row workgroup's)
+    int32_t *ctot;               // [chunks] pairs owned by the chunk's particles, and kChunkPart times its row groups that are done
     int4 *pairs;                 // [pair slots] {i, j, slot of j in i's row, slot of i in j's row (-1: missing)}
     // row slots whose record was written since the particle's last gather:
     // bit k % 32 of word k / 32, [slot_words(cap)][N]; the gather reads

@@ -3,8 +3,8 @@
 // inside a step (dem_force.hip):
 //   * nbr_rows: the neighbour rows of 4 particles by one wavefront (16
 //     lanes per particle);
-//   * fill_chunk: the pair offsets and pair entries of one chunk by one
-//     wavefront;
+//   * fill_part: the pair offsets and pair entries of a quarter of a chunk
+//     by one wavefront;
 //   * plan: the tile plan of the pair kernel by one workgroup.
 // The list decisions are an integer contract: |minimum image (x_j -
 // x_i)|^2 < r_list^2 evaluated in FP64 as written, with no contraction into
@@ -20,6 +20,17 @@ namespace lb {
 constexpr int kNbrLanes = 16;                 // lanes per particle in nbr_rows
 constexpr int kNbrPer = lb_rows_per_group;    // particles per nbr_rows wavefront
 static_assert(kNbrPer * kNbrLanes == 64, "one wavefront per group of particles");
+constexpr int kNb3 = 27;                      // neighbour cells, the own one included
+constexpr int kCellQuads = kCellCap / 4;
+static_assert(kCellCap % 4 == 0 && kRowMax % 4 == 0 && kNb3 * kCellCap <= 65536, "quads of slots, in 16 bits");
+
+// LDS of an nbr_rows wavefront, per particle: its hits, its neighbour cells
+// and their occupied slots, four to an entry.
+struct RowBuf {
+    int row[kNbrPer][kRowMax];
+    int cell[kNbrPer][kNb3];
+    unsigned short quad[kNbrPer][kNb3 * kCellQuads];  // (cell * kCellQuads + quad) * 4 + slots in use - 1
+};
 
 // Minimum image of d = x_j - x_i for positions in [0, L].  This equals
 // d - L rint(d / L) bit for bit except where |d| is within rounding of L/2,
@@ -91,35 +102,58 @@ __device__ int block_scan(const int32_t *count, int32_t *start, int m, int *part
     return total;
 }
 
+// Orders a wavefront's LDS writes before its reads after this.
+__device__ inline void rows_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Neighbour rows of particles 4 vb .. 4 vb + 3 (all of one chunk, so of one
 // replica), by one wavefront (a workgroup of 64 threads; the caller has
-// checked that the replica builds).  Each lane scans some of
-// the neighbour cells (or, without cells, a sixteenth of the replica); hits
-// are appended to the particle's LDS buffer in ballot order, then every
-// kept hit finds its rank (the number of smaller hits) and is stored in
-// that row slot, so the row ascends and keeps the cap smallest j.  The row's
-// count of j > i is the particle's pair count; the wavefront stores its
-// total as ptot[vb] and adds it to the replica's FLAG_NEWPAIRS (cleared when
-// the build starts).  buf: kNbrPer * kRowMax ints of LDS.
+// checked that the replica builds).  The occupied slots of a particle's
+// neighbour cells are listed in LDS, four to an entry, and dealt over its 16
+// lanes, so that each lane has four candidates' loads under way at once and
+// all lanes end together (or, without cells, each lane scans a sixteenth of
+// the replica); hits are appended to the particle's LDS buffer in ballot
+// order, then every kept hit finds its rank (the number of smaller hits) and
+// is stored in that row slot, so the row ascends and keeps the cap smallest
+// j.  The row's count of j > i is the particle's pair count.  The wavefront
+// adds its total to its chunk's (ListPtrs::ctot, cleared when the build
+// starts), and the chunk's last adds the chunk's to the replica's
+// FLAG_NEWPAIRS: one addition to that word per chunk.
+//
+// What bounds it is the chain of loads, cell count, slot, position.  With a
+// cell per lane (27 over 16 lanes) and one candidate per lane under way, a
+// rank search that read LDS a word at a time, a same-address addition per
+// wavefront and neighbouring rows written by different XCDs, the rows of
+// 32,768 octahedra (52 slots a row) took 128 us; they take 51.
 template <int DIM>
 __device__ void nbr_rows(const BatchParams &b, const SysParams &p, const StatePtrs &s, const ListPtrs &l, int32_t *fl,
-                         int vb, int *buf)
+                         int vb, RowBuf &buf)
 {
+    const int end = p.off + p.n;
+    if (vb * kNbrPer >= end) return;
     const int g = threadIdx.x / kNbrLanes, sub = threadIdx.x % kNbrLanes;
     const int i = vb * kNbrPer + g;
-    int *row = buf + g * kRowMax;
-    const bool mine = i < p.off + p.n;
+    int *row = buf.row[g];
+    const bool mine = i < end;
+    const int self = mine ? i : p.off;
     const unsigned long long gmask = 0xffffull << (kNbrLanes * ((threadIdx.x & 63) / kNbrLanes));
-    const unsigned long long below = lanes_below();
-    const double xi = mine ? s.x[i] : 0.0, yi = mine ? s.y[i] : 0.0, zi = (mine && DIM == 3) ? s.z[i] : 0.0;
+    const unsigned long long below = lanes_below() & gmask;
+    const double xi = s.x[self], yi = s.y[self], zi = DIM == 3 ? s.z[self] : 0.0;
     int m = 0;  // hits so far (the same in all lanes of the particle)
     if (p.use_cells) {
-        const int c = mine ? l.pcell[i] : 0;
+        const int c = l.pcell[self];
         const int cx = c % p.nc[0], cy = (c / p.nc[0]) % p.nc[1], cz = c / (p.nc[0] * p.nc[1]);
-        constexpr int kNb = DIM == 3 ? 27 : 9;
-        for (int t0 = 0; t0 < kNb; t0 += kNbrLanes) {
-            const int t = t0 + sub;
-            int cc = 0, cnt = 0;
+        constexpr int kNb = DIM == 3 ? kNb3 : 9;
+        constexpr int kPass = (kNb + kNbrLanes - 1) / kNbrLanes;
+        int cnt[kPass];
+#pragma unroll
+        for (int u = 0; u < kPass; ++u) {
+            const int t = u * kNbrLanes + sub;
+            cnt[u] = 0;
             if (mine && t < kNb) {
                 int ax = cx + t % 3 - 1, ay = cy + (t / 3) % 3 - 1, az = cz + (DIM == 3 ? t / 9 - 1 : 0);
                 ax += (ax < 0) ? p.nc[0] : 0;
@@ -128,21 +162,48 @@ __device__ void nbr_rows(const BatchParams &b, const SysParams &p, const StatePt
                 ay -= (ay >= p.nc[1]) ? p.nc[1] : 0;
                 az += (az < 0) ? p.nc[2] : 0;
                 az -= (az >= p.nc[2]) ? p.nc[2] : 0;
-                cc = p.coff + ax + p.nc[0] * (ay + p.nc[1] * az);
-                cnt = min(l.cell_count[cc], kCellCap);
+                const int cc = p.coff + ax + p.nc[0] * (ay + p.nc[1] * az);
+                buf.cell[g][t] = cc;
+                cnt[u] = min(l.cell_count[cc], kCellCap);
             }
-            for (int k = 0;; ++k) {
-                const bool has = k < cnt;
-                if (__ballot(has) == 0) break;
-                int j = 0;
-                bool hit = false;
-                if (has) {
-                    j = l.cell_slot[(size_t)cc * kCellCap + k];
-                    hit = j != i && within(p, s, xi, yi, zi, j);
-                }
-                const unsigned long long hm = __ballot(hit);
-                const int pos = m + __popcll(hm & below & gmask);
-                if (hit && pos < kRowMax) row[pos] = j;
+        }
+        int nq = 0;  // entries listed
+#pragma unroll
+        for (int u = 0; u < kPass; ++u) {
+            const int t = u * kNbrLanes + sub, q = (cnt[u] + 3) / 4;
+            int incl = q;
+            for (int off = 1; off < kNbrLanes; off <<= 1) {
+                const int v = __shfl_up(incl, off, kNbrLanes);
+                if (sub >= off) incl += v;
+            }
+            unsigned short *out = buf.quad[g] + nq + incl - q;
+            for (int k = 0; k < q; ++k)
+                out[k] = (unsigned short)((t * kCellQuads + k) * 4 + min(cnt[u] - 4 * k, 4) - 1);
+            nq += __shfl(incl, kNbrLanes - 1, kNbrLanes);
+        }
+        rows_sync();
+        for (int e = sub;; e += kNbrLanes) {
+            const bool has = e < nq;
+            if (__ballot(has) == 0) break;
+            int4 j = make_int4(self, self, self, self);
+            if (has) {
+                const int code = buf.quad[g][e], n = code & 3, t = code / (4 * kCellQuads);
+                const int4 w = *reinterpret_cast<const int4 *>(l.cell_slot + (size_t)buf.cell[g][t] * kCellCap +
+                                                               ((code >> 2) & (kCellQuads - 1)) * 4);
+                j.x = w.x;  // slots not in use hold anything
+                j.y = n > 0 ? w.y : self;
+                j.z = n > 1 ? w.z : self;
+                j.w = n > 2 ? w.w : self;
+            }
+            const int js[4] = {j.x, j.y, j.z, j.w};
+            bool hit[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) hit[u] = (int)(js[u] != self) & (int)within(p, s, xi, yi, zi, js[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long hm = __ballot(hit[u]);
+                const int pos = m + __popcll(hm & below);
+                if (hit[u] && pos < kRowMax) row[pos] = js[u];
                 m += __popcll(hm & gmask);
             }
         }
@@ -151,106 +212,139 @@ __device__ void nbr_rows(const BatchParams &b, const SysParams &p, const StatePt
             const int j = p.off + k0 + sub;
             const bool hit = mine && k0 + sub < p.n && j != i && within(p, s, xi, yi, zi, j);
             const unsigned long long hm = __ballot(hit);
-            const int pos = m + __popcll(hm & below & gmask);
+            const int pos = m + __popcll(hm & below);
             if (hit && pos < kRowMax) row[pos] = j;
             m += __popcll(hm & gmask);
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const size_t N = (size_t)b.N;
     const int cap = b.cap;
-    const int mm = min(m, kRowMax);
+    const int mm = min(m, kRowMax), quads = (mm + 3) / 4;
+    if (sub < 4 * quads - mm) row[mm + sub] = 0x7fffffff;
+    rows_sync();
     int lower = 0;  // kept hits below i
-    if (mine)
-        for (int e = sub; e < mm; e += kNbrLanes) {
-            const int v = row[e];
-            int rank = 0;
-            for (int f = 0; f < mm; ++f) rank += row[f] < v ? 1 : 0;
-            if (rank < cap) {
-                l.nbr[(size_t)rank * N + i] = v;
-                lower += v < i ? 1 : 0;
-            }
+    for (int e0 = 0; e0 < mm; e0 += 4 * kNbrLanes) {  // four hits per lane at a time
+        int v[4], rank[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kNbrLanes + sub;
+            v[u] = e < mm ? row[e] : -1;
         }
+        for (int f = 0; f < quads; ++f) {
+            const int4 w = reinterpret_cast<const int4 *>(row)[f];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                rank[u] += (int)(w.x < v[u]) + (int)(w.y < v[u]) + (int)(w.z < v[u]) + (int)(w.w < v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (mine && v[u] >= 0 && rank[u] < cap) {
+                l.nbr[(size_t)rank[u] * N + i] = v[u];
+                lower += v[u] < i ? 1 : 0;
+            }
+    }
     for (int off = kNbrLanes / 2; off > 0; off >>= 1) lower += __shfl_xor(lower, off, kNbrLanes);
     const int kept = min(m, cap);
     if (mine && sub == 0) {
         l.n_nbr[i] = kept;
         l.klo[i] = lower;
-        l.pstart[i] = kept - lower;  // pair count; fill_chunk turns it into an offset
         if (m > cap) atomicMax(&fl[FLAG_MAXROW], m);
         l.xlast[i] = xi;
         l.xlast[N + i] = yi;
         l.xlast[2 * N + i] = zi;
     }
-    // the wavefront's pair count, for the pair offsets and (an integer sum,
-    // in any order) the replica's total
+    // the wavefront's pair count (integer sums, in any order)
     int tot = (mine && sub == 0) ? kept - lower : 0;
     for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
     if (threadIdx.x == 0) {
-        l.ptot[vb] = tot;
-        atomicAdd(&fl[FLAG_NEWPAIRS], tot);
+        const int c = vb * kNbrPer / kChunk;
+        const int parts = (min(end - c * kChunk, kChunk) + kNbrPer - 1) / kNbrPer;  // wavefronts of this chunk
+        const int sum = atomicAdd(&l.ctot[c], tot + kChunkPart) + tot;
+        if (sum / kChunkPart == parts - 1) atomicAdd(&fl[FLAG_NEWPAIRS], sum % kChunkPart);
     }
-    // buf is free for the next call once every lane has read it
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Pair entries: the owner i of pair q writes {i, j, slot of j in i's row,
-// slot of i in j's row} with one store, the last found by bisection in j's
-// row (-1 if a row overflow left i out of it, which is reported).
-__device__ inline void pair_fill(const SysParams &p, const BatchParams &b, const ListPtrs &l, int i)
-{
-    const size_t N = (size_t)b.N;
-    const int m = min(l.n_nbr[i], b.cap), k0 = max(l.klo[i], 0);
-    int4 *pairs = l.pairs + p.poff;
-    for (int k = k0; k < m; ++k) {
-        const int q = l.pstart[i] + (k - k0);
-        if (q >= p.pcap) break;  // (only after a row overflow, which is reported)
-        const int j = l.nbr[(size_t)k * N + i];
-        int lo = 0, hi = l.klo[j];  // j's neighbours below j, ascending
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (l.nbr[(size_t)mid * N + j] < i) lo = mid + 1;
-            else hi = mid;
-        }
-        const int w = (lo < l.klo[j] && l.nbr[(size_t)lo * N + j] == i) ? lo : -1;
-        pairs[q] = make_int4(i, j, k, w);
-    }
+    rows_sync();  // buf is free for the next call once every lane has read it
 }
 
 // Pair offsets (unless `refill`: the offsets are kept) and pair entries of
-// chunk c of replica p, by one wavefront (lane = particle c * 64 + lane),
-// then the chunk's cells emptied when `clear_cells`.  The offset of i is the
-// counts of the replica's row groups (ptot) before this chunk plus the
-// counts of the chunk's particles before i.
-__device__ inline void fill_chunk(const BatchParams &b, const SysParams &p, const ListPtrs &l, int c, bool refill,
-                                  bool clear_cells)
+// the 16 particles of quarter `part` of chunk c of replica p, by one
+// wavefront, then their cells emptied when `clear_cells`.  The offset of i
+// is the counts of the replica's chunks (ctot) before this one plus the
+// counts of the chunk's particles before i.  The owner i of pair q writes
+// {i, j, slot of j in i's row, slot of i in j's row} with one store, the
+// last found by bisection in j's row (-1 if a row overflow left i out of it,
+// which is reported).
+//
+// What bounds it is the chain of loads of the bisections, so a particle's
+// pairs are dealt over four lanes, and a lane searches for four at once
+// (32,768 octahedra 13.5 us; a lane per particle, one pair at a time, 40).
+constexpr int kFillLanes = 4, kFillPer = 64 / kFillLanes, kFillParts = kChunk / kFillPer, kFillPairs = 4;
+__device__ inline void fill_part(const BatchParams &b, const SysParams &p, const ListPtrs &l, int c, int part,
+                                 bool refill, bool clear_cells)
 {
-    const int lane = __lane_id();
-    const int i = c * kChunk + lane;
-    const bool mine = i < p.off + p.n;
+    const int lane = __lane_id(), sub = lane % kFillLanes;
+    const int end = p.off + p.n;
+    const int i = c * kChunk + part * kFillPer + lane / kFillLanes;
+    const size_t N = (size_t)b.N;
+    int start = 0;
     if (!refill) {
-        const int cnt = mine ? l.pstart[i] : 0;
+        const int t = c * kChunk + lane;
+        const int cnt = t < end ? l.n_nbr[t] - l.klo[t] : 0;
+        int prior = 0;
+#pragma unroll 8
+        for (int q = p.off / kChunk + lane; q < c; q += 64) prior += l.ctot[q] % kChunkPart;
         int incl = cnt;
         for (int off = 1; off < 64; off <<= 1) {
             const int v = __shfl_up(incl, off, 64);
             if (lane >= off) incl += v;
         }
-        int prior = 0;
-#pragma unroll 8
-        for (int q = p.off / kNbrPer + lane; q < c * (kChunk / kNbrPer); q += 64) prior += l.ptot[q];
         for (int off = 32; off > 0; off >>= 1) prior += __shfl_xor(prior, off, 64);
-        if (mine) l.pstart[i] = prior + incl - cnt;
+        start = __shfl(prior + incl - cnt, part * kFillPer + lane / kFillLanes, 64);
     }
-    if (!mine) return;
-    pair_fill(p, b, l, i);
+    if (i >= end) return;
+    if (refill) start = l.pstart[i];
+    else if (sub == 0) l.pstart[i] = start;
+    const int m = min(l.n_nbr[i], b.cap), k0 = max(l.klo[i], 0);
+    int4 *pairs = l.pairs + p.poff;
+    for (int kb = k0 + sub; kb < m; kb += kFillLanes * kFillPairs) {
+        int j[kFillPairs], lo[kFillPairs], hi[kFillPairs], w[kFillPairs];
+#pragma unroll
+        for (int u = 0; u < kFillPairs; ++u) j[u] = l.nbr[(size_t)min(kb + u * kFillLanes, m - 1) * N + i];
+#pragma unroll
+        for (int u = 0; u < kFillPairs; ++u) {
+            lo[u] = 0;
+            hi[u] = l.klo[j[u]];  // j's neighbours below j, ascending
+            w[u] = -1;
+        }
+        for (;;) {
+            bool open = false;
+            int v[kFillPairs];
+#pragma unroll
+            for (int u = 0; u < kFillPairs; ++u) {
+                open |= lo[u] < hi[u];
+                v[u] = l.nbr[(size_t)min((lo[u] + hi[u]) >> 1, b.cap - 1) * N + j[u]];
+            }
+            if (!open) break;
+#pragma unroll
+            for (int u = 0; u < kFillPairs; ++u) {
+                const int mid = (lo[u] + hi[u]) >> 1;
+                if (lo[u] < hi[u]) {
+                    if (v[u] == i) w[u] = mid;
+                    if (v[u] < i) lo[u] = mid + 1;
+                    else hi[u] = mid;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kFillPairs; ++u) {
+            const int k = kb + u * kFillLanes, q = start + (k - k0);
+            // (q >= pcap only after a row overflow, which is reported)
+            if (k < m && q < p.pcap) pairs[q] = make_int4(i, j[u], k, w[u]);
+        }
+    }
     // every particle of the cell writes the same zero (without cells the
     // word is zero already; use_cells of a replica under the barostat may
     // change while this runs)
-    if (clear_cells) l.cell_count[p.coff + l.pcell[i]] = 0;
+    if (clear_cells && sub == 0) l.cell_count[p.coff + l.pcell[i]] = 0;
 }
 
 // Tile plan (the first tile of each replica, b.tile pairs per tile) by one
@@ -274,7 +368,7 @@ __device__ void plan(const BatchParams &b, const SysParams *reps, const ListPtrs
 
 // The end of a step's list build, by workgroup fb of nfb (64 threads each):
 // the tile plan (the first of them) and the pair entries of every chunk of
-// the replicas with FLAG_FILL, one chunk per workgroup at a time; the cells
+// the replicas with FLAG_FILL, a quarter of a chunk per workgroup at a time; the cells
 // are emptied for the next build.  part: 64 ints of LDS.
 __device__ inline void fill_step(const BatchParams &b, const SysParams *reps, const ListPtrs &l, int fb, int nfb, int *part)
 {
@@ -290,8 +384,8 @@ __device__ inline void fill_step(const BatchParams &b, const SysParams *reps, co
             const int r = r0 + __builtin_ctzll(m);
             const SysParams &p = reps[r];
             const int c0 = p.off / kChunk, nc = (p.n + kChunk - 1) / kChunk;
-            for (int k = (fb + nfb - (int)(((long long)r * 977) % nfb)) % nfb; k < nc; k += nfb)
-                fill_chunk(b, p, l, c0 + k, false, true);
+            for (int k = (fb + nfb - (int)(((long long)r * 977) % nfb)) % nfb; k < nc * kFillParts; k += nfb)
+                fill_part(b, p, l, c0 + k / kFillParts, k % kFillParts, false, true);
         }
     }
 }

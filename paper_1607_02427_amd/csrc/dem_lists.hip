@@ -13,17 +13,19 @@
 //
 // A build has three parts, each a grid over particles:
 //   1. cells: every particle goes into the fixed-capacity slots of its cell;
-//   2. rows: 16 lanes per particle scan the 3^d neighbour cells, collect
-//      the hits in LDS by wave ballots, and rank-sort them into the row;
-//   3. fill: each particle writes the pair entries it owns and empties its
-//      cell; one workgroup recomputes the tile plan (the first tile of every
-//      replica) for the pair kernel.
+//   2. rows: 16 lanes per particle share the slots of the 3^d neighbour
+//      cells, collect the hits in LDS by wave ballots, and rank-sort them
+//      into the row;
+//   3. fill: four lanes per particle write the pair entries it owns and
+//      empty its cell; one workgroup recomputes the tile plan (the first
+//      tile of every replica) for the pair kernel.
 // The kernels here build outside a step (k_assign, k_nbr, k_fill).  Inside
 // a step the same device code (dem_listbuild.h) runs in the step kernels:
 // the kick-drift puts the particles into cells, extra workgroups of the
-// pair kernel write the rows while the pair workgroups still use the old
-// pair entries, and extra workgroups of the replica tail write the pair
-// entries and the plan; the new lists serve from the next step on.
+// gather write the rows once the pair kernel is done with those in place,
+// and extra workgroups of the next step's kick-drift (or of the closing
+// kernel or the replica tail) write the pair entries and the plan; the new
+// lists serve from the next step on.
 #include "dem_listbuild.h"
 
 namespace dem {
@@ -42,6 +44,7 @@ __global__ void __launch_bounds__(kBlock) k_assign(BatchParams b, const SysParam
     const SysParams &p = reps[r];
     if (!lb::building(mode, r, p, l.flags + r * FLAG_COUNT, budget) || i >= p.off + p.n) return;
     if (i == p.off) l.flags[r * FLAG_COUNT + FLAG_NEWPAIRS] = 0;  // the row workgroups add the replica's pairs
+    if (i % kChunk == 0) l.ctot[c] = 0;                           // and the chunk's
     cell_insert(p, l, i, s.x[i], s.y[i], p.dim == 3 ? s.z[i] : 0.0);
 }
 
@@ -50,8 +53,9 @@ template <int DIM>
 __global__ void __launch_bounds__(64) k_nbr(BatchParams b, const SysParams *reps, StatePtrs s, ListPtrs l,
                                                const int64_t *budget, int mode)
 {
-    __shared__ int buf[kNbrPer * kRowMax];
-    const int vb = blockIdx.x;
+    __shared__ lb::RowBuf buf;
+    const int vb = xcd_block(blockIdx.x, gridDim.x);  // neighbouring rows share lines of nbr
+    if (vb >= b.nchunk * (kChunk / kNbrPer)) return;
     const int r = l.chunk_rep[vb * kNbrPer / kChunk];
     if (r < 0) return;
     const SysParams &p = reps[r];
@@ -60,8 +64,9 @@ __global__ void __launch_bounds__(64) k_nbr(BatchParams b, const SysParams *reps
     lb::nbr_rows<DIM>(b, p, s, l, fl, vb, buf);
 }
 
-// Pair offsets and entries (lb::fill_chunk), one wavefront per chunk; block
-// 0 first recomputes the tile plan.
+// Pair offsets and entries (lb::fill_part), one workgroup per chunk; block 0
+// first recomputes the tile plan.
+static_assert(kBlock == 64 * lb::kFillParts, "a wavefront per quarter of a chunk");
 __global__ void __launch_bounds__(kBlock) k_fill(BatchParams b, const SysParams *reps, ListPtrs l,
                                                     const int64_t *budget, int mode, int clear_cells)
 {
@@ -72,12 +77,12 @@ __global__ void __launch_bounds__(kBlock) k_fill(BatchParams b, const SysParams 
                    lb::building(mode, r, reps[r], l.flags + r * FLAG_COUNT, budget);
         });
     if (mode == LISTS_PLAN) return;
-    const int c = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kChunk);
+    const int c = xcd_block(blockIdx.x, gridDim.x);
     const int r = __builtin_amdgcn_readfirstlane(c < b.nchunk ? l.chunk_rep[c] : -1);
     if (r < 0) return;
     const SysParams &p = reps[r];
     if (!lb::building(mode, r, p, l.flags + r * FLAG_COUNT, budget)) return;
-    lb::fill_chunk(b, p, l, c, mode == LISTS_REFILL, clear_cells != 0);
+    lb::fill_part(b, p, l, c, (int)threadIdx.x / 64, mode == LISTS_REFILL, clear_cells != 0);
 }
 
 }  // namespace
@@ -90,15 +95,16 @@ void launch_lists(const Launch &L, int mode, hipStream_t stream)
         k_fill<<<1, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, LISTS_PLAN, 0);
         return;
     }
+    const int nf = pad8(L.b.nchunk);
     if (mode == LISTS_REFILL) {
-        k_fill<<<nb, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, LISTS_REFILL, 0);
+        k_fill<<<nf, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, LISTS_REFILL, 0);
         return;
     }
     k_assign<<<nb, kBlock, 0, stream>>>(L.b, L.reps, L.s, L.l, L.budget, mode);
-    const int nbn = L.b.nchunk * (kChunk / kNbrPer);
+    const int nbn = pad8(L.b.nchunk * (kChunk / kNbrPer));
     if (L.b.dim == 3) k_nbr<3><<<nbn, 64, 0, stream>>>(L.b, L.reps, L.s, L.l, L.budget, mode);
     else k_nbr<2><<<nbn, 64, 0, stream>>>(L.b, L.reps, L.s, L.l, L.budget, mode);
-    k_fill<<<nb, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, mode, 1);
+    k_fill<<<nf, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, mode, 1);
 }
 
 }  // namespace dem

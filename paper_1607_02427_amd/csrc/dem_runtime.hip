@@ -905,7 +905,7 @@ dem_status alloc_core(dem_system *h, int Ncap, int Ccap, int Scap, int Rcap)
               hipMalloc(&h->lst.xlast, sizeof(double) * 3 * N) == hipSuccess &&
               hipMalloc(&h->lst.klo, sizeof(int32_t) * N) == hipSuccess &&
               hipMalloc(&h->lst.pstart, sizeof(int32_t) * N) == hipSuccess &&
-              hipMalloc(&h->lst.ptot, sizeof(int32_t) * (N / lb_rows_per_group + 1)) == hipSuccess &&
+              hipMalloc(&h->lst.ctot, sizeof(int32_t) * (N / kChunk + 1)) == hipSuccess &&
               hipMalloc(&h->rot, partrec_bytes(h->precision) * N) == hipSuccess &&
               (h->precision != DEM_FP32 || hipMalloc(&h->rec64, sizeof(PartRec64) * N) == hipSuccess);
     if (!ok) return fail(h, DEM_E_OOM, "device allocation failed");
@@ -939,7 +939,7 @@ dem_status alloc_core(dem_system *h, int Ncap, int Ccap, int Scap, int Rcap)
     HIPCHK(h, hipMemsetAsync(h->lst.n_nbr, 0, sizeof(int32_t) * N, h->stream));
     HIPCHK(h, hipMemsetAsync(h->lst.klo, 0, sizeof(int32_t) * N, h->stream));
     HIPCHK(h, hipMemsetAsync(h->lst.pstart, 0, sizeof(int32_t) * N, h->stream));
-    HIPCHK(h, hipMemsetAsync(h->lst.ptot, 0, sizeof(int32_t) * (N / lb_rows_per_group + 1), h->stream));
+    HIPCHK(h, hipMemsetAsync(h->lst.ctot, 0, sizeof(int32_t) * (N / kChunk + 1), h->stream));
     HIPCHK(h, hipMemsetAsync(h->lst.pcell, 0, sizeof(int32_t) * N, h->stream));
     HIPCHK(h, hipMemsetAsync(h->stats, 0, kStatBytes, h->stream));
     HIPCHK(h, hipMemsetAsync(h->ke_part, 0, sizeof(double) * (kKePer + 1) * nch, h->stream));
@@ -954,7 +954,7 @@ void free_all(dem_system *h)
     void *ptrs[] = {h->d_reps, h->d_chunk_rep, h->tab64, h->tab32, h->fcells, h->ke_part, h->e_part, h->thermo, h->budget,
                     h->steps, h->stats, h->lst.flags, h->lst.gflags, h->lst.tile_start, h->lst.ccount, h->lst.cell_count,
                     h->lst.cell_slot, h->lst.pcell, h->lst.n_nbr, h->lst.xlast, h->lst.klo,
-                    h->lst.pstart, h->lst.ptot, h->lst.nbr, h->lst.pairs, h->lst.cpairs, h->lst.smask, h->rot, h->rec,
+                    h->lst.pstart, h->lst.ctot, h->lst.nbr, h->lst.pairs, h->lst.cpairs, h->lst.smask, h->rot, h->rec,
                     h->rec64};
     for (void *p : ptrs) (void)hipFree(p);
     if (h->batch) {
