@@ -893,6 +893,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     // results of one pooled solve step, one per lane
     constexpr bool kPool = pooled(DIM, GL);
     constexpr int kRes = pool_results<T>(GL, SL);
+    constexpr bool kSeq = GL == 16;  // the prefilter takes both bodies' vertices (faces) in one sequence
     Acc<T> *pres = reinterpret_cast<Acc<T> *>(qall + kWaves * kEnt);
     // the feature-cell form's per-group prefix and edge masks
     PairFc *pfc = reinterpret_cast<PairFc *>(reinterpret_cast<unsigned char *>(pres) +
@@ -1046,83 +1047,82 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             int fc_total = 0;
             PairFc &Fc = pfc[FC ? wid * kGroups + grp : 0];
             const T thr = rcm + T(1e-5) * (Bi + Bj);
-            for (int v0 = 0; v0 < DEM_MAX_VERTS; v0 += kGL) {
-                const int vk = v0 + sub;
-                bool nj = false, ni = false;
-                if (live && vk < Sj.nv) {
-                    const V3<T> v = t + mul(Rr, xyz(Sj.v[vk]));
-                    unsigned mb = 0;
+            // What bounds it is the chain of LDS reads and dependent terms of
+            // each pass.  With 16 lanes, both bodies' vertices, and both
+            // bodies' faces, are taken in one sequence (kSeq), so that a pass
+            // has few idle lanes: of two cubes, 16 vertices and 12 faces each
+            // fill one pass (216 cubes 12.8 us against 13.5, 1000 tetrahedra
+            // 14.5 against 15.1).  Edges, of which bodies have more than 8,
+            // and 8 lanes per pair take a pass of each body at once, whose
+            // chains overlap (262,144 octahedra 338 us against 354 in one
+            // sequence).
+            auto vertex = [&](bool has, bool of_j, int vk) {
+                if (!has) return false;
+                const ShapeTab<T> &A = of_j ? Sj : Si;
+                const ShapeTab<T> &B = of_j ? Si : Sj;
+                const V3<T> u = xyz(A.v[vk]);
+                const V3<T> vj = t + mul(Rr, u), vi = mulT(Rr, u - t);
+                const V3<T> v = v3<T>(of_j ? vj.x : vi.x, of_j ? vj.y : vi.y, of_j ? vj.z : vi.z);
+                const T lim = of_j ? Bi : Bj;
+                const int nsep = B.nsep;
+                unsigned mb = 0;
 #pragma unroll 4
-                    for (int p = 0; p < Si.nsep; ++p) mb |= (plane_gap(Si.sp[p], v) > thr ? 1u : 0u) << p;
-                    Vec4<T> v4 = {v.x, v.y, v.z, T(0)};
-                    set_plane_bits(v4.w, mb);
-                    W.vj[vk] = v4;
-                    nj = mb == 0 && dot(v, v) < grow * Bi * Bi;
-                }
-                if (live && vk < Si.nv) {
-                    const V3<T> v = mulT(Rr, xyz(Si.v[vk]) - t);
-                    unsigned mb = 0;
+                for (int p = 0; p < nsep; ++p) mb |= (plane_gap(B.sp[p], v) > thr ? 1u : 0u) << p;
+                Vec4<T> v4 = {v.x, v.y, v.z, T(0)};
+                set_plane_bits(v4.w, mb);
+                (of_j ? W.vj : W.vi)[vk] = v4;
+                return mb == 0 && dot(v, v) < grow * lim * lim;
+            };
+            auto edge = [&](bool has, bool of_i, int e) {
+                if (!has) return false;
+                const ShapeTab<T> &A = of_i ? Si : Sj;
+                const Vec4<T> *vs = of_i ? W.vi : W.vj;
+                const Vec4<T> em = A.em[e], a = vs[A.e[e][0]], b = vs[A.e[e][1]];
+                const V3<T> di = xyz(em) - t, dj = T(0.5) * (xyz(a) + xyz(b));
+                const V3<T> d = v3<T>(of_i ? di.x : dj.x, of_i ? di.y : dj.y, of_i ? di.z : dj.z);
+                const T lim = (of_i ? Bj : Bi) + em.w;
+                return (plane_bits(a.w) & plane_bits(b.w)) == 0 && dot(d, d) < grow * lim * lim;
+            };
+            const V3<T> ti = DIM == 3 ? -(T)1 * mulT(Rr, t) : t;  // i's centre in j's frame
+            auto face = [&](bool has, bool of_i, int f) {
+                if (!has) return false;
+                const ShapeTab<T> &A = of_i ? Si : Sj;
+                const Vec4<T> *vs = of_i ? W.vi : W.vj;
+                const Vec4<T> fc = A.fc[f];
+                const V3<T> d = v3<T>(fc.x - (of_i ? t.x : ti.x), fc.y - (of_i ? t.y : ti.y), fc.z - (of_i ? t.z : ti.z));
+                const T lim = (of_i ? Bj : Bi) + fc.w;
+                const int fi = A.fi[f];
+                unsigned all = ~0u;
 #pragma unroll 4
-                    for (int p = 0; p < Sj.nsep; ++p) mb |= (plane_gap(Sj.sp[p], v) > thr ? 1u : 0u) << p;
-                    Vec4<T> v4 = {v.x, v.y, v.z, T(0)};
-                    set_plane_bits(v4.w, mb);
-                    W.vi[vk] = v4;
-                    ni = mb == 0 && dot(v, v) < grow * Bj * Bj;
+                for (int k = face_first(fi); k < face_end(fi); ++k) all &= plane_bits(vs[A.floop[k]].w);
+                return all == 0 && dot(d, d) < grow * lim * lim;
+            };
+            // na features of the first body and nb of the second: near ones
+            // listed by index
+            auto list = [&](auto one, auto near, int na, int nb, int most, unsigned char *la, unsigned char *lb, int &ca, int &cb) {
+                constexpr bool seq = decltype(one)::value;
+                for (int x0 = 0; x0 < (seq ? 2 : 1) * most; x0 += kGL) {
+                    const int x = x0 + sub;
+                    if constexpr (seq) {
+                        const bool first = x < na;
+                        const int k = first ? x : x - na;
+                        const bool hit = near(live && x < na + nb, first, k);
+                        ca = group_append(hit && first, la, ca, k, gmask);
+                        cb = group_append(hit && !first, lb, cb, k, gmask);
+                        if (__ballot(live && x0 + kGL < na + nb) == 0) break;
+                    } else {
+                        const bool ha = near(live && x < na, true, x), hb = near(live && x < nb, false, x);
+                        ca = group_append(ha, la, ca, x, gmask);
+                        cb = group_append(hb, lb, cb, x, gmask);
+                        if (__ballot(live && (x0 + kGL < na || x0 + kGL < nb)) == 0) break;
+                    }
                 }
-                cvj = group_append(nj, W.vj_near, cvj, vk, gmask);
-                cvi = group_append(ni, W.vi_near, cvi, vk, gmask);
-                if (__ballot(live && (v0 + kGL < Si.nv || v0 + kGL < Sj.nv)) == 0) break;
-            }
+            };
+            list(std::integral_constant<bool, kSeq>(), vertex, Sj.nv, Si.nv, DEM_MAX_VERTS, W.vj_near, W.vi_near, cvj, cvi);
             wave_sync_lds();
-            for (int e0 = 0; e0 < DEM_MAX_EDGES; e0 += kGL) {
-                const int e = e0 + sub;
-                bool ne = false, me = false;
-                if (live && e < Si.ne) {
-                    const Vec4<T> em = Si.em[e];
-                    const V3<T> d = xyz(em) - t;
-                    const T lim = Bj + em.w;
-                    ne = (plane_bits(W.vi[Si.e[e][0]].w) & plane_bits(W.vi[Si.e[e][1]].w)) == 0 && dot(d, d) < grow * lim * lim;
-                }
-                if (live && e < Sj.ne) {
-                    const Vec4<T> a = W.vj[Sj.e[e][0]], b = W.vj[Sj.e[e][1]];
-                    const V3<T> m = T(0.5) * (xyz(a) + xyz(b));
-                    const T lim = Bi + Sj.em[e].w;
-                    me = (plane_bits(a.w) & plane_bits(b.w)) == 0 && dot(m, m) < grow * lim * lim;
-                }
-                cei = group_append(ne, W.ei_near, cei, e, gmask);
-                cej = group_append(me, W.ej_near, cej, e, gmask);
-                if (__ballot(live && (e0 + kGL < Si.ne || e0 + kGL < Sj.ne)) == 0) break;
-            }
-            if (DIM == 3) {
-                const V3<T> ti = -(T)1 * mulT(Rr, t);  // i's centre in j's frame
-                for (int f0 = 0; f0 < DEM_MAX_FACES; f0 += kGL) {
-                    const int f = f0 + sub;
-                    bool nf = false, mf = false;
-                    if (live && f < Si.nf) {
-                        const Vec4<T> fc = Si.fc[f];
-                        const V3<T> d = xyz(fc) - t;
-                        const T lim = Bj + fc.w;
-                        const int fi = Si.fi[f];
-                        unsigned all = ~0u;
-#pragma unroll 4
-                        for (int k = face_first(fi); k < face_end(fi); ++k) all &= plane_bits(W.vi[Si.floop[k]].w);
-                        nf = all == 0 && dot(d, d) < grow * lim * lim;
-                    }
-                    if (live && f < Sj.nf) {
-                        const Vec4<T> fc = Sj.fc[f];
-                        const V3<T> d = xyz(fc) - ti;
-                        const T lim = Bi + fc.w;
-                        const int fi = Sj.fi[f];
-                        unsigned all = ~0u;
-#pragma unroll 4
-                        for (int k = face_first(fi); k < face_end(fi); ++k) all &= plane_bits(W.vj[Sj.floop[k]].w);
-                        mf = all == 0 && dot(d, d) < grow * lim * lim;
-                    }
-                    cfi = group_append(nf, W.fi_near, cfi, f, gmask);
-                    cfj = group_append(mf, W.fj_near, cfj, f, gmask);
-                    if (__ballot(live && (f0 + kGL < Si.nf || f0 + kGL < Sj.nf)) == 0) break;
-                }
-            }
+            list(std::false_type(), edge, Si.ne, Sj.ne, DEM_MAX_EDGES, W.ei_near, W.ej_near, cei, cej);
+            if (DIM == 3)
+                list(std::integral_constant<bool, kSeq>(), face, Si.nf, Sj.nf, DEM_MAX_FACES, W.fi_near, W.fj_near, cfi, cfj);
             wave_sync_lds();
             if constexpr (FC) {
                 // Shape-local feature cells narrow the near sets per feature:
