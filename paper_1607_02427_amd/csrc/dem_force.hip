@@ -1575,7 +1575,9 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                 // bit p of bi (bj): every vertex of j (i) this lane holds lies
                 // more than thr beyond supporting plane p of i (j); no early exit
                 // and one group reduction at the end, so the plane loads of
-                // successive planes overlap.  VP vertices of each body per lane,
+                // successive planes overlap, and one loop for both bodies, so
+                // theirs do (1000 tetrahedra 14.0 us, one body after the other
+                // 14.5).  VP vertices of each body per lane,
                 // as few as the replica's shapes need: with VP for
                 // DEM_MAX_VERTS throughout, half of the plane tests of bodies
                 // with 8 vertices or fewer were made on empty slots.
@@ -1594,26 +1596,18 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
                     }
                     const int nsi = live ? Si.nsep : 0, nsj = live ? Sj.nsep : 0;
 #pragma unroll 2
-                    for (int p = 0; p < nsi; ++p) {
-                        const Vec4<T> pl = Si.sp[p];
-                        bool all = true;
+                    for (int p = 0; p < (nsi > nsj ? nsi : nsj); ++p) {
+                        const bool oi = p < nsi, oj = p < nsj;
+                        const Vec4<T> pi = Si.sp[oi ? p : 0], pj = Sj.sp[oj ? p : 0];
+                        bool ai = oi, aj = oj;
 #pragma unroll
                         for (int v = 0; v < VP; ++v) {
-                            all &= !hj[v] || plane_gap(pl, wj[v]) > thr;
-                            c_pv.add(hj[v] ? 1 : 0);
+                            ai &= !hj[v] || plane_gap(pi, wj[v]) > thr;
+                            aj &= !hi[v] || plane_gap(pj, wi[v]) > thr;
+                            c_pv.add((oi && hj[v] ? 1 : 0) + (oj && hi[v] ? 1 : 0));
                         }
-                        bi |= (all ? 1u : 0u) << p;
-                    }
-#pragma unroll 2
-                    for (int p = 0; p < nsj; ++p) {
-                        const Vec4<T> pl = Sj.sp[p];
-                        bool all = true;
-#pragma unroll
-                        for (int v = 0; v < VP; ++v) {
-                            all &= !hi[v] || plane_gap(pl, wi[v]) > thr;
-                            c_pv.add(hi[v] ? 1 : 0);
-                        }
-                        bj |= (all ? 1u : 0u) << p;
+                        bi |= (ai ? 1u : 0u) << p;
+                        bj |= (aj ? 1u : 0u) << p;
                     }
                 };
                 if (kSepLanes == 4 && rl.wide == 0.0) planes(std::integral_constant<int, kSepLanes == 4 ? 2 : 1>());
