@@ -664,35 +664,37 @@ int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 // from the pair slots of its live replicas and their shapes.
 //  * Few slots: 16 lanes in both stages, a tile of 16 pairs, so that a
 //    wavefront holds few of the long feature chains that set a small
-//    system's time (216 cubes 14.6 us against 17.4 with 8 lanes and 20.7
-//    with 16 lanes and tiles of 64; 2000 cubes, 36,864 slots, 16.4 against
-//    17.0; 4096 cubes, 73,728 slots, 23.9 against 17.8).  In FP64 the lines
-//    cross earlier (2000 cubes 18.1 against 17.5).
+//    system's time (216 cubes 12.6 us against 15.9 with 8 lanes and 19.3
+//    with 16 lanes and tiles of 64; 2000 cubes, 36,864 slots, 15.0 against
+//    15.7; 3000 cubes, 54,144 slots, 19.4 against 16.7).  In FP64 the lines
+//    cross earlier (1000 cubes, 18,432 slots, 13.9 against 15.0; 2000 cubes
+//    21.8 against 14.8).
 //  * Otherwise 8 lanes, whose rounds share their culls and solves over twice
-//    as many pairs (4096 cubes 17.8 us against 21.7 with 16 lanes, 64,000
-//    cubes 76 against 95, 20,000 pentagons 16.1 against 24.5),
-//  * but 16 for bodies whose features take 8 lanes many passes: more than 24
-//    edges (9001 icosahedra 26.3 against 27.9), and in FP64 more than 8
-//    vertices (5003 L-prisms on a contact lattice 69 against 96; as a fluid
-//    of 4096 they would gain from 8 lanes, 22.5 against 26.9).
+//    as many pairs (4096 cubes 17.5 us against 19.8 with 16 lanes, 20,000
+//    pentagons 14.2 against 18.6),
+//  * but 16 where bodies whose features take 8 lanes many passes hold most
+//    of the slots: in FP64 those of more than 8 vertices (5003 L-prisms on a
+//    contact lattice 67 against 92) or of more than 24 edges (9001 icosahedra
+//    31.8 against 33.5), in FP32 those of more than 24 edges (26.6 against
+//    32.4 soon after the start; once mixed 27.8 against 26.5).
+//    A batch of which they hold a part gains from 8 (24 systems of cubes,
+//    tetrahedra and L-prisms in FP64, 201 against 225).
 void pick_shape(dem_system *h)
 {
     if (!h->pair_auto) return;
-    long long slots = 0;
-    bool wide = false, edged = false;
+    const bool f32 = h->precision == DEM_FP32;
+    long long slots = 0, many = 0;
     for (const Replica &R : h->reps) {
         if (!R.live) continue;
         slots += R.sp.pcap;
-        wide |= R.sp.wide != 0.0;
-        edged |= R.edges > 24;
+        if (R.edges > 24 || (R.sp.wide != 0.0 && !f32)) many += R.sp.pcap;
     }
-    const bool f32 = h->precision == DEM_FP32;
     const bool few = slots <= (f32 ? 40960 : 32768);
     h->pair_grid = 1;
     h->pair_waves = kDefaultPairWaves;
     h->pair_split = 0;
     h->pair_sep = few ? 16 : 4;
-    h->pair_lanes = few || edged || (wide && !f32) ? 16 : 8;
+    h->pair_lanes = few || 2 * many > slots ? 16 : 8;
 }
 
 // Whether the separation stage of a handle with four lanes per pair there
