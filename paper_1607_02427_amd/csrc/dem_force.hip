@@ -11,7 +11,8 @@
 //
 // Mapping to gfx950:
 //  1. k_pairs: each unordered pair of the half list once, in two stages.
-//     The separation stage (4 lanes per pair, 16 pairs per wavefront) loads
+//     The separation stage (4 lanes per pair, 16 in small systems, 1 in
+//     large ones) loads
 //     the pair, drops it beyond R_i + R_j + r_cut, and tests each body's
 //     vertices against the other's supporting planes; a pair separated by
 //     more than r_cut has no feature pair inside the cutoff.  The rest queue
@@ -23,16 +24,17 @@
 //     vertex-face; bounding spheres, then the distance of the two lines, for
 //     edge-edge; bounding spheres for vertex-edge), and the survivors are
 //     compacted into a per-pair LDS queue so the exact nearest-point and WCA
-//     work runs on dense lanes.  The group reduces force, both torques and
+//     work runs on dense lanes, those of the wavefront's other pairs
+//     included.  The group reduces force, both torques and
 //     energy in a fixed order; a pair with a feature pair inside the cutoff
 //     writes one record into each particle's row slot (FP32 records in FP32
 //     mode; every sum over pairs is FP64) and sets the slot's bit in the
 //     particle's written-slot mask.
 //  2. k_gather: each particle sums the records of its written slots in slot
 //     order (deterministic) into F, tau, U_i and W_i and clears its mask,
-//     optionally fused with the closing kick of the integrator;
-//     k_replica_tail then closes the step of each replica (thermostat half
-//     steps, budget, rebuilds).
+//     optionally fused with the closing kick of the integrator.  Where
+//     steps are not folded, k_replica_tail then closes the step of each
+//     replica (thermostat half steps, budget, rebuilds).
 // FP32 mode does the geometry in FP32 from FP64 pair offsets rounded once;
 // problems within 1% of the cutoff, segment pairs that are nearly parallel
 // (sin^2 < 1e-2) and terms whose force line passes close to a centre are

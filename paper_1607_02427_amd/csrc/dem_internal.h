@@ -25,7 +25,7 @@ constexpr int kChunk = 64;
 // straddle replicas.
 // The separation stage takes sep_lanes lanes per pair (4: 16 pairs per
 // wavefront; 16: 4 pairs per wavefront, which spreads a small system's
-// pairs over four times the wavefronts), so a tile is kPairWaves * 64 /
+// pairs over four times the wavefronts; 1: 64, see kLanePairSlots), so a tile is kPairWaves * 64 /
 // sep_lanes pairs.
 constexpr int kPairWaves = 4;
 constexpr int kDefaultPairLanes = 16;
