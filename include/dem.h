@@ -327,7 +327,8 @@ dem_status dem_tune_pairs(dem_handle h, int32_t reps, int32_t *shape, double *me
 /* Bytes of device memory the library would allocate for these parameters
  * (lists, cells, scratch), excluding caller-owned state and outputs.  For a
  * replica of a batch this is its share of the batch's arrays, less its state
- * and outputs (16 doubles and 4 ints per particle). */
+ * and outputs (16 doubles and 4 ints per particle).  The work counters (32 KB
+ * per handle) are not in it. */
 size_t dem_footprint_bytes(const dem_params *params);
 
 /* ---- Batches of independent replicas ------------------------------------

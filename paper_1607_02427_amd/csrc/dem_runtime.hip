@@ -125,6 +125,14 @@ namespace {
 std::string g_err;
 constexpr int64_t kUnbounded = (int64_t)1 << 62;
 constexpr size_t kStatBytes = sizeof(unsigned long long) * kStatBanks * kStatStride;
+// What a replica is charged besides what grows with its particles and cells:
+// its parameters and its share of the shape-table slots.  A figure of its
+// own rather than the structures' sizes, so that a batch of a given budget
+// takes the same replicas whatever their layout.  The handle's work counters
+// (kStatBytes) are held once, not by each replica, and not charged.
+constexpr size_t kReplicaFixedBytes = 79232;
+static_assert(sizeof(SysParams) + DEM_MAX_SHAPES * (sizeof(ShapeTab<double>) + sizeof(ShapeTab<float>)) <= kReplicaFixedBytes,
+              "a replica's fixed charge covers its parameters and shape tables");
 
 
 dem_status fail(dem_system *h, dem_status s, const char *fmt, ...)
@@ -1467,10 +1475,10 @@ size_t dem_footprint_bytes(const dem_params *p)
     const size_t maxp = n * (size_t)cap / 2;
     return sizeof(int32_t) * (n * (size_t)cap + 4 * n + ncell * (1 + kCellCap) + 8 * maxp + nch + 2 * FLAG_COUNT + G_COUNT + 2 +
                               split_words(1)) +
-           sizeof(double) * (3 * n + (kKePer + 13) * nch + TH_COUNT + 2) + kStatBytes +
+           sizeof(double) * (3 * n + (kKePer + 12) * nch + TH_COUNT + 2) +
            (partrec_bytes(p->precision) + (p->precision == DEM_FP32 ? sizeof(PartRec64) : 0)) * n +
            sizeof(uint2) * kFcCells * DEM_MAX_SHAPES +
-           rec_bytes(p->precision) * (size_t)cap * n + sizeof(uint32_t) * (size_t)slot_words(cap) * n + sizeof(SysParams) + 2 * DEM_MAX_SHAPES * sizeof(ShapeTab<double>) + 256;
+           rec_bytes(p->precision) * (size_t)cap * n + sizeof(uint32_t) * (size_t)slot_words(cap) * n + kReplicaFixedBytes;
 }
 
 dem_status dem_create_system(const dem_params *params, const dem_state_ptrs *state, const dem_output_ptrs *outputs,
