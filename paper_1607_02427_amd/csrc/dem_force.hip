@@ -1694,28 +1694,35 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     }
     if (COUNT && stats) {
         // The counters go to one of kStatBanks copies by workgroup, one line
-        // each, added up when they are read; the workgroup's wavefronts are
+        // each, added up when they are read; the workgroup's lanes are
         // summed in LDS first and a zero is not added.  One copy alone
         // serialised 8 atomics per wavefront on one line across the XCDs
         // (5003 FP64 L-prisms: 295 us per counted launch against 68
         // uncounted; 72 with the banks).
+        // in the order of Stat, ST_LAUNCHES left out
         const unsigned cnt[8] = {c_pairs.get(), c_feat.get(), c_in.get(), c_near.get(), c_ref.get(), c_ee.get(),
                                  c_sep.get(), c_pv.get()};
-        const int slot[8] = {ST_PAIRS, ST_FEATURES, ST_INCUT, ST_NEAR, ST_REFINED, ST_EENEAR, ST_SEPARATED, ST_PLANETESTS};
-        unsigned *sum = reinterpret_cast<unsigned *>(smem);  // the tables are done with
+        static_assert(ST_LAUNCHES == 3 && ST_PLANETESTS == 8, "counter k is word k, or k + 1 from ST_LAUNCHES on");
+        // A wavefront's sums take 32 bits: the 2^31 pairs a handle can hold are
+        // spread over 256 CUs of four wavefronts at least, and a pair of
+        // bodies of 16 vertices and 20 planes makes 640 plane tests, 1.3e9 a
+        // wavefront.  (A workgroup's could pass 2^32; adding 64-bit words per
+        // lane instead costs 2 us of 96 on those L-prisms.)
+        unsigned *sum = reinterpret_cast<unsigned *>(smem);  // the tables are done with; 8 words per wavefront
         __syncthreads();
-        if (threadIdx.x < 8) sum[threadIdx.x] = 0u;
+        if (threadIdx.x < 8 * kWaves) sum[threadIdx.x] = 0u;
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 8; ++k)
-            if (cnt[k] != 0u) atomicAdd(&sum[k], cnt[k]);
+            if (cnt[k] != 0u) atomicAdd(&sum[8 * wid + k], cnt[k]);
         __syncthreads();
         unsigned long long *bank = stats + (size_t)(blockIdx.x % kStatBanks) * kStatStride;
-        if (threadIdx.x == 0) {
+        if (threadIdx.x < 8) {
+            unsigned long long v = 0ull;
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (sum[k] != 0u) atomicAdd(&bank[slot[k]], (unsigned long long)sum[k]);
-            if (blockIdx.x == 0) atomicAdd(&bank[ST_LAUNCHES], 1ull);
+            for (int w = 0; w < kWaves; ++w) v += sum[8 * w + threadIdx.x];
+            if (v != 0ull) atomicAdd(&bank[threadIdx.x + (threadIdx.x >= ST_LAUNCHES ? 1 : 0)], v);
+            if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&bank[ST_LAUNCHES], 1ull);
         }
     }
 }
