@@ -25,12 +25,14 @@ constexpr int kCellQuads = kCellCap / 4;
 static_assert(kCellCap % 4 == 0 && kRowMax % 4 == 0 && kNb3 * kCellCap <= 65536, "quads of slots, in 16 bits");
 
 // LDS of an nbr_rows wavefront, per particle: its hits, its neighbour cells
-// and their occupied slots, four to an entry.
-struct RowBuf {
+// and their occupied slots, four to an entry.  Rows are read in 16-byte words.
+struct alignas(16) RowBuf {
     int row[kNbrPer][kRowMax];
     int cell[kNbrPer][kNb3];
     unsigned short quad[kNbrPer][kNb3 * kCellQuads];  // (cell * kCellQuads + quad) * 4 + slots in use - 1
 };
+static_assert(alignof(RowBuf) % 16 == 0 && offsetof(RowBuf, row) % 16 == 0 && sizeof(RowBuf::row[0]) % 16 == 0,
+              "every row starts on a 16-byte boundary, wherever the compiler puts the buffer");
 
 // Minimum image of d = x_j - x_i for positions in [0, L].  This equals
 // d - L rint(d / L) bit for bit except where |d| is within rounding of L/2,
