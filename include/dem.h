@@ -283,7 +283,8 @@ dem_status dem_time_forces(dem_handle h, int32_t reps, double *mean_ms);
  * buffer as large as the pair entries; a force kernel then gives each
  * wavefront one feature round of those pairs (lanes_per_pair applies to it;
  * grid_factor does not).  Until it is called (or dem_tune_pairs), the library
- * picks a shape by the number of pair slots and by the bodies' features.
+ * picks a shape by the number of pair slots and by the bodies' features;
+ * slots are counted at the automatic row capacity, whatever nbr_capacity is.
  * The next dem_step captures its graph again.
  * DEM_E_ARG for other values. */
 enum { DEM_PAIR_SHAPES = 16 };

@@ -32,7 +32,7 @@ constexpr int kDefaultPairLanes = 16;
 constexpr int kDefaultPairWaves = 2;
 constexpr int kDefaultPairSep = 4;
 __host__ __device__ constexpr int pair_tile(int sep_lanes) { return kPairWaves * (64 / sep_lanes); }
-// From this many pair slots up, 3D systems with 8 lanes per pair and the
+// From this many pair slots up (counted at the automatic row capacity), 3D systems with 8 lanes per pair and the
 // 4-lane separation stage run that stage with one lane per pair instead (64
 // pairs per wavefront, 256 per tile): a quarter of its instructions, but
 // tiles four times as long, of which a workgroup has to have several for the

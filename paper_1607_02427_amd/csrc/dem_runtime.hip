@@ -74,6 +74,7 @@ struct Replica {
     int cell0 = 0, ncells = 0;
     int shape0 = 0, nshapes = 0;
     int edges = 0;               // of the shape that has the most
+    long long slots = 0;         // pair slots at the automatic row capacity, whatever the capacity in use
 };
 
 }  // namespace
@@ -700,7 +701,11 @@ Launch make_launch(const dem_system *h)
 int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 
 // The pair-kernel shape of a handle that nobody has set or tuned one for,
-// from the pair slots of its live replicas and their shapes.
+// from the pair slots of its live replicas and their shapes.  Slots are
+// counted at the automatic row capacity (Replica::slots: 0.9 of the pairs
+// that the density gives within the list radius, and 8 per body), for which
+// the limits were measured: a measure of the pairs that neither a caller's
+// nbr_capacity nor another replica's rows move.
 //  * Few slots: 16 lanes in both stages, a tile of 16 pairs, so that a
 //    wavefront holds few of the long feature chains that set a small
 //    system's time (216 cubes 12.6 us against 15.9 with 8 lanes and 19.3
@@ -725,8 +730,8 @@ void pick_shape(dem_system *h)
     long long slots = 0, many = 0;
     for (const Replica &R : h->reps) {
         if (!R.live) continue;
-        slots += R.sp.pcap;
-        if (R.edges > 24 || (R.sp.wide != 0.0 && !f32)) many += R.sp.pcap;
+        slots += R.slots;
+        if (R.edges > 24 || (R.sp.wide != 0.0 && !f32)) many += R.slots;
     }
     const bool few = slots <= (f32 ? 40960 : 32768);
     h->pair_grid = 1;
@@ -747,7 +752,7 @@ bool lane_per_pair(const dem_system *h)
     bool points = true;
     for (const Replica &R : h->reps) {
         if (!R.live) continue;
-        slots += R.sp.pcap;
+        slots += R.slots;
         points &= R.edges == 0;
     }
     return slots >= (points ? kLanePointSlots : kLanePairSlots);
@@ -1148,6 +1153,7 @@ dem_status describe_replica(dem_system *h, const dem_params &p, Replica &R, std:
     // r_list = 2 R_max + 2^(1/6) sigma_max + skin
     const double rl = 2.0 * Rmax + kWcaCut * (2.0 * rmax) + p.skin;
     R.r_list = rl;
+    R.slots = (p.n + kChunk - 1) / kChunk * kChunk * auto_capacity(p, rl) / 2;
     sp.n = (int)p.n;
     sp.dim = p.dim;
     sp.n_shapes = p.n_shapes;
@@ -1467,6 +1473,15 @@ dem_status run_steps(dem_system *h, int64_t n_steps)
 }  // namespace
 
 extern "C" {
+
+// The pair-kernel shape in use: {lanes, grid factor, waves, separation lanes,
+// split}, with 1 separation lane where a lane takes a whole pair.  For the
+// tests; not part of the ABI.
+void dem_pair_shape_in_use(dem_handle h, int32_t *shape)
+{
+    const int32_t now[5] = {h->bp.pair_lanes, h->pair_grid, h->pair_waves, h->bp.pair_sep, h->bp.pair_split};
+    std::copy(now, now + 5, shape);
+}
 
 const char *dem_status_string(dem_status s)
 {
