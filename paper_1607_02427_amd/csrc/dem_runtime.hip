@@ -716,13 +716,25 @@ int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 //  * Otherwise 8 lanes, whose rounds share their culls and solves over twice
 //    as many pairs (4096 cubes 17.5 us against 19.8 with 16 lanes, 20,000
 //    pentagons 14.2 against 18.6),
-//  * but 16 where bodies whose features take 8 lanes many passes hold most
-//    of the slots: in FP64 those of more than 8 vertices (5003 L-prisms on a
-//    contact lattice 67 against 92) or of more than 24 edges (9001 icosahedra
-//    31.8 against 33.5), in FP32 those of more than 24 edges (26.6 against
-//    32.4 soon after the start; once mixed 27.8 against 26.5).
-//    A batch of which they hold a part gains from 8 (24 systems of cubes,
-//    tetrahedra and L-prisms in FP64, 201 against 225).
+//  * but 16 where polyhedra whose features take 8 lanes many passes hold most
+//    of the slots: in FP64 those of more than 8 vertices or 24 edges, in FP32
+//    those of more than 24 edges.  Which is faster goes with the contacts per
+//    body: with many (a dense or near-lattice state, whose pairs have tens
+//    of problems) 16, with few (a dilute fluid, a handful) 8; the lines
+//    lie where 16 costs less in the one than it gains in the other.  Step
+//    times with 16 lanes over those with 8, the range of five windows of the
+//    first 8000 steps and of 3000 to 20,000 bodies, from a lattice gas of
+//    volume fraction 0.35 to 0.4, and from a contact lattice: FP32
+//    icosahedra 0.94-1.03 and 0.87-1.05, 14- and 16-vertex antiprisms
+//    0.89-1.03 and 0.77-0.90; FP64 L-prisms 0.91-1.14 and 0.70-1.13, hexagonal
+//    and octagonal prisms 0.98-1.10 and 0.73-0.84, icosahedra 0.97-1.03 and
+//    0.66-1.06.  Of fewer features the gas loses more than the lattice gains:
+//    FP32 hexagonal and octagonal prisms 0.97-1.10 and 0.87-0.92, L-prisms
+//    1.05-1.09 and 0.92-1.05.  Polygons are with 8 lanes throughout (squares
+//    to 16-gons in both precisions 0.94-1.14 and 1.09-1.43: planar pairs have
+//    few problems).
+//    A batch of which such bodies hold a part gains from 8 (24 systems of
+//    cubes, tetrahedra and L-prisms in FP64, 201 us against 225).
 void pick_shape(dem_system *h)
 {
     if (!h->pair_auto) return;
@@ -731,7 +743,7 @@ void pick_shape(dem_system *h)
     for (const Replica &R : h->reps) {
         if (!R.live) continue;
         slots += R.slots;
-        if (R.edges > 24 || (R.sp.wide != 0.0 && !f32)) many += R.slots;
+        if (h->dim == 3 && (R.edges > 24 || (R.sp.wide != 0.0 && !f32))) many += R.slots;
     }
     const bool few = slots <= (f32 ? 40960 : 32768);
     h->pair_grid = 1;

@@ -39,7 +39,9 @@ def _slots(n, cap):
     (lambda: I.lprism(), 900, "fp64", True, (16, 16)), (lambda: I.lprism(), 1500, "fp64", False, (16, 4)),
     (lambda: I.lprism(), 2500, "fp32", False, (8, 4)),
     (lambda: I.icosahedron(), 2000, "fp32", True, (16, 16)), (lambda: I.icosahedron(), 4000, "fp32", False, (16, 4)),
-    (lambda: I.square(), 1500, "fp32", True, (16, 16)), (lambda: I.square(), 4500, "fp64", False, (8, 4))])
+    (lambda: I.square(), 1500, "fp32", True, (16, 16)), (lambda: I.square(), 4500, "fp64", False, (8, 4)),
+    (lambda: I.hexadecagon(), 4500, "fp64", False, (8, 4)), (lambda: I.hexadecagon(), 4500, "fp32", False, (8, 4)),
+    (lambda: I.regular_polygon(9, 0.6), 4500, "fp64", False, (8, 4))])
 def test_either_side_of_a_limit(make, n, precision, few, want):
     from paper_1607_02427_amd import dem
     s = _gas(make(), n)
