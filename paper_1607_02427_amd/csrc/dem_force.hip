@@ -2105,10 +2105,14 @@ __global__ void k_rotations(BatchParams b, const SysParams *reps, StatePtrs s, L
     if (r < 0 || i >= reps[r].off + reps[r].n) return;
     double R[9];
     quat_to_rot(s.qw[i], s.qx[i], s.qy[i], s.qz[i], R);
+    // the pair kernel's minimum image reaches one box: a position that the
+    // caller has left outside the box is taken as its image inside
+    const double *box = reps[r].box;
+    auto inside = [](double x, double L) { return x >= 0.0 && x <= L ? x : x - L * floor(x / L); };
     PartRec<T> rc;
-    rc.x = s.x[i];
-    rc.y = s.y[i];
-    rc.z = b.dim == 3 ? s.z[i] : 0.0;
+    rc.x = inside(s.x[i], box[0]);
+    rc.y = inside(s.y[i], box[1]);
+    rc.z = b.dim == 3 ? inside(s.z[i], box[2]) : 0.0;
     for (int k = 0; k < 9; ++k) rc.R[k] = (T)R[k];
     rc.sid = s.sid[i];
     rot[i] = rc;
