@@ -252,7 +252,7 @@ dem_status dem_force_stats(dem_handle h, int64_t *out, int32_t reset);
 
 /* Enables (on != 0) or disables the work counters inside dem_step's
  * captured step (dem_compute_forces always counts).  Counting adds a few
- * atomics per wave; the arithmetic and results are unchanged. */
+ * atomics per workgroup; the arithmetic and results are unchanged. */
 dem_status dem_set_counting(dem_handle h, int32_t on);
 
 /* Launches the force kernel alone `reps` times on the current state (no
@@ -336,11 +336,10 @@ size_t dem_footprint_bytes(const dem_params *params);
  * A batch handle holds many independent periodic systems ("replicas") of
  * one dimension and one force precision, of any sizes and shapes, and
  * advances all of them with one launch per kernel per step: the pair
- * kernel walks one list of tiles (64 particle pairs of one replica each)
- * over every replica, the list build runs one workgroup per replica, and
- * the integrator and force gather cover every replica's particles.  A
- * replica's arithmetic does not depend on which other replicas share the
- * batch: its results are the same bit for bit alone, in any mix, and as a
+ * kernel walks one list of tiles (16 to 256 particle pairs of one replica
+ * each) over every replica, and the list builds, the integrator and the force
+ * gather cover every replica's particles.  A replica's arithmetic does not
+ * depend on which other replicas share the batch: its results are the same bit for bit alone, in any mix, and as a
  * single system (dem_create_system).  Replicas may be added and removed
  * between calls; each keeps its state in the batch's own device arrays.
  * The batch calls below are asynchronous on the batch's stream unless

@@ -16,7 +16,7 @@
 //     the pair, drops it beyond R_i + R_j + r_cut, and tests each body's
 //     vertices against the other's supporting planes; a pair separated by
 //     more than r_cut has no feature pair inside the cutoff.  The rest queue
-//     in LDS for the feature stage (8 or 16 lanes per pair, a tuning knob):
+//     in LDS for the feature stage (8 or 16 lanes per pair):
 //     a per-feature prefilter keeps only vertices, edges and faces within
 //     reach of the other body and not wholly beyond one of its supporting
 //     planes, every remaining feature pair of Eq. 1/2 gets a cheap
@@ -821,9 +821,9 @@ __host__ __device__ constexpr int pool_results(int lanes, int sep)
     return lanes == 8 && (sizeof(T) == 8 || sep == 1) ? 32 : 64;
 }
 
-// One block of 4 waves takes a contiguous range of tiles (64 or 16 pairs
-// of one replica each; wave w takes pairs (64 / SL) w .. (64 / SL)(w + 1)
-// - 1 of a tile in the first stage).
+// One block of 4 waves takes a contiguous range of tiles (256 / SL pairs of
+// one replica each, 16, 64 or 256; wave w takes pairs (64 / SL) w .. (64 /
+// SL)(w + 1) - 1 of a tile in the first stage).
 // Blocks are dealt round-robin to the 8 XCDs, so block b runs on XCD b % 8:
 // XCD x gets the x-th eighth of the tiles, and pairs of neighbouring
 // particles share its L2.  The tables of the block's current replica live
@@ -834,7 +834,7 @@ __host__ __device__ constexpr int pool_results(int lanes, int sep)
 // when every vertex of one body lies more than r_cut beyond a supporting
 // plane of the other, the two inner bodies are farther apart than r_cut, no
 // feature pair of Eq. 1/2 is inside the cutoff, and the pair's record is
-// zero (4 lanes per pair, 16 pairs per wavefront).  The other live pairs
+// zero (SL lanes per pair, 64 / SL pairs per wavefront).  The other live pairs
 // wait in the wave's LDS queue; whenever it holds one for each group of the
 // second stage (GL lanes per pair; or the range or the replica ends) that
 // stage runs the feature prefilter, the per-problem cull and the exact
@@ -853,11 +853,12 @@ struct Tally<false> {
     __device__ unsigned get() const { return 0; }
 };
 
-// OCC wavefronts per SIMD (2 or 3, a tuning knob): the kernel is
-// latency-bound, so more resident waves overlap more round trips, but at 3
-// the compiler must fit 168 registers and schedules with less freedom.  The
-// uncounted variants fit without spilling because the feature stage reads
-// the pair's transform from the LDS queue instead of holding it.
+// OCC wavefronts per SIMD, one build for each precision and form
+// (pair_occ): the kernel is latency-bound, so more resident waves overlap
+// more round trips, as many as the registers (168 at 3) and a workgroup's
+// LDS allow.  The uncounted variants fit without spilling because the
+// feature stage reads the pair's transform from LDS (the queue where pairs
+// wait with it, parked(), else the group's own slot) instead of holding it.
 template <typename T, int DIM, int GL, bool COUNT, int OCC, int SL, int STAGE, bool FC>
 __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const SysParams *__restrict__ reps, StatePtrs s,
                                                           ListPtrs l, const PartRec<T> *__restrict__ prec,
@@ -1460,7 +1461,7 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
             ++tt;
             continue;
         }
-        // ---- first stage on tile tt: 4 lanes per pair ----
+        // ---- first stage on tile tt: SL lanes per pair ----
         // (lane indices formed here, not held across the feature stage: an
         // empty asm keeps the compiler from hoisting them out of the loop)
         int lane1 = lane;
@@ -1740,9 +1741,15 @@ __device__ inline void body_torque(const double q[4], double tx, double ty, doub
 // closing kick.  One block per chunk, so a block belongs to one replica.
 // Each particle's row is split over kGatherLanes lanes (lane l takes slots
 // l, l + kGatherLanes, ... in order) and combined by a fixed butterfly, so
-// the result does not depend on scheduling.  With the kick and NVT each
-// block writes its chunk's kinetic partials for k_replica_tail.  A replica
-// with no budget left is skipped.
+// the result does not depend on scheduling.  With the kick and a thermostat
+// each block writes its chunk's kinetic partials, for the next kick-drift
+// (folded steps) or k_replica_tail.  A replica with no budget left is
+// skipped.  The kick's form carries the row workgroups and the step's words,
+// and so takes 171 registers in FP32 and 181 in FP64 (3D): two wavefronts per
+// SIMD.  Built for three it spills 20 and 68 bytes a lane, which is faster
+// only where two leave a second round short, and in FP32 alone (160,000
+// spheres 52.4 -> 51.6 us a step; 64,000 28.5 -> 29.0, 160,000 in FP64 58.0 ->
+// 59.6; 262,144 octahedra 445 -> 452).
 // written row slots a lane loads together in the gather (a record is 48
 // bytes in FP32, 96 in FP64; about a quarter of a row's slots are written)
 template <typename T>
@@ -1778,12 +1785,12 @@ inline int row_workgroups(const BatchParams &b) { return pad8(std::min(b.nchunk 
 // replica-dependent workgroup so that small replicas spread out too.
 template <int DIM>
 __device__ void step_rows(const BatchParams &b, const SysParams *reps, const StatePtrs &s, const ListPtrs &l,
-                          const int64_t *budget, lb::RowBuf &buf, int first)
+                          lb::RowBuf &buf, int first)
 {
     const int nrole = (int)gridDim.x - first, me = xcd_block((int)blockIdx.x - first, nrole);
     for (int r0 = 0; r0 < b.nrep; r0 += 64) {
         const int rl = r0 + (int)__lane_id();
-        const bool bld = rl < b.nrep && lb::building(LISTS_STEP, rl, reps[rl], l.flags + rl * FLAG_COUNT, budget);
+        const bool bld = rl < b.nrep && lb::building(LISTS_STEP, rl, reps[rl], l.flags + rl * FLAG_COUNT);
         for (unsigned long long m = __ballot(bld); m != 0ull; m &= m - 1ull) {
             const int r = r0 + __builtin_ctzll(m);
             const SysParams &p = reps[r];
@@ -1822,7 +1829,7 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather(BatchParams b, const Sy
     const int G = KICK ? pad8(b.nchunk) : (int)gridDim.x;  // chunk workgroups
     if (KICK && (int)blockIdx.x >= G) {
         __shared__ lb::RowBuf rbuf;
-        if (l.gflags[G_NOW] != 0) step_rows<DIM>(b, reps, s, l, budget, rbuf, G);
+        if (l.gflags[G_NOW] != 0) step_rows<DIM>(b, reps, s, l, rbuf, G);
         return;
     }
     constexpr int kB = gather_batch<T>();

@@ -18,15 +18,13 @@ constexpr double kWcaCut = 1.122462048309373;
 // boundary, so a wavefront's particles (and a gather block's) belong to one
 // replica, and per-chunk partial sums do not depend on the other replicas.
 constexpr int kChunk = 64;
-// The pair kernel: kPairWaves waves per workgroup; its separation stage
-// takes 4 lanes per particle pair and its feature stage 8 or 16
-// (BatchParams::pair_lanes, chosen by the pair-shape tuner).  A tile is what
-// one workgroup takes at a time (16 pairs per wavefront), and tiles never
-// straddle replicas.
-// The separation stage takes sep_lanes lanes per pair (4: 16 pairs per
-// wavefront; 16: 4 pairs per wavefront, which spreads a small system's
-// pairs over four times the wavefronts; 1: 64, see kLanePairSlots), so a tile is kPairWaves * 64 /
-// sep_lanes pairs.
+// The pair kernel: kPairWaves waves per workgroup; its feature stage takes 8
+// or 16 lanes per particle pair (BatchParams::pair_lanes, by the library's
+// rule, the caller or the pair-shape tuner).  Its separation stage takes
+// sep_lanes (4: 16 pairs per wavefront; 16: 4 pairs per wavefront, which
+// spreads a small system's pairs over four times the wavefronts; 1: 64, see
+// kLanePairSlots).  A tile is what one workgroup takes at a time, kPairWaves *
+// 64 / sep_lanes pairs, and tiles never straddle replicas.
 constexpr int kPairWaves = 4;
 constexpr int kDefaultPairLanes = 16;
 constexpr int kDefaultPairWaves = 2;
@@ -304,7 +302,6 @@ struct BatchParams {
     int tab_slots;               // shape tables of one replica staged in LDS
     int pair_blocks;             // grid of the pair kernel (a multiple of 8)
     int pair_lanes;              // lanes per particle pair in the pair kernel (8 or 16)
-    int pair_waves;              // its wavefronts per SIMD (2 or 3)
     int pair_sep;                // lanes per pair in its separation stage (1, 4 or 16)
     int tile;                    // pairs per tile: pair_tile(pair_sep)
     int pair_split;              // 1: two kernels, contact search then contact forces
@@ -403,9 +400,7 @@ struct ForcePtrs {
 };
 
 // ---- launchers (all asynchronous on `stream`) ----
-// `reps` is the device array of replica parameters; `host` the host copy of
-// replica 0, used only by the one-kernel-per-phase list build of a single
-// large system.
+// `reps` is the device array of replica parameters.
 struct Launch {
     BatchParams b;
     const SysParams *reps;
@@ -414,7 +409,7 @@ struct Launch {
     ListPtrs l;
     ForcePtrs f;
     int precision;
-    double *ke_part;             // [kKePer * nchunk]
+    double *ke_part;             // [kKePer * nchunk], and [nchunk] totals behind them (put_kinetic)
     double *thermo;              // [replica][TH_COUNT]
     int64_t *budget;             // [replica] steps left; a replica with none left is held still
     int64_t *steps;              // [replica] steps done
@@ -605,9 +600,10 @@ void launch_pairs(const Launch &L, unsigned long long *stats, hipStream_t stream
 
 // Per-particle sums of pair records in row order (fixed, atomic-free):
 // F, tau, U_i, W_i; with kick != 0 also the closing velocity/angular
-// momentum kick and then the step tail of every replica (Nose-Hoover half
-// steps, step budget and count, rebuild scheduling), which also carries
-// the pair entries and the tile plan of the step's list build.
+// momentum kick, the neighbour rows of the step's list build, and the step's
+// bookkeeping (step budget and count, rebuild scheduling); where steps are
+// not folded then the replica tail, which takes the bookkeeping over and
+// carries the thermostat half steps, the pair entries and the tile plan.
 void launch_gather(const Launch &L, bool kick, hipStream_t stream);
 
 // Integrator pieces.  launch_begin prepares the opening half step of a

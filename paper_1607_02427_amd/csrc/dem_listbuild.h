@@ -1,6 +1,6 @@
 // Device parts of a list build, shared by the list kernels of a build
 // outside a step (dem_lists.hip) and by the step kernels that carry a build
-// inside a step (dem_force.hip):
+// inside a step (dem_force.hip, dem_integrate.hip):
 //   * nbr_rows: the neighbour rows of 4 particles by one wavefront (16
 //     lanes per particle);
 //   * fill_part: the pair offsets and pair entries of a quarter of a chunk
@@ -64,8 +64,9 @@ __device__ inline unsigned long long lanes_below()
 }
 
 // Does this build take replica r?  (LISTS_REFILL: every live replica that
-// has lists; LISTS_STEP: a replica whose step rebuilds and has steps left.)
-__device__ inline bool building(int mode, int r, const SysParams &p, const int32_t *fl, const int64_t *budget)
+// has lists; LISTS_STEP: a replica whose step rebuilds and has steps left,
+// FLAG_BUILD.)
+__device__ inline bool building(int mode, int r, const SysParams &p, const int32_t *fl)
 {
     if (!p.live) return false;
     if (mode == LISTS_STEP) return fl[FLAG_BUILD] != 0;

@@ -35,14 +35,14 @@ using lb::kNbrPer;
 
 // Cells from the current positions (builds outside a step).
 __global__ void __launch_bounds__(kBlock) k_assign(BatchParams b, const SysParams *reps, StatePtrs s, ListPtrs l,
-                                                      const int64_t *budget, int mode)
+                                                      int mode)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int c = i / kChunk;
     const int r = __builtin_amdgcn_readfirstlane(c < b.nchunk ? l.chunk_rep[c] : -1);
     if (r < 0) return;
     const SysParams &p = reps[r];
-    if (!lb::building(mode, r, p, l.flags + r * FLAG_COUNT, budget) || i >= p.off + p.n) return;
+    if (!lb::building(mode, r, p, l.flags + r * FLAG_COUNT) || i >= p.off + p.n) return;
     if (i == p.off) l.flags[r * FLAG_COUNT + FLAG_NEWPAIRS] = 0;  // the row workgroups add the replica's pairs
     if (i % kChunk == 0) l.ctot[c] = 0;                           // and the chunk's
     cell_insert(p, l, i, s.x[i], s.y[i], p.dim == 3 ? s.z[i] : 0.0);
@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(kBlock) k_assign(BatchParams b, const SysParam
 // Neighbour rows (lb::nbr_rows), one wavefront per 4 particles.
 template <int DIM>
 __global__ void __launch_bounds__(64) k_nbr(BatchParams b, const SysParams *reps, StatePtrs s, ListPtrs l,
-                                               const int64_t *budget, int mode)
+                                               int mode)
 {
     __shared__ lb::RowBuf buf;
     const int vb = xcd_block(blockIdx.x, gridDim.x);  // neighbouring rows share lines of nbr
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(64) k_nbr(BatchParams b, const SysParams *reps
     if (r < 0) return;
     const SysParams &p = reps[r];
     int32_t *fl = l.flags + r * FLAG_COUNT;
-    if (!lb::building(mode, r, p, fl, budget)) return;
+    if (!lb::building(mode, r, p, fl)) return;
     lb::nbr_rows<DIM>(b, p, s, l, fl, vb, buf);
 }
 
@@ -68,20 +68,20 @@ __global__ void __launch_bounds__(64) k_nbr(BatchParams b, const SysParams *reps
 // first recomputes the tile plan.
 static_assert(kBlock == 64 * lb::kFillParts, "a wavefront per quarter of a chunk");
 __global__ void __launch_bounds__(kBlock) k_fill(BatchParams b, const SysParams *reps, ListPtrs l,
-                                                    const int64_t *budget, int mode, int clear_cells)
+                                                    int mode, int clear_cells)
 {
     __shared__ int part[kBlock];
     if (blockIdx.x == 0)
         lb::plan<kBlock>(b, reps, l, part, [&](int r) {
             return mode != LISTS_PLAN && mode != LISTS_REFILL &&
-                   lb::building(mode, r, reps[r], l.flags + r * FLAG_COUNT, budget);
+                   lb::building(mode, r, reps[r], l.flags + r * FLAG_COUNT);
         });
     if (mode == LISTS_PLAN) return;
     const int c = xcd_block(blockIdx.x, gridDim.x);
     const int r = __builtin_amdgcn_readfirstlane(c < b.nchunk ? l.chunk_rep[c] : -1);
     if (r < 0) return;
     const SysParams &p = reps[r];
-    if (!lb::building(mode, r, p, l.flags + r * FLAG_COUNT, budget)) return;
+    if (!lb::building(mode, r, p, l.flags + r * FLAG_COUNT)) return;
     lb::fill_part(b, p, l, c, (int)threadIdx.x / 64, mode == LISTS_REFILL, clear_cells != 0);
 }
 
@@ -92,19 +92,19 @@ void launch_lists(const Launch &L, int mode, hipStream_t stream)
     if (L.b.nrep == 0) return;
     const int nb = blocks_for(L.b.nchunk * kChunk);
     if (mode == LISTS_PLAN || L.b.nchunk == 0) {
-        k_fill<<<1, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, LISTS_PLAN, 0);
+        k_fill<<<1, kBlock, 0, stream>>>(L.b, L.reps, L.l, LISTS_PLAN, 0);
         return;
     }
     const int nf = pad8(L.b.nchunk);
     if (mode == LISTS_REFILL) {
-        k_fill<<<nf, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, LISTS_REFILL, 0);
+        k_fill<<<nf, kBlock, 0, stream>>>(L.b, L.reps, L.l, LISTS_REFILL, 0);
         return;
     }
-    k_assign<<<nb, kBlock, 0, stream>>>(L.b, L.reps, L.s, L.l, L.budget, mode);
+    k_assign<<<nb, kBlock, 0, stream>>>(L.b, L.reps, L.s, L.l, mode);
     const int nbn = pad8(L.b.nchunk * (kChunk / kNbrPer));
-    if (L.b.dim == 3) k_nbr<3><<<nbn, 64, 0, stream>>>(L.b, L.reps, L.s, L.l, L.budget, mode);
-    else k_nbr<2><<<nbn, 64, 0, stream>>>(L.b, L.reps, L.s, L.l, L.budget, mode);
-    k_fill<<<nf, kBlock, 0, stream>>>(L.b, L.reps, L.l, L.budget, mode, 1);
+    if (L.b.dim == 3) k_nbr<3><<<nbn, 64, 0, stream>>>(L.b, L.reps, L.s, L.l, mode);
+    else k_nbr<2><<<nbn, 64, 0, stream>>>(L.b, L.reps, L.s, L.l, mode);
+    k_fill<<<nf, kBlock, 0, stream>>>(L.b, L.reps, L.l, mode, 1);
 }
 
 }  // namespace dem

@@ -87,7 +87,7 @@ struct dem_system {
     bool counting = false;
     int pair_lanes = kDefaultPairLanes;  // pair-kernel shape: lanes per pair,
     int pair_grid = 1;                   // blocks per resident block slot
-    int pair_waves = kDefaultPairWaves;  // wavefronts per SIMD
+    int pair_waves = kDefaultPairWaves;  // wavefronts per SIMD as set (no kernel depends on it)
     int pair_sep = kDefaultPairSep;      // and lanes per pair of its separation stage;
     int pair_split = 0;                  // 1: search and force kernels instead of one
     bool pair_auto = true;               // the shape follows the rule of pick_shape until one is set or tuned
@@ -778,7 +778,6 @@ void refresh_batch(dem_system *h)
     b.nrep = 0;
     b.tab_slots = 1;
     b.pair_lanes = h->pair_lanes;
-    b.pair_waves = h->pair_waves;
     b.pair_split = h->pair_split;
     b.feature_cells = h->feature_cells;
     b.pair_sep = lane_per_pair(h) ? 1 : h->pair_sep;

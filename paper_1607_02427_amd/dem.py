@@ -411,9 +411,9 @@ class DemSystem:
         return {name: getattr(v, name) for name, _ in OutputView._fields_}
 
     def set_pair_shape(self, lanes: int, grid: int = 1, waves: int = 2, sep: int = 4, split: int = 0):
-        """Pair-kernel launch shape (8 or 16 lanes per pair, grid factor 1..4, 2 or 3 waves per SIMD, 4 or 16
-        separation lanes, split 0 or 1: one kernel, or a search kernel and a force kernel); results do not
-        change."""
+        """Pair-kernel launch shape (8 or 16 lanes per pair, grid factor 1..4, waves 2 or 3, which select the same
+        kernel, 4 or 16 separation lanes, split 0 or 1: one kernel, or a search kernel and a force kernel) instead
+        of the one the library picks; results do not change."""
         self._check(lib().dem_set_pair_shape(self.h, int(lanes), int(grid), int(waves), int(sep), int(split)),
                     "dem_set_pair_shape")
 
