@@ -75,7 +75,6 @@ struct Replica {
     int shape0 = 0, nshapes = 0;
     int edges = 0;               // of the shape that has the most
     long long slots = 0;         // pair slots at the automatic row capacity, whatever the capacity in use
-    bool packed = false;         // its polyhedra fill most of the box (kPackedFill)
 };
 
 }  // namespace
@@ -701,46 +700,6 @@ Launch make_launch(const dem_system *h)
 
 int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 
-// Volume of a rounded polyhedron (Steiner's formula: the inner body, slabs of
-// the rounding radius on its faces, wedges along its convex edges and a
-// sphere's worth at its vertices; exact for convex bodies).
-double body_volume(const HostShape &T)
-{
-    if (T.nf == 0) return 4.0 / 3.0 * M_PI * T.r * T.r * T.r;
-    // the face whose loop runs from vertex u to vertex v, or -1
-    auto face_of = [&](int u, int v) {
-        for (int f = 0; f < T.nf; ++f)
-            for (int k = T.foff[f]; k < T.foff[f + 1]; ++k)
-                if (T.floop[k] == u && T.floop[k + 1 < T.foff[f + 1] ? k + 1 : T.foff[f]] == v) return f;
-        return -1;
-    };
-    double vol = 4.0 / 3.0 * M_PI * T.r * T.r * T.r;
-    for (int f = 0; f < T.nf; ++f) {
-        HostVec twice = {0.0, 0.0, 0.0};
-        for (int k = T.foff[f]; k < T.foff[f + 1]; ++k) {
-            const HostVec c = hcross(hv(T.v[T.floop[k]]), hv(T.v[T.floop[k + 1 < T.foff[f + 1] ? k + 1 : T.foff[f]]]));
-            twice = {twice.x + c.x, twice.y + c.y, twice.z + c.z};
-        }
-        vol += 0.5 * hdot(twice, hv(T.fn[f])) * (T.fo[f] / 3.0 + T.r);
-    }
-    for (int e = 0; e < T.ne; ++e) {
-        const int f = face_of(T.e[e][0], T.e[e][1]), g = face_of(T.e[e][1], T.e[e][0]);
-        if (f < 0 || g < 0 || hdot(hv(T.fn[f]), hv(T.fc[g])) > T.fo[f]) continue;  // (a concave edge)
-        const double angle = std::acos(std::max(-1.0, std::min(1.0, hdot(hv(T.fn[f]), hv(T.fn[g])))));
-        vol += 0.5 * angle * 2.0 * T.eh[e] * T.r * T.r;
-    }
-    return vol;
-}
-// From this part of the box that its bodies fill, a system of polyhedra is
-// packed face to face, and its pairs have tens of problems for good.  In
-// FP64 such pairs are faster with 16 lanes: step times of 8000 cubes and of
-// flat and long boxes, 16 lanes over 8, 0.65-0.73 where they fill 0.90 to 0.96,
-// 0.80-0.86 at 0.87 to 0.92 with a wider gap, 0.90-0.93 at 0.79 to 0.88, 0.91-0.99
-// at 0.70 to 0.80, 0.92-1.06 at 0.4 to 0.7.  (With 8 lanes, which add up twice
-// as many of a pair's terms one after the other, cubes at 0.9 and more were
-// up to 1.18 times slower than the earlier kernel of 16 lanes.)
-constexpr double kPackedFill = 0.8;
-
 // The pair-kernel shape of a handle that nobody has set or tuned one for,
 // from the pair slots of its live replicas and their shapes.  Slots are
 // counted at the automatic row capacity (Replica::slots: 0.9 of the pairs
@@ -758,9 +717,8 @@ constexpr double kPackedFill = 0.8;
 //    as many pairs (4096 cubes 17.5 us against 19.8 with 16 lanes, 20,000
 //    pentagons 14.2 against 18.6),
 //  * but 16 where polyhedra whose features take 8 lanes many passes hold most
-//    of the slots: in FP64 those of more than 8 vertices or 24 edges and any
-//    that are packed (kPackedFill), in FP32 those of more than 24 edges.
-//    Which is faster goes with the contacts per
+//    of the slots: in FP64 those of more than 8 vertices or 24 edges, in FP32
+//    those of more than 24 edges.  Which is faster goes with the contacts per
 //    body: with many (a dense or near-lattice state, whose pairs have tens
 //    of problems) 16, with few (a dilute fluid, a handful) 8; the lines
 //    lie where 16 costs less in the one than it gains in the other.  Step
@@ -785,7 +743,7 @@ void pick_shape(dem_system *h)
     for (const Replica &R : h->reps) {
         if (!R.live) continue;
         slots += R.slots;
-        if (h->dim == 3 && (R.edges > 24 || (!f32 && (R.sp.wide != 0.0 || R.packed)))) many += R.slots;
+        if (h->dim == 3 && (R.edges > 24 || (R.sp.wide != 0.0 && !f32))) many += R.slots;
     }
     const bool few = slots <= (f32 ? 40960 : 32768);
     h->pair_grid = 1;
@@ -1306,12 +1264,6 @@ dem_status place_replica(dem_system *h, Replica &R, const std::vector<HostShape>
         for (int i = 0; i < n; ++i)
             if (sid[i] < 0 || sid[i] >= R.sp.n_shapes)
                 return fail(h, DEM_E_ARG, "shape_id[%d] = %d outside [0, %d)", i, sid[i], R.sp.n_shapes);
-        if (h->dim == 3) {
-            double volume[DEM_MAX_SHAPES] = {}, filled = 0.0;
-            for (int k = 0; k < R.nshapes; ++k) volume[k] = body_volume(tabs[k]);
-            for (int i = 0; i < n; ++i) filled += volume[sid[i]];
-            R.packed = filled >= kPackedFill * (R.sp.box[0] * R.sp.box[1] * R.sp.box[2]);
-        }
     }
     std::vector<ShapeTab<double>> t64((size_t)R.nshapes);
     std::vector<ShapeTab<float>> t32((size_t)R.nshapes);
