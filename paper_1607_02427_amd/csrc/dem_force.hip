@@ -811,15 +811,18 @@ struct alignas(16) WaveCtl {
 };
 // Whether the wavefront's 64 lanes share the solves of all its pairs (their
 // results pass through LDS), and how many results LDS holds at a time: half
-// a wavefront's with 8 lanes in FP64, so that two workgroups still share a
-// CU, and with a lane per pair in the separation stage, so that three do
-// (FP32).  Not with 8 lanes in 2D, where pairs have few problems.
-__host__ __device__ constexpr bool pooled(int dim, int lanes) { return lanes == 16 || dim == 3; }
+// a wavefront's with a lane per pair in the separation stage, so that three
+// workgroups share a CU (FP32).  Not with 8 lanes in 2D, where pairs have few
+// problems, nor in FP64: the 8 lanes of a pair add its results up one after
+// the other, twice as many each as with 16 and twice as wide as in FP32, which
+// costs more than the sharing saves where pairs have many (8000 cubes packed
+// face to face 331 us a step pooled, 177 not; in a fluid of volume fraction 0.4
+// 37.8 and 36.0; 8000 icosahedra in a gas 40.3 and 42.1, but those take 16),
+// and the results' LDS left one workgroup a CU with the feature cells (those
+// cubes 498 and 209).
 template <typename T>
-__host__ __device__ constexpr int pool_results(int lanes, int sep)
-{
-    return lanes == 8 && (sizeof(T) == 8 || sep == 1) ? 32 : 64;
-}
+__host__ __device__ constexpr bool pooled(int dim, int lanes) { return lanes == 16 || (dim == 3 && sizeof(T) == 4); }
+__host__ __device__ constexpr int pool_results(int sep) { return sep == 1 ? 32 : 64; }
 
 // One block of 4 waves takes a contiguous range of tiles (256 / SL pairs of
 // one replica each, 16, 64 or 256; wave w takes pairs (64 / SL) w .. (64 /
@@ -894,8 +897,8 @@ __global__ void __launch_bounds__(64 * kWaves, OCC) k_pairs(BatchParams b, const
     WaveCtl<kGroups> *ctl = reinterpret_cast<WaveCtl<kGroups> *>(geo + kWaves * kGeo);
     QueueEnt<SL> *qall = reinterpret_cast<QueueEnt<SL> *>(ctl + kWaves);
     // results of one pooled solve step, one per lane
-    constexpr bool kPool = pooled(DIM, GL);
-    constexpr int kRes = pool_results<T>(GL, SL);
+    constexpr bool kPool = pooled<T>(DIM, GL);
+    constexpr int kRes = pool_results(SL);
     constexpr bool kSeq = GL == 16;  // the prefilter takes both bodies' vertices (faces) in one sequence
     Acc<T> *pres = reinterpret_cast<Acc<T> *>(qall + kWaves * kEnt);
     // the feature-cell form's per-group prefix and edge masks
@@ -2248,8 +2251,9 @@ size_t pair_kernel_lds(int precision, int dim, int tab_slots, int lanes, int sep
     const bool park = f32 ? parked<float>(dim, lanes, sep, stage) : parked<double>(dim, lanes, sep, stage);
     const size_t queue = park ? slots * pg : groups * pg + slots * qe;
     const size_t ctl = lanes == 8 ? sizeof(WaveCtl<8>) : sizeof(WaveCtl<4>);
-    const size_t acc = !pooled(dim, lanes) ? 0 : f32 ? pool_results<float>(lanes, sep) * sizeof(Acc<float>)
-                                                      : pool_results<double>(lanes, sep) * sizeof(Acc<double>);
+    const size_t acc = !(f32 ? pooled<float>(dim, lanes) : pooled<double>(dim, lanes))
+                           ? 0
+                           : pool_results(sep) * (f32 ? sizeof(Acc<float>) : sizeof(Acc<double>));
     const size_t en = kWaves * (64 / sep) * qe;  // entry slots
     if (stage == kSearchOnly)  // tables, replica, and the last workgroup's scan
         return en + (size_t)tab_slots * w + sizeof(RepLds) + sizeof(int) * 64 * kWaves;

@@ -36,7 +36,7 @@ __host__ __device__ constexpr int pair_tile(int sep_lanes) { return kPairWaves *
 // tiles four times as long, of which a workgroup has to have several for the
 // last ones not to leave the chip idle.  Four lanes against one, in us:
 // 262,144 octahedra (6.8 million slots) 452 and 359, 131,072 L-prisms (3.1
-// million) 257 and 239, in FP64 384 and 349, 262,144 tetrahedra (7.3 million)
+// million) 257 and 239, in FP64 490 and 421, 262,144 tetrahedra (7.3 million)
 // 604 and 533; but 131,072 cubes (2.4 million) 164 and 169, 64,000 tetrahedra
 // (1.8 million) 140 and 159, 32,768 octahedra (0.85 million) 76 and 82.
 // Bodies of one vertex have no feature stage to speak of, and gain earlier:

@@ -702,7 +702,7 @@ int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 
 // The pair-kernel shape of a handle that nobody has set or tuned one for,
 // from the pair slots of its live replicas and their shapes.  Slots are
-// counted at the automatic row capacity (Replica::slots: 0.9 of the pairs
+// counted at the automatic row capacity (Replica::slots: 1.8 times the pairs
 // that the density gives within the list radius, and 8 per body), for which
 // the limits were measured: a measure of the pairs that neither a caller's
 // nbr_capacity nor another replica's rows move.
@@ -711,10 +711,10 @@ int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 //    system's time (216 cubes 12.6 us against 15.9 with 8 lanes and 19.3
 //    with 16 lanes and tiles of 64; 2000 cubes, 36,864 slots, 15.0 against
 //    15.7; 3000 cubes, 54,144 slots, 19.4 against 16.7).  In FP64 the lines
-//    cross earlier (1000 cubes, 18,432 slots, 13.9 against 15.0; 2000 cubes
-//    21.8 against 14.8).
-//  * Otherwise 8 lanes, whose rounds share their culls and solves over twice
-//    as many pairs (4096 cubes 17.5 us against 19.8 with 16 lanes, 20,000
+//    cross earlier (1000 cubes, 18,432 slots, 13.6 against 16.2; 2000 cubes
+//    22.0 against 16.3).
+//  * Otherwise 8 lanes, whose rounds take twice as many pairs (4096 cubes 17.0
+//    us against 19.6 with 16 lanes, in FP64 18.1 against 21.1, 20,000
 //    pentagons 14.2 against 18.6),
 //  * but 16 where polyhedra whose features take 8 lanes many passes hold most
 //    of the slots: in FP64 those of more than 8 vertices or 24 edges, in FP32
@@ -726,15 +726,16 @@ int tiles_of(int pcap, int tile) { return (pcap + tile - 1) / tile; }
 //    first 8000 steps and of 3000 to 20,000 bodies, from a lattice gas of
 //    volume fraction 0.35 to 0.4, and from a contact lattice: FP32
 //    icosahedra 0.94-1.03 and 0.87-1.05, 14- and 16-vertex antiprisms
-//    0.89-1.03 and 0.77-0.90; FP64 L-prisms 0.91-1.14 and 0.70-1.13, hexagonal
-//    and octagonal prisms 0.98-1.10 and 0.73-0.84, icosahedra 0.97-1.03 and
-//    0.66-1.06.  Of fewer features the gas loses more than the lattice gains:
+//    0.89-1.03 and 0.77-0.90; FP64 L-prisms 0.93-1.24 and 0.69-1.23, hexagonal
+//    and octagonal prisms 0.94-1.13 and 0.73-0.94, antiprisms 0.84-1.08 and
+//    0.58-0.89, icosahedra 0.86-1.02 and 0.96-1.18.  Of fewer features 8 is the
+//    faster in both or loses less: FP64 cubes 1.00-1.18 and 1.05-1.30,
 //    FP32 hexagonal and octagonal prisms 0.97-1.10 and 0.87-0.92, L-prisms
 //    1.05-1.09 and 0.92-1.05.  Polygons are with 8 lanes throughout (squares
 //    to 16-gons in both precisions 0.94-1.14 and 1.09-1.43: planar pairs have
 //    few problems).
 //    A batch of which such bodies hold a part gains from 8 (24 systems of
-//    cubes, tetrahedra and L-prisms in FP64, 201 us against 225).
+//    cubes, tetrahedra and L-prisms in FP64, 202 us against 228).
 void pick_shape(dem_system *h)
 {
     if (!h->pair_auto) return;
