@@ -230,11 +230,14 @@ dem_status dem_set_barostat(dem_handle h, double veps);
 /* Copies the lists to host buffers (synchronises): cell_start[n_cells+1],
  * cell_particles[n], nbr[capacity * n] column-major (row i of particle i is
  * nbr[k * n + i], k < n_nbr[i], ascending in j) and n_nbr[n].  Any pointer
- * may be NULL.  dims receives {cells_x, cells_y, cells_z, capacity}. */
+ * may be NULL.  dims receives {cells_x, cells_y, cells_z, capacity}, the
+ * cells of the last build (under DEM_NPT they follow its box; cell_start has
+ * one entry more than them). */
 dem_status dem_copy_lists(dem_handle h, int32_t *cell_start, int32_t *cell_particles, int32_t *nbr, int32_t *n_nbr,
                           int32_t *dims);
 
-/* Neighbour-list radius and number of cells. */
+/* Neighbour-list radius, number of cells (under DEM_NPT at creation, the most
+ * that any later box has) and row capacity. */
 dem_status dem_list_info(dem_handle h, double *r_list, int32_t *n_cells, int32_t *capacity);
 
 /* Work counters accumulated by counted force evaluations since the last

@@ -1439,7 +1439,13 @@ dem_status copy_lists(dem_system *h, int r, int32_t *cell_start, int32_t *cell_p
     if (n_nbr && n)
         HIPCHK(h, hipMemcpyAsync(n_nbr, h->lst.n_nbr + off, sizeof(int32_t) * n, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
-    const int ncell = R.sp.ncell;
+    // particles' cells are of the grid of the last build, which under the
+    // barostat is that of the box it was made in (set_box), not of today's
+    int nc[3] = {R.sp.nc[0], R.sp.nc[1], R.sp.nc[2]};
+    if (R.sp.ensemble == DEM_NPT)
+        for (int a = 0; a < R.sp.dim; ++a)
+            nc[a] = std::max(1, std::min(R.sp.nc0[a], (int)std::floor(R.sp.box_build[a] / R.sp.rlist)));
+    const int ncell = nc[0] * nc[1] * nc[2];
     std::vector<int32_t> start((size_t)ncell + 1, 0);
     for (size_t i = 0; i < n; ++i) start[(size_t)pcell[i] + 1] += 1;
     for (int c = 0; c < ncell; ++c) start[(size_t)c + 1] += start[c];
@@ -1452,9 +1458,7 @@ dem_status copy_lists(dem_system *h, int r, int32_t *cell_start, int32_t *cell_p
         for (size_t i = 0; i < n; ++i)
             for (int k = 0; k < n_nbr[i]; ++k) nbr[(size_t)k * n + i] -= (int32_t)off;
     if (dims) {
-        dims[0] = R.sp.nc[0];
-        dims[1] = R.sp.nc[1];
-        dims[2] = R.sp.nc[2];
+        for (int a = 0; a < 3; ++a) dims[a] = nc[a];
         dims[3] = h->bp.cap;
     }
     return DEM_OK;
@@ -1891,7 +1895,8 @@ dem_status dem_list_info(dem_handle h, double *r_list, int32_t *n_cells, int32_t
     if (!h) return fail(nullptr, DEM_E_ARG, "null handle");
     if (!valid_replica(h, 0)) return fail(h, DEM_E_ARG, "no replica 0");
     if (r_list) *r_list = h->reps[0].r_list;
-    if (n_cells) *n_cells = h->reps[0].sp.ncell;
+    const SysParams &sp = h->reps[0].sp;  // (a grid never has more cells than at creation)
+    if (n_cells) *n_cells = sp.nc0[0] * sp.nc0[1] * sp.nc0[2];
     if (capacity) *capacity = h->bp.cap;
     return DEM_OK;
 }

@@ -284,7 +284,7 @@ def _lists_np(call, n, ncell, cap):
     dims = np.zeros(4, np.int32)
     call(cs.ctypes.data_as(_ip), cp.ctypes.data_as(_ip), nb.ctypes.data_as(_ip), nn.ctypes.data_as(_ip),
          dims.ctypes.data_as(_ip))
-    return dict(dims=dims[:3].copy(), capacity=int(dims[3]), cell_start=cs, cell_particles=cp[:n],
+    return dict(dims=dims[:3].copy(), capacity=int(dims[3]), cell_start=cs[: int(np.prod(dims[:3])) + 1], cell_particles=cp[:n],
                 nbr=nb[: cap * n].reshape(cap, n) if n else nb[:0].reshape(cap, 0), n_nbr=nn[:n])
 
 
