@@ -13,14 +13,15 @@ pytestmark = pytest.mark.skipif(not os.path.exists(dem.LIB_PATH), reason="libdem
 FUSED, FORCES = 0, 2
 
 
+# (a lane per pair in the separation stage: 3D without the feature cells)
+FORMS = [(dim, cells, *form) for dim in (2, 3) for cells in (0, 1)
+         for form in ((16, 4, FUSED), (8, 4, FUSED), (16, 16, FUSED), (8, 1, FUSED), (16, 4, FORCES), (8, 4, FORCES))
+         if form[1] != 1 or (dim == 3 and not cells)]
+
+
 @pytest.mark.parametrize("precision", [dem.DEM_FP32, dem.DEM_FP64])
-@pytest.mark.parametrize("dim", [2, 3])
-@pytest.mark.parametrize("cells", [0, 1])
-@pytest.mark.parametrize("lanes,sep,stage", [(16, 4, FUSED), (8, 4, FUSED), (16, 16, FUSED), (8, 1, FUSED), (16, 4, FORCES),
-                                             (8, 4, FORCES)])
+@pytest.mark.parametrize("dim,cells,lanes,sep,stage", FORMS)
 def test_workgroups_per_cu(precision, dim, cells, lanes, sep, stage):
-    if sep == 1 and (cells or dim == 2):
-        pytest.skip("no such form")
     f = dem.lib()["_ZN3dem15pair_kernel_ldsEiiiiiii"]  # dem::pair_kernel_lds
     f.restype = C.c_size_t
     lds = f(precision, dim, 1, lanes, sep, stage, cells)
